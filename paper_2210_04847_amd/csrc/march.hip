@@ -30,8 +30,10 @@
 // correctly rounded + - * / sqrt, min/max, ldexp and float->int truncation of
 // non-negative values.
 #include <cmath>
+#include <type_traits>
 
 #include "common.h"
+#include "halo.h"
 #include "lattice.h"
 #include "scan.h"
 
@@ -558,9 +560,6 @@ __global__ __launch_bounds__(WAVES * kWave) void fill_uniform_kernel(
         spans = ray_span<LOOKUP>(mine, rays_o, rays_d, grid_id, g, c, p);
     }
     bool overflow = false;
-    // the box lookup's count pass leaves the plain traversal's masks also
-    // when it marched by segments
-    constexpr bool kFillSkip = SKIP && !kSegments<LOOKUP, SKIP>;
     if (masks != nullptr) {
         // kFillBatch rays at a time: their ranges and masks are all loaded
         // before any of their samples is stored.  A wave waits on its loads
@@ -613,7 +612,7 @@ __global__ __launch_bounds__(WAVES * kWave) void fill_uniform_kernel(
                                                 t_starts, t_ends, overflow, mk[b]);
                 }
                 if (written < limit) {  // samples past the stored chunks: traverse from there
-                    march_ray_uniform<LOOKUP, true, kFillSkip>(r, span, rays_o, rays_d, bits, skip, g, p, start,
+                    march_ray_uniform<LOOKUP, true, SKIP>(r, span, rays_o, rays_d, bits, skip, g, p, start,
                                                                limit, capacity, ray_indices, t_starts, t_ends,
                                                                overflow, nullptr, 0, n_masks, written);
                 }
@@ -629,15 +628,8 @@ __global__ __launch_bounds__(WAVES * kWave) void fill_uniform_kernel(
         const int limit = uniform<int>(packed_info[2 * r + 1]);
         if (limit == 0) continue;
         const RaySpan span = read_span(spans, i / WAVES);
-        if constexpr (kSegments<LOOKUP, SKIP>) {
-            // no stored masks: the segment count pass finds the samples with
-            // fewer lookups; its ballots are written here directly
-            march_ray_uniform<LOOKUP, true, false>(r, span, rays_o, rays_d, bits, skip, g, p, start, limit,
-                                                   capacity, ray_indices, t_starts, t_ends, overflow);
-        } else {
-            march_ray_uniform<LOOKUP, true, SKIP>(r, span, rays_o, rays_d, bits, skip, g, p, start, limit, capacity,
-                                                  ray_indices, t_starts, t_ends, overflow);
-        }
+        march_ray_uniform<LOOKUP, true, SKIP>(r, span, rays_o, rays_d, bits, skip, g, p, start, limit, capacity,
+                                              ray_indices, t_starts, t_ends, overflow);
     }
     if (overflow && status != nullptr) *status = NACC_ECAPACITY;
 }
@@ -1028,10 +1020,10 @@ __device__ __forceinline__ uint64_t cone_chunk_bits(const uint32_t* __restrict__
 
 constexpr int kTaskThreads = 256;
 
-template <int LOOKUP, bool SKIP>
+template <int LOOKUP>
 __global__ __launch_bounds__(kTaskThreads) void count_cone_chunks_kernel(
     const float* __restrict__ rays_o, const float* __restrict__ rays_d, const int32_t* __restrict__ grid_id,
-    int64_t n_rays, const uint32_t* __restrict__ bits, const uint8_t* __restrict__ skip, GridK g, StepK p,
+    int64_t n_rays, const uint32_t* __restrict__ bits, GridK g, StepK p,
     int n_masks, const float* __restrict__ chunk_t, const float* __restrict__ t_far_in,
     uint64_t* __restrict__ masks, int32_t* __restrict__ extra) {
     const int64_t task = static_cast<int64_t>(blockIdx.x) * kTaskThreads + threadIdx.x;
@@ -1053,16 +1045,15 @@ __global__ __launch_bounds__(kTaskThreads) void count_cone_chunks_kernel(
     uint32_t word0;
     grid_of_ray<LOOKUP>(grid_id, r, g, word0);  // valid: the ray has candidates
     SkipRay sk{};
-    if (SKIP) sk = skip_ray(g, o, d, t_far);
     float skip_end = -INFINITY;
     bool ended;
-    masks[task] = cone_chunk_bits<LOOKUP, SKIP>(bits, skip, g, sk, skip_end, word0, o, d, t, t_far, p, ended);
+    masks[task] = cone_chunk_bits<LOOKUP, false>(bits, nullptr, g, sk, skip_end, word0, o, d, t, t_far, p, ended);
     if (j == n_masks - 1 && !ended) {
         // past the stored chunks: count the rest of the ray here
         int count = 0;
         for (int k0 = n_masks * kWave; k0 < kMaxCandidates; k0 += kWave) {
             count += __popcll(
-                cone_chunk_bits<LOOKUP, SKIP>(bits, skip, g, sk, skip_end, word0, o, d, t, t_far, p, ended));
+                cone_chunk_bits<LOOKUP, false>(bits, nullptr, g, sk, skip_end, word0, o, d, t, t_far, p, ended));
             if (ended) break;
         }
         extra[r] = count;
@@ -1124,10 +1115,10 @@ __global__ __launch_bounds__(kRaysPerBlock) void cone_counts_kernel(int64_t n_ra
     if (threadIdx.x == 0) block_sums[blockIdx.x] = sum;
 }
 
-template <int LOOKUP, bool SKIP>
+template <int LOOKUP>
 __global__ __launch_bounds__(kTaskThreads) void fill_cone_chunks_kernel(
     const float* __restrict__ rays_o, const float* __restrict__ rays_d, const int32_t* __restrict__ grid_id,
-    int64_t n_rays, const uint32_t* __restrict__ bits, const uint8_t* __restrict__ skip, GridK g, StepK p,
+    int64_t n_rays, const uint32_t* __restrict__ bits, GridK g, StepK p,
     int n_masks, const float* __restrict__ chunk_t, const float* __restrict__ t_far_in,
     const uint64_t* __restrict__ masks, const int32_t* __restrict__ packed_info, int64_t capacity,
     float* __restrict__ t_starts, float* __restrict__ t_ends, int32_t* __restrict__ status) {
@@ -1182,12 +1173,11 @@ __global__ __launch_bounds__(kTaskThreads) void fill_cone_chunks_kernel(
         uint32_t word0;
         grid_of_ray<LOOKUP>(grid_id, r, g, word0);
         SkipRay sk{};
-        if (SKIP) sk = skip_ray(g, o, d, t_far);
-        float skip_end = -INFINITY;
+            float skip_end = -INFINITY;
         for (int k0 = n_masks * kWave; k0 < kMaxCandidates && idx < limit; k0 += kConeBatch) {
             float tb[kConeBatch + 1];
             const int n_valid = cone_steps(t, t_far, p, tb);
-            const uint32_t hits = cone_hits<LOOKUP, SKIP>(bits, skip, g, sk, skip_end, word0, o, d, tb, n_valid) &
+            const uint32_t hits = cone_hits<LOOKUP, false>(bits, nullptr, g, sk, skip_end, word0, o, d, tb, n_valid) &
                                   ((1u << n_valid) - 1u);
 #pragma unroll
             for (int u = 0; u < kConeBatch; ++u) {
@@ -1762,10 +1752,27 @@ struct Layout {
     int64_t chunk_t_off, t_far_off, extra_off;  // cone steps only (0 otherwise)
     int64_t base_off, seg_t_off;                // cone steps, segment passes
     int64_t live_off, tsum_off, tlist_off;      // cone steps, the task list of the segment passes
+    int64_t halo_off;                           // halo bits built by the count pass (0: none)
     int64_t bytes;
 };
 
 int64_t align256(int64_t b) { return ((b + 255) / 256) * 256; }
+
+// Whether a count pass without a skip buffer builds halo bits of its own
+// (halo.h, 4.5 us up to a few 128^3 grids, 23 us for 64 of them) in the
+// workspace, so as to look up only the candidates near occupied cells.
+// Uniform steps through the box gain 0.3 ns a ray (128^3: 110 -> 106 us a
+// call at 32,768 rays, 317 -> 243 us at 262,144; even at 16,384, 64 grids
+// even near 200,000).  Cone steps gain from the smallest batches on (they
+// also lose a separate expansion of the ray indices; cascades 96 -> 88 us at
+// 256 rays, 544 -> 281 us at 262,144; contraction 132 -> 124 and 1,391 ->
+// 480 us) unless a few rays are spread over many grids.
+bool builds_halo(int64_t n_rays, int n_masks, const nacc_grid_desc& grid, const nacc_march_params& p) {
+    if (n_masks == 0) return false;
+    const int64_t words = halo_words(grid.res) * grid.n_grids;
+    if (p.cone > 0.0f) return words <= 65536 + 16 * n_rays;
+    return grid.lookup == NACC_LOOKUP_AABB && n_rays >= 16384 + words / 4;
+}
 
 Layout workspace_layout(int64_t n_rays, const nacc_grid_desc& grid, const nacc_march_params& p) {
     Layout l;
@@ -1792,6 +1799,11 @@ Layout workspace_layout(int64_t n_rays, const nacc_grid_desc& grid, const nacc_m
         l.tlist_off = l.tsum_off + align256((n_sums + 1 + scan_scratch_values(n_sums)) *
                                             static_cast<int64_t>(sizeof(int64_t)));
         l.bytes = l.tlist_off + align256(n_rays * l.n_masks * static_cast<int64_t>(sizeof(int32_t)));
+    }
+    l.halo_off = 0;
+    if (builds_halo(n_rays, l.n_masks, grid, p)) {
+        l.halo_off = l.bytes;
+        l.bytes += align256(halo_words(grid.res) * 4 * grid.n_grids);
     }
     return l;
 }
@@ -1838,24 +1850,25 @@ const uint32_t* halo_of(const uint8_t* skip, const GridK& g) {
 }
 
 template <int LOOKUP, bool SKIP, int WAVES>
-void launch_count_uniform(int64_t nb, hipStream_t s, const float* o, const float* d, const int32_t* gid, int64_t n,
-                          const uint32_t* bits, const uint8_t* skip, const GridK& g, const ClipK& c, const StepK& p,
-                          int32_t* packed, int64_t* sums, uint64_t* masks, int n_masks) {
+void launch_count_uniform(const uint8_t* skip, const uint32_t* halo, int64_t nb, hipStream_t s, const float* o,
+                          const float* d, const int32_t* gid, int64_t n, const uint32_t* bits, const GridK& g,
+                          const ClipK& c, const StepK& p, int32_t* packed, int64_t* sums, uint64_t* masks,
+                          int n_masks) {
     const int split = march_split(nb);
     if (split > 1) {
         hipLaunchKernelGGL(zero_sums_kernel, dim3(static_cast<unsigned>((nb + 255) / 256)), dim3(256), 0, s, sums,
                            nb);
     }
     hipLaunchKernelGGL((count_uniform_kernel<LOOKUP, SKIP, WAVES>), dim3(static_cast<unsigned>(nb * split)),
-                       dim3(WAVES * kWave), 0, s, o, d, gid, n, bits, skip, halo_of(skip, g), g, c, p, packed, sums,
-                       masks, n_masks, split);
+                       dim3(WAVES * kWave), 0, s, o, d, gid, n, bits, skip, halo, g, c, p, packed, sums, masks,
+                       n_masks, split);
 }
 
 template <int LOOKUP, bool SKIP, int WAVES>
-void launch_fill_uniform(int64_t nb, hipStream_t s, const float* o, const float* d, const int32_t* gid, int64_t n,
-                         const uint32_t* bits, const uint8_t* skip, const GridK& g, const ClipK& c, const StepK& p,
-                         const int32_t* packed, int64_t capacity, int32_t* ri, float* ts, float* te, int32_t* status,
-                         const uint64_t* masks, int n_masks) {
+void launch_fill_uniform(const uint8_t* skip, int64_t nb, hipStream_t s, const float* o, const float* d,
+                         const int32_t* gid, int64_t n, const uint32_t* bits, const GridK& g, const ClipK& c,
+                         const StepK& p, const int32_t* packed, int64_t capacity, int32_t* ri, float* ts, float* te,
+                         int32_t* status, const uint64_t* masks, int n_masks) {
     const int split = march_split(nb);
     hipLaunchKernelGGL((fill_uniform_kernel<LOOKUP, SKIP, WAVES>), dim3(static_cast<unsigned>(nb * split)),
                        dim3(WAVES * kWave), 0, s, o, d, gid, n, bits, skip, g, c, p, packed, capacity, ri, ts, te,
@@ -1867,115 +1880,130 @@ unsigned task_blocks(int n_masks, int64_t n_rays) {
 }
 
 // The segment passes run over a task list of the chunks the starts pass
-// could not prove empty: contraction lookup with halo bits, task ids within
-// int32.
-template <int LOOKUP, bool SKIP>
+// could not prove empty: contraction lookup, task ids within int32.  The
+// culling and the list's scan cost 60 us, the segment passes they save take
+// less up to 4 million chunks (40 chunks a ray: 126 against 168 us a call at
+// 4,096 rays, 220 against 226 us at 65,536, 582 against 480 us at 262,144).
+constexpr int64_t kMinListedTasks = int64_t{1} << 22;
+
+template <int LOOKUP>
 bool cone_task_list(const ConeWork& cw, int64_t n_rays) {
-    return SKIP && LOOKUP == NACC_LOOKUP_CONTRACT && cw.n_masks > 0 &&
-           static_cast<int64_t>(cw.n_masks) * n_rays <= INT32_MAX;
+    const int64_t tasks = static_cast<int64_t>(cw.n_masks) * n_rays;
+    return LOOKUP == NACC_LOOKUP_CONTRACT && tasks >= kMinListedTasks && tasks <= INT32_MAX;
+}
+
+template <int LOOKUP>
+void launch_count_cone(const ConeWork& cw, const uint32_t* halo, int64_t nb, hipStream_t s, const float* o,
+                       const float* d, const int32_t* gid, int64_t n, const uint32_t* bits, const GridK& g,
+                       const ClipK& c, const StepK& p, int32_t* packed, int64_t* sums, uint64_t*, int) {
+    const bool segments = halo != nullptr;
+    const bool listed = segments && cone_task_list<LOOKUP>(cw, n);
+    const ConeTable tab = cone_table(p, cw.n_masks);
+    if (listed) {
+        hipLaunchKernelGGL((cone_starts_kernel<LOOKUP, true>), dim3(nb), dim3(kRaysPerBlock), 0, s, o, d, gid, n, g, c,
+                           p, cw.n_masks, cw.chunk_t, cw.t_far, cw.extra, halo, cw.live_chunks, cw.task_sums, tab);
+        const int64_t n_sums = nb * cw.n_masks;
+        scan_exclusive(cw.task_sums, n_sums, cw.task_sums + n_sums, cw.task_sums + n_sums + 1, s);
+        hipLaunchKernelGGL(task_list_kernel, dim3(nb), dim3(kRaysPerBlock), 0, s, cw.task_sums, n, cw.n_masks,
+                           cw.live_chunks, cw.task_list);
+    } else {
+        hipLaunchKernelGGL((cone_starts_kernel<LOOKUP, false>), dim3(nb), dim3(kRaysPerBlock), 0, s, o, d, gid, n, g,
+                           c, p, cw.n_masks, cw.chunk_t, cw.t_far, cw.extra, nullptr, nullptr, nullptr, tab);
+    }
+    if (cw.n_masks > 0 && segments) {
+        hipLaunchKernelGGL((count_cone_segments_kernel<LOOKUP>), dim3(task_blocks(cw.n_masks, n)), dim3(kTaskThreads),
+                           0, s, o, d, gid, n, bits, halo, g, p, cw.n_masks, cw.chunk_t, cw.t_far, cw.masks, cw.extra,
+                           cw.seg_t, listed ? cw.task_list : nullptr,
+                           listed ? cw.task_sums + nb * cw.n_masks : nullptr, tab);
+    } else if (cw.n_masks > 0) {
+        hipLaunchKernelGGL((count_cone_chunks_kernel<LOOKUP>), dim3(task_blocks(cw.n_masks, n)), dim3(kTaskThreads), 0,
+                           s, o, d, gid, n, bits, g, p, cw.n_masks, cw.chunk_t, cw.t_far, cw.masks, cw.extra);
+    }
+    hipLaunchKernelGGL(cone_counts_kernel, dim3(nb), dim3(kRaysPerBlock), 0, s, n, cw.n_masks, p.max_per_ray, cw.masks,
+                       cw.extra, packed, sums, segments ? cw.chunk_base : nullptr,
+                       listed ? cw.live_chunks : nullptr, segments ? cw.live_chunks : nullptr);
+}
+
+template <int LOOKUP, bool SKIP, typename... A>
+void launch_count_waves(A&&... a) {
+    switch (tuning().march_waves_per_group) {
+        case 1: launch_count_uniform<LOOKUP, SKIP, 1>(a...); break;
+        case 2: launch_count_uniform<LOOKUP, SKIP, 2>(a...); break;
+        case 8: launch_count_uniform<LOOKUP, SKIP, 8>(a...); break;
+        case 16: launch_count_uniform<LOOKUP, SKIP, 16>(a...); break;
+        default: launch_count_uniform<LOOKUP, SKIP, 4>(a...); break;
+    }
 }
 
 template <int LOOKUP, bool SKIP>
-void launch_count_impl(const ConeWork* cw, int64_t nb, hipStream_t s, const float* o, const float* d,
-                       const int32_t* gid, int64_t n, const uint32_t* bits, const uint8_t* skip, const GridK& g,
-                       const ClipK& c, const StepK& p, int32_t* packed, int64_t* sums, uint64_t* masks, int n_masks) {
-    if (cw != nullptr) {  // cone steps
-        const bool listed = cone_task_list<LOOKUP, SKIP>(*cw, n);
-        const ConeTable tab = cone_table(p, cw->n_masks);
-        if (listed) {
-            hipLaunchKernelGGL((cone_starts_kernel<LOOKUP, true>), dim3(nb), dim3(kRaysPerBlock), 0, s, o, d, gid, n,
-                               g, c, p, cw->n_masks, cw->chunk_t, cw->t_far, cw->extra, halo_of(skip, g),
-                               cw->live_chunks, cw->task_sums, tab);
-            const int64_t n_sums = nb * cw->n_masks;
-            scan_exclusive(cw->task_sums, n_sums, cw->task_sums + n_sums, cw->task_sums + n_sums + 1, s);
-            hipLaunchKernelGGL(task_list_kernel, dim3(nb), dim3(kRaysPerBlock), 0, s, cw->task_sums, n,
-                               cw->n_masks, cw->live_chunks, cw->task_list);
-        } else {
-            hipLaunchKernelGGL((cone_starts_kernel<LOOKUP, false>), dim3(nb), dim3(kRaysPerBlock), 0, s, o, d, gid, n,
-                               g, c, p, cw->n_masks, cw->chunk_t, cw->t_far, cw->extra, nullptr, nullptr, nullptr, tab);
-        }
-        if (cw->n_masks > 0 && SKIP) {  // segments through the halo bits
-            hipLaunchKernelGGL((count_cone_segments_kernel<LOOKUP>), dim3(task_blocks(cw->n_masks, n)),
-                               dim3(kTaskThreads), 0, s, o, d, gid, n, bits, halo_of(skip, g), g, p, cw->n_masks,
-                               cw->chunk_t, cw->t_far, cw->masks, cw->extra, cw->seg_t,
-                               listed ? cw->task_list : nullptr,
-                               listed ? cw->task_sums + nb * cw->n_masks : nullptr, tab);
-        } else if (cw->n_masks > 0) {
-            hipLaunchKernelGGL((count_cone_chunks_kernel<LOOKUP, false>), dim3(task_blocks(cw->n_masks, n)),
-                               dim3(kTaskThreads), 0, s, o, d, gid, n, bits, skip, g, p, cw->n_masks, cw->chunk_t,
-                               cw->t_far, cw->masks, cw->extra);
-        }
-        hipLaunchKernelGGL(cone_counts_kernel, dim3(nb), dim3(kRaysPerBlock), 0, s, n, cw->n_masks, p.max_per_ray,
-                           cw->masks, cw->extra, packed, sums, SKIP ? cw->chunk_base : nullptr,
-                           listed ? cw->live_chunks : nullptr, SKIP ? cw->live_chunks : nullptr);
+void launch_fill_cone(const uint8_t* skip, bool segments, const ConeWork* cw, int64_t nb, hipStream_t s,
+                      const float* o, const float* d, const int32_t* gid, int64_t n, const uint32_t* bits,
+                      const GridK& g, const ClipK& c, const StepK& p, const int32_t* packed, int64_t capacity,
+                      int32_t* ri, float* ts, float* te, int32_t* status, const uint64_t*, int) {
+    if (cw != nullptr && cw->n_masks > 0 && segments) {
+        // the segment count's masks, segment starts and chunks holding
+        // samples, ray-major (the ray indices written with the samples)
+        const int64_t per_block = static_cast<int64_t>(kTaskWaves) * kFillRays;
+        const unsigned blocks = static_cast<unsigned>((n + per_block - 1) / per_block);
+        hipLaunchKernelGGL((fill_cone_rays_kernel<LOOKUP>), dim3(blocks), dim3(kTaskThreads), 0, s, o, d, gid, n, bits,
+                           g, p, cw->n_masks, cw->chunk_t, cw->t_far, cw->masks, cw->chunk_base, cw->seg_t,
+                           cw->live_chunks, packed, capacity, ri, ts, te, status);
         return;
     }
+    if (cw != nullptr && cw->n_masks > 0) {  // replay the count pass's chunks, one lane per chunk
+        hipLaunchKernelGGL((fill_cone_chunks_kernel<LOOKUP>), dim3(task_blocks(cw->n_masks, n)), dim3(kTaskThreads), 0,
+                           s, o, d, gid, n, bits, g, p, cw->n_masks, cw->chunk_t, cw->t_far, cw->masks, packed,
+                           capacity, ts, te, status);
+    } else {  // traversal, one lane per ray
+        hipLaunchKernelGGL((fill_cone_kernel<LOOKUP, SKIP>), dim3(nb), dim3(kRaysPerBlock), 0, s, o, d, gid, n, bits,
+                           skip, g, c, p, packed, capacity, ts, te, status);
+    }
+    const int64_t blocks = std::min<int64_t>((n + kExpandThreads / kWave - 1) / (kExpandThreads / kWave), 256 * 64);
+    hipLaunchKernelGGL(expand_rays_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kExpandThreads), 0, s, packed, n,
+                       capacity, ri);
+}
+
+template <int LOOKUP, bool SKIP, typename... A>
+void launch_fill_waves(A&&... a) {
     switch (tuning().march_waves_per_group) {
-        case 1: launch_count_uniform<LOOKUP, SKIP, 1>(nb, s, o, d, gid, n, bits, skip, g, c, p, packed, sums, masks, n_masks); break;
-        case 2: launch_count_uniform<LOOKUP, SKIP, 2>(nb, s, o, d, gid, n, bits, skip, g, c, p, packed, sums, masks, n_masks); break;
-        case 8: launch_count_uniform<LOOKUP, SKIP, 8>(nb, s, o, d, gid, n, bits, skip, g, c, p, packed, sums, masks, n_masks); break;
-        case 16: launch_count_uniform<LOOKUP, SKIP, 16>(nb, s, o, d, gid, n, bits, skip, g, c, p, packed, sums, masks, n_masks); break;
-        default: launch_count_uniform<LOOKUP, SKIP, 4>(nb, s, o, d, gid, n, bits, skip, g, c, p, packed, sums, masks, n_masks); break;
+        case 1: launch_fill_uniform<LOOKUP, SKIP, 1>(a...); break;
+        case 2: launch_fill_uniform<LOOKUP, SKIP, 2>(a...); break;
+        case 8: launch_fill_uniform<LOOKUP, SKIP, 8>(a...); break;
+        case 16: launch_fill_uniform<LOOKUP, SKIP, 16>(a...); break;
+        default: launch_fill_uniform<LOOKUP, SKIP, 4>(a...); break;
     }
 }
 
-template <int LOOKUP, bool SKIP>
-void launch_fill_impl(bool cone, const ConeWork* cw, int64_t nb, hipStream_t s, const float* o, const float* d,
-                      const int32_t* gid, int64_t n, const uint32_t* bits, const uint8_t* skip, const GridK& g,
-                      const ClipK& c, const StepK& p, const int32_t* packed, int64_t capacity, int32_t* ri, float* ts,
-                      float* te, int32_t* status, const uint64_t* masks, int n_masks) {
-    if (cone) {
-        if (cw != nullptr && cw->n_masks > 0 && SKIP) {
-            // the segment count's masks, segment starts and chunks holding
-            // samples, ray-major (the ray indices written with the samples)
-            const int64_t per_block = static_cast<int64_t>(kTaskWaves) * kFillRays;
-            const unsigned blocks = static_cast<unsigned>((n + per_block - 1) / per_block);
-            hipLaunchKernelGGL((fill_cone_rays_kernel<LOOKUP>), dim3(blocks), dim3(kTaskThreads), 0, s, o, d, gid, n,
-                               bits, g, p, cw->n_masks, cw->chunk_t, cw->t_far, cw->masks, cw->chunk_base,
-                               cw->seg_t, cw->live_chunks, packed, capacity, ri, ts, te, status);
-            return;
-        } else if (cw != nullptr && cw->n_masks > 0) {  // replay the count pass's chunks, one lane per chunk
-            hipLaunchKernelGGL((fill_cone_chunks_kernel<LOOKUP, false>), dim3(task_blocks(cw->n_masks, n)),
-                               dim3(kTaskThreads), 0, s, o, d, gid, n, bits, skip, g, p, cw->n_masks, cw->chunk_t,
-                               cw->t_far, cw->masks, packed, capacity, ts, te, status);
-        } else {  // traversal, one lane per ray
-            hipLaunchKernelGGL((fill_cone_kernel<LOOKUP, SKIP>), dim3(nb), dim3(kRaysPerBlock), 0, s, o, d, gid, n,
-                               bits, skip, g, c, p, packed, capacity, ts, te, status);
-        }
-        const int64_t blocks = std::min<int64_t>((n + kExpandThreads / kWave - 1) / (kExpandThreads / kWave),
-                                                 256 * 64);
-        hipLaunchKernelGGL(expand_rays_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kExpandThreads), 0, s,
-                           packed, n, capacity, ri);
-        return;
-    }
-    switch (tuning().march_waves_per_group) {
-        case 1: launch_fill_uniform<LOOKUP, SKIP, 1>(nb, s, o, d, gid, n, bits, skip, g, c, p, packed, capacity, ri, ts, te, status, masks, n_masks); break;
-        case 2: launch_fill_uniform<LOOKUP, SKIP, 2>(nb, s, o, d, gid, n, bits, skip, g, c, p, packed, capacity, ri, ts, te, status, masks, n_masks); break;
-        case 8: launch_fill_uniform<LOOKUP, SKIP, 8>(nb, s, o, d, gid, n, bits, skip, g, c, p, packed, capacity, ri, ts, te, status, masks, n_masks); break;
-        case 16: launch_fill_uniform<LOOKUP, SKIP, 16>(nb, s, o, d, gid, n, bits, skip, g, c, p, packed, capacity, ri, ts, te, status, masks, n_masks); break;
-        default: launch_fill_uniform<LOOKUP, SKIP, 4>(nb, s, o, d, gid, n, bits, skip, g, c, p, packed, capacity, ri, ts, te, status, masks, n_masks); break;
-    }
-}
+template <int LOOKUP>
+using Lookup = std::integral_constant<int, LOOKUP>;
 
-// The skip field serves every lookup (res % 4 == 0).
+// `halo`: the halo bits the call marches by (the skip buffer's, or built in
+// the workspace), or nullptr.  The box lookup's uniform steps and every
+// lookup's cone steps use them; the skip buffer's distances serve the
+// uniform steps of the other lookups.
 template <int LOOKUP, typename... A>
-void dispatch_count(const uint8_t* skip, const ConeWork* cw, int64_t nb, hipStream_t s, const float* o,
-                    const float* d, const int32_t* gid, int64_t n, const uint32_t* bits, A&&... a) {
-    if (skip != nullptr) {
-        launch_count_impl<LOOKUP, true>(cw, nb, s, o, d, gid, n, bits, skip, a...);
-        return;
+void dispatch_count(const uint8_t* skip, const uint32_t* halo, const ConeWork* cw, A&&... a) {
+    if (cw != nullptr) {
+        launch_count_cone<LOOKUP>(*cw, halo, a...);
+    } else if (LOOKUP == NACC_LOOKUP_AABB ? halo != nullptr : skip != nullptr) {
+        launch_count_waves<LOOKUP, true>(skip, halo, a...);
+    } else {
+        launch_count_waves<LOOKUP, false>(nullptr, nullptr, a...);
     }
-    launch_count_impl<LOOKUP, false>(cw, nb, s, o, d, gid, n, bits, nullptr, a...);
 }
 
+// `segments` (cone steps): the count pass marched by halo bits.
 template <int LOOKUP, typename... A>
-void dispatch_fill(const uint8_t* skip, bool cone, const ConeWork* cw, int64_t nb, hipStream_t s, const float* o,
-                   const float* d, const int32_t* gid, int64_t n, const uint32_t* bits, A&&... a) {
-    if (skip != nullptr) {
-        launch_fill_impl<LOOKUP, true>(cone, cw, nb, s, o, d, gid, n, bits, skip, a...);
-        return;
+void dispatch_fill(const uint8_t* skip, bool cone, bool segments, const ConeWork* cw, A&&... a) {
+    if (cone && skip != nullptr) {
+        launch_fill_cone<LOOKUP, true>(skip, segments, cw, a...);
+    } else if (cone) {
+        launch_fill_cone<LOOKUP, false>(nullptr, segments, cw, a...);
+    } else if (LOOKUP != NACC_LOOKUP_AABB && skip != nullptr) {
+        launch_fill_waves<LOOKUP, true>(skip, a...);
+    } else {
+        launch_fill_waves<LOOKUP, false>(nullptr, a...);
     }
-    launch_fill_impl<LOOKUP, false>(cone, cw, nb, s, o, d, gid, n, bits, nullptr, a...);
 }
 
 const uint8_t* usable_skip(const uint8_t* skip, const nacc_grid_desc& grid) {
@@ -1989,7 +2017,7 @@ const uint8_t* usable_skip(const uint8_t* skip, const nacc_grid_desc& grid) {
 int march_count_launch(const float* rays_o, const float* rays_d, const int32_t* grid_id, int64_t n_rays,
                        const uint32_t* grid_bits, const uint8_t* grid_skip, const nacc_grid_desc* grid,
                        const nacc_march_params* params, int32_t* packed_info, int64_t* total, int64_t* sums,
-                       uint64_t* masks, int n_masks, const ConeWork* cw, hipStream_t s) {
+                       uint64_t* masks, int n_masks, const ConeWork* cw, uint32_t* own_halo, hipStream_t s) {
     GridK g;
     ClipK c;
     StepK p;
@@ -1998,19 +2026,21 @@ int march_count_launch(const float* rays_o, const float* rays_d, const int32_t* 
     const uint8_t* skip = usable_skip(grid_skip, *grid);
     int st = NACC_OK;
     if (nb > 0) {
+        const uint32_t* halo = halo_of(skip, g);
+        if (halo == nullptr && own_halo != nullptr) {
+            launch_halo(grid_bits, g.res, g.n_grids, own_halo, s);
+            st = check_launch("march halo");
+            if (st != NACC_OK) return st;
+            halo = own_halo;
+        }
+        auto run = [&](auto lookup) {
+            dispatch_count<decltype(lookup)::value>(skip, halo, cw, nb, s, rays_o, rays_d, grid_id, n_rays, grid_bits,
+                                                    g, c, p, packed_info, sums, masks, n_masks);
+        };
         switch (grid->lookup) {
-            case NACC_LOOKUP_AABB:
-                dispatch_count<NACC_LOOKUP_AABB>(skip, cw, nb, s, rays_o, rays_d, grid_id, n_rays, grid_bits, g, c,
-                                                 p, packed_info, sums, masks, n_masks);
-                break;
-            case NACC_LOOKUP_CASCADE:
-                dispatch_count<NACC_LOOKUP_CASCADE>(skip, cw, nb, s, rays_o, rays_d, grid_id, n_rays, grid_bits, g,
-                                                    c, p, packed_info, sums, masks, n_masks);
-                break;
-            default:
-                dispatch_count<NACC_LOOKUP_CONTRACT>(skip, cw, nb, s, rays_o, rays_d, grid_id, n_rays, grid_bits,
-                                                     g, c, p, packed_info, sums, masks, n_masks);
-                break;
+            case NACC_LOOKUP_AABB: run(Lookup<NACC_LOOKUP_AABB>{}); break;
+            case NACC_LOOKUP_CASCADE: run(Lookup<NACC_LOOKUP_CASCADE>{}); break;
+            default: run(Lookup<NACC_LOOKUP_CONTRACT>{}); break;
         }
         st = check_launch("march count");
         if (st != NACC_OK) return st;
@@ -2077,8 +2107,11 @@ int nacc_march_count(const float* rays_o, const float* rays_d, const int32_t* gr
         cw_store = cone_work(workspace, lay);
         cw = &cw_store;
     }
+    uint32_t* own_halo =
+        lay.halo_off != 0 ? reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + lay.halo_off) : nullptr;
     return march_count_launch(rays_o, rays_d, grid_id, n_rays, grid_bits, grid_skip, grid, params, packed_info,
-                              total, static_cast<int64_t*>(workspace), masks, lay.n_masks, cw, as_stream(stream));
+                              total, static_cast<int64_t*>(workspace), masks, lay.n_masks, cw, own_halo,
+                              as_stream(stream));
 }
 
 int nacc_march_fill(const float* rays_o, const float* rays_d, const int32_t* grid_id, int64_t n_rays,
@@ -2121,22 +2154,17 @@ int nacc_march_fill(const float* rays_o, const float* rays_d, const int32_t* gri
         cw_store = cone_work(const_cast<void*>(workspace), lay);
         cw = &cw_store;
     }
+    // as the count pass decided: by the skip buffer's halo bits or its own
+    const bool segments = skip != nullptr || lay.halo_off != 0;
+    auto run = [&](auto lookup) {
+        dispatch_fill<decltype(lookup)::value>(skip, cone, segments, cw, nb, s, rays_o, rays_d, grid_id, n_rays,
+                                               grid_bits, g, c, p, packed_info, capacity, ray_indices, t_starts,
+                                               t_ends, status, masks, lay.n_masks);
+    };
     switch (grid->lookup) {
-        case NACC_LOOKUP_AABB:
-            dispatch_fill<NACC_LOOKUP_AABB>(skip, cone, cw, nb, s, rays_o, rays_d, grid_id, n_rays, grid_bits, g, c, p,
-                                            packed_info, capacity, ray_indices, t_starts, t_ends, status, masks,
-                                            lay.n_masks);
-            break;
-        case NACC_LOOKUP_CASCADE:
-            dispatch_fill<NACC_LOOKUP_CASCADE>(skip, cone, cw, nb, s, rays_o, rays_d, grid_id, n_rays, grid_bits, g, c,
-                                               p, packed_info, capacity, ray_indices, t_starts, t_ends, status, masks,
-                                               lay.n_masks);
-            break;
-        default:
-            dispatch_fill<NACC_LOOKUP_CONTRACT>(skip, cone, cw, nb, s, rays_o, rays_d, grid_id, n_rays, grid_bits, g, c,
-                                                p, packed_info, capacity, ray_indices, t_starts, t_ends, status,
-                                                masks, lay.n_masks);
-            break;
+        case NACC_LOOKUP_AABB: run(Lookup<NACC_LOOKUP_AABB>{}); break;
+        case NACC_LOOKUP_CASCADE: run(Lookup<NACC_LOOKUP_CASCADE>{}); break;
+        default: run(Lookup<NACC_LOOKUP_CONTRACT>{}); break;
     }
     return check_launch("march fill");
 }

@@ -1,0 +1,37 @@
+"""The sizes at which the library changes kernels, against the oracle: the
+marching count pass building halo bits of its own (or not), and listing the
+chunks of cone steps (or not)."""
+import numpy as np
+import pytest
+
+import synth
+from test_gpu_march import BOX, compare
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_rays", [16415, 16416])
+def test_uniform_own_halo(n_rays):
+    """Halo bits of a 32^3 grid (128 words) are built from 16,416 rays on."""
+    mask = synth.random_mask(32 ** 3, 0.02, 11)
+    o, d = synth.rays_toward_origin(n_rays, 61)
+    compare(o, d, mask, 32, BOX, 0.0, 1e10, 0.0137)
+
+
+@pytest.mark.parametrize("n_grids,n_rays", [(64, 1), (65, 64), (66, 64), (66, 200)])
+def test_cone_many_grids(n_grids, n_rays):
+    """64^3 grids have 1,024 halo words each; a call of n rays builds up to
+    65,536 + 16 n words (66 grids: not for 64 rays, but for 200)."""
+    mask = synth.random_mask(n_grids * 64 ** 3, 0.01, 12)
+    o, d = synth.rays_toward_origin(n_rays, 62)
+    gid = np.random.default_rng(5).integers(0, n_grids, n_rays).astype(np.int32)
+    compare(o, d, mask, 64, BOX, 0.0, 1e10, 0.006, cone=1 / 256, n_grids=n_grids, grid_id=gid)
+
+
+@pytest.mark.parametrize("n_rays", [104857, 104858])
+def test_contraction_task_list(n_rays):
+    """2,512 candidates, 40 chunks a ray: listed from 104,858 rays on."""
+    mask = synth.random_mask(64 ** 3, 0.01, 13)
+    o, d = synth.rays_unbounded(n_rays, 63)
+    compare(o, d, mask, 64, np.array(synth.CONTRACT_BOX, np.float32), 0.2, 1e4, synth.STEP_1024,
+            cone=1 / 256, lookup=2, max_per_ray=64)
