@@ -35,3 +35,16 @@ def test_contraction_task_list(n_rays):
     o, d = synth.rays_unbounded(n_rays, 63)
     compare(o, d, mask, 64, np.array(synth.CONTRACT_BOX, np.float32), 0.2, 1e4, synth.STEP_1024,
             cone=1 / 256, lookup=2, max_per_ray=64)
+
+
+@pytest.mark.parametrize("n_rays,dt", [(1, 0.0137), (63, 0.0137), (2049, 0.0137), (4095, 0.0025),
+                                       (4096, 0.0025), (8192, 0.0025), (16384, 0.0137), (16385, 0.00125)])
+@pytest.mark.parametrize("cap", [0, 70])
+def test_uniform_fill_rays_per_wave(n_rays, dt, cap):
+    """1, 2, 4 and 8 rays per wave of the fill; 6, 33 and 64 stored chunks
+    (the last one with rays going on past them); full and ragged masks; rays
+    cut by the cap."""
+    for p_occ in (0.05, 1.0):
+        mask = synth.random_mask(16 ** 3, p_occ, 14)
+        o, d = synth.rays_toward_origin(n_rays, 64)
+        compare(o, d, mask, 16, BOX, 0.0, 1e10, dt, max_per_ray=cap)
