@@ -38,7 +38,7 @@ using namespace nacc::blob;
 using namespace nacc::vr;
 
 constexpr int kFusedWaves = 4;
-constexpr int kFusedRays = 64;  // rays per workgroup: lane j of a wave clips its j-th ray
+constexpr int kFusedRays = 64;  // most rays per workgroup: lane j of a wave clips its j-th ray
 constexpr int kRing = 256;      // candidate indices per wave: < 64 held + 128 appended
 
 // Appends the occupied candidates of one wave iteration (ballot m of the
@@ -68,7 +68,8 @@ struct SegWalk {
 };
 
 template <int LOOKUP, bool PER_SET, bool SEG>
-__device__ __forceinline__ void render_ray_fused(int64_t r, const RaySpan& span, const float* __restrict__ table,
+__device__ __forceinline__ void render_ray_fused(int64_t r, const RaySpan& span, const SegRay& sg,
+                                                 const float* __restrict__ table,
                                                  int n_blobs, int n_sets, const int32_t* __restrict__ ray_set,
                                                  const float* __restrict__ rays_o, const float* __restrict__ rays_d,
                                                  const uint32_t* __restrict__ bits,
@@ -86,7 +87,11 @@ __device__ __forceinline__ void render_ray_fused(int64_t r, const RaySpan& span,
     }
     const float* cc = table + static_cast<int64_t>(n_sets) * n_blobs * kBlobStride;
     const bool contract = cc[12] != 0.0f;
+    const float* blobs = table + static_cast<int64_t>(set) * n_blobs * kBlobStride;
     const float t_near = span.t_near, t_far = span.t_far;
+    const float d_norm = sqrtf((d[0] * d[0] + d[1] * d[1]) + d[2] * d[2]) * (1.0f + 0x1p-18f);
+    // |o_i| + |d_i| t stays below this times (t + 1)
+    const float ray_size = fmaxf(fmaxf(fabsf(o[0]), fabsf(o[1])), fabsf(o[2])) + d_norm;
     double carry = 0.0;
     float acc_r = 0.0f, acc_g = 0.0f, acc_b = 0.0f, acc_a = 0.0f, acc_d = 0.0f;
     int head = 0;      // ring slot of the oldest queued candidate
@@ -96,8 +101,6 @@ __device__ __forceinline__ void render_ray_fused(int64_t r, const RaySpan& span,
     int n_kept = -1;
     bool more = span.valid;
     int k0 = 0;
-    SegRay sg{0, 0u};
-    if (SEG && span.valid) sg = seg_ray(g, span, p);
     SegWalk sw;
     while (true) {
         // march until a whole chunk is queued or the ray's candidates end,
@@ -200,12 +203,27 @@ __device__ __forceinline__ void render_ray_fused(int64_t r, const RaySpan& span,
             const int k = ring[(head + lane) & (kRing - 1)];
             t0 = t_near + static_cast<float>(k) * p.dt;
             t1 = t_near + static_cast<float>(k + 1) * p.dt;
+        }
+        {
+            // the chunk's samples lie within `reach` of the point halfway
+            // between its ends (the contraction brings points no farther
+            // apart), with the rounding of t and of the positions, a few
+            // ulps of the largest coordinate each, taken generously
+            const float ta = uniform<float>(t0), tb = read_lane(t1, n_chunk - 1);
+            const float tc = 0.5f * (ta + tb);
+            float c0 = o[0] + d[0] * tc, c1 = o[1] + d[1] * tc, c2 = o[2] + d[2] * tc;
+            to_scene(contract, c0, c1, c2);
+            const float far = ray_size * (fabsf(ta) + fabsf(tb) + 1.0f);
+            const float reach = 0.5f * (tb - ta) * d_norm + far * 0x1p-18f;
             float x0 = midpoint_coord(o[0], d[0], t0, t1);
             float x1 = midpoint_coord(o[1], d[1], t0, t1);
             float x2 = midpoint_coord(o[2], d[2], t0, t1);
             to_scene(contract, x0, x1, x2);
-            eval_field(table, n_blobs, set, x0, x1, x2, sigma);
-            eval_rgb(cc, x0, x1, x2, cr, cg, cb);
+            const float s = eval_near(blobs, n_blobs, c0, c1, c2, reach, x0, x1, x2);
+            if (valid) {
+                sigma = s;
+                eval_rgb(cc, x0, x1, x2, cr, cg, cb);
+            }
         }
         wave_lds_sync();
         head = (head + n_chunk) & (kRing - 1);
@@ -239,30 +257,40 @@ __device__ __forceinline__ void render_ray_fused(int64_t r, const RaySpan& span,
 }
 
 // clocks (nullable): the device wall clock when the workgroup started and
-// when its last wave finished, per workgroup of kFusedRays rays.
+// when its last wave finished, per workgroup.
+// group: rays per workgroup, kFusedWaves to kFusedRays.
 template <int LOOKUP, bool PER_SET, bool SEG>
 __global__ __launch_bounds__(kFusedWaves * kWave) void fused_render_kernel(
     const float* __restrict__ table, int n_blobs, int n_sets, const int32_t* __restrict__ ray_set,
     const float* __restrict__ rays_o, const float* __restrict__ rays_d, const int32_t* __restrict__ grid_id,
     int64_t n_rays, const uint32_t* __restrict__ bits, const uint32_t* __restrict__ halo, GridK g, ClipK c,
     StepK p, float eps, float* __restrict__ color, float* __restrict__ opacity, float* __restrict__ depth,
-    int32_t* __restrict__ kept, uint64_t* __restrict__ clocks) {
+    int32_t* __restrict__ kept, uint64_t* __restrict__ clocks, int group) {
     __shared__ int rings[kFusedWaves][kRing];
     __shared__ uint8_t lists[kFusedWaves][SEG ? kWave : 1];
     const uint64_t t_start = clocks != nullptr ? wall_clock64() : 0ull;
     const int wave = uniform<int>(static_cast<int>(threadIdx.x) / kWave);
-    const int64_t first = static_cast<int64_t>(blockIdx.x) * kFusedRays;
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * group;
     // this wave's rays are first + wave + j kFusedWaves; lane j clips ray j
     const int64_t mine = first + wave + static_cast<int64_t>(lane_id()) * kFusedWaves;
     RaySpan spans{};
-    if (lane_id() < kFusedRays / kFusedWaves && mine < n_rays) {
+    if (wave + lane_id() * kFusedWaves < group && mine < n_rays) {
         spans = ray_span<LOOKUP>(mine, rays_o, rays_d, grid_id, g, c, p);
     }
-    for (int i = wave; i < kFusedRays; i += kFusedWaves) {
+    const int seg_logs = SEG ? seg_log(g, spans, p) : 0;
+    // rays without candidates are finished by their lanes
+    if (wave + lane_id() * kFusedWaves < group && mine < n_rays && !spans.valid) {
+        color[3 * mine] = color[3 * mine + 1] = color[3 * mine + 2] = 0.0f;
+        opacity[mine] = depth[mine] = 0.0f;
+        if (kept != nullptr) kept[mine] = 0;
+    }
+    for (int i = wave; i < group; i += kFusedWaves) {
         const int64_t r = first + i;
         if (r >= n_rays) break;
         const RaySpan span = read_span(spans, i / kFusedWaves);
-        render_ray_fused<LOOKUP, PER_SET, SEG>(r, span, table, n_blobs, n_sets, ray_set, rays_o, rays_d, bits, halo,
+        if (!span.valid) continue;
+        const SegRay sg = read_seg(seg_logs, span, g, i / kFusedWaves);
+        render_ray_fused<LOOKUP, PER_SET, SEG>(r, span, sg, table, n_blobs, n_sets, ray_set, rays_o, rays_d, bits, halo,
                                                g, p, eps, rings[wave], lists[wave], color, opacity, depth, kept);
     }
     if (clocks != nullptr) {
@@ -274,19 +302,30 @@ __global__ __launch_bounds__(kFusedWaves * kWave) void fused_render_kernel(
     }
 }
 
+// Rays per workgroup: a wave takes its rays one after the other, whose costs
+// differ by the samples they hold, so a small image needs many short waves
+// (64 rays against 4: 3,072 rays 116 -> 21 us, 30,000 rays 212 -> 54 us),
+// while a large one gains from what a wave does once for all its rays (4
+// against 32: 640,000 rays 824 -> 675 us).  In between: 120,000 rays 174 us
+// with 8 (16: 177, 4: 185), 226,400 rays 317 us with 16 (8: 324, 32: 337).
+int fused_group(int64_t n_rays) {
+    return n_rays < 40000 ? 4 : (n_rays < 160000 ? 8 : (n_rays < 400000 ? 16 : 32));
+}
+
 template <int LOOKUP, bool SEG>
-void launch_fused_seg(bool per_set, unsigned nb, hipStream_t s, const float* table, int n_blobs, int n_sets,
+void launch_fused_seg(bool per_set, int group, hipStream_t s, const float* table, int n_blobs, int n_sets,
                       const int32_t* ray_set, const float* o, const float* d, const int32_t* gid, int64_t n,
                       const uint32_t* bits, const uint32_t* halo, const GridK& g, const ClipK& c, const StepK& p,
                       float eps, float* color, float* opacity, float* depth, int32_t* kept, uint64_t* clocks) {
+    const unsigned nb = static_cast<unsigned>((n + group - 1) / group);
     if (per_set) {
         hipLaunchKernelGGL((fused_render_kernel<LOOKUP, true, SEG>), dim3(nb), dim3(kFusedWaves * kWave), 0, s,
                            table, n_blobs, n_sets, ray_set, o, d, gid, n, bits, halo, g, c, p, eps, color, opacity,
-                           depth, kept, clocks);
+                           depth, kept, clocks, group);
     } else {
         hipLaunchKernelGGL((fused_render_kernel<LOOKUP, false, SEG>), dim3(nb), dim3(kFusedWaves * kWave), 0, s,
                            table, n_blobs, n_sets, ray_set, o, d, gid, n, bits, halo, g, c, p, eps, color, opacity,
-                           depth, kept, clocks);
+                           depth, kept, clocks, group);
     }
 }
 
@@ -323,7 +362,7 @@ int nacc_synth_render_fused(const void* table, int32_t n_blobs, int32_t n_sets, 
     ClipK c;
     StepK p;
     make_constants(*grid, *params, g, c, p);
-    const unsigned nb = static_cast<unsigned>((n_rays + kFusedRays - 1) / kFusedRays);
+    const int group = clocks != nullptr ? kFusedRays : fused_group(n_rays);
     hipStream_t s = as_stream(stream);
     const float* tb = static_cast<const float*>(table);
     const bool per_set = ray_set != nullptr;
@@ -334,22 +373,22 @@ int nacc_synth_render_fused(const void* table, int32_t n_blobs, int32_t n_sets, 
     switch (grid->lookup) {
         case NACC_LOOKUP_AABB:
             if (halo != nullptr) {
-                launch_fused_seg<NACC_LOOKUP_AABB, true>(per_set, nb, s, tb, n_blobs, n_sets, ray_set, rays_o,
+                launch_fused_seg<NACC_LOOKUP_AABB, true>(per_set, group, s, tb, n_blobs, n_sets, ray_set, rays_o,
                                                          rays_d, grid_id, n_rays, grid_bits, halo, g, c, p,
                                                          early_stop_eps, color, opacity, depth, kept, clocks);
             } else {
-                launch_fused_seg<NACC_LOOKUP_AABB, false>(per_set, nb, s, tb, n_blobs, n_sets, ray_set, rays_o,
+                launch_fused_seg<NACC_LOOKUP_AABB, false>(per_set, group, s, tb, n_blobs, n_sets, ray_set, rays_o,
                                                           rays_d, grid_id, n_rays, grid_bits, nullptr, g, c, p,
                                                           early_stop_eps, color, opacity, depth, kept, clocks);
             }
             break;
         case NACC_LOOKUP_CASCADE:
-            launch_fused_seg<NACC_LOOKUP_CASCADE, false>(per_set, nb, s, tb, n_blobs, n_sets, ray_set, rays_o, rays_d,
+            launch_fused_seg<NACC_LOOKUP_CASCADE, false>(per_set, group, s, tb, n_blobs, n_sets, ray_set, rays_o, rays_d,
                                                          grid_id, n_rays, grid_bits, nullptr, g, c, p,
                                                          early_stop_eps, color, opacity, depth, kept, clocks);
             break;
         default:
-            launch_fused_seg<NACC_LOOKUP_CONTRACT, false>(per_set, nb, s, tb, n_blobs, n_sets, ray_set, rays_o,
+            launch_fused_seg<NACC_LOOKUP_CONTRACT, false>(per_set, group, s, tb, n_blobs, n_sets, ray_set, rays_o,
                                                           rays_d, grid_id, n_rays, grid_bits, nullptr, g, c, p,
                                                           early_stop_eps, color, opacity, depth, kept, clocks);
             break;

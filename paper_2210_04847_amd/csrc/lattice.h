@@ -291,8 +291,9 @@ struct SegRay {
     uint32_t halo0;  // first halo word of the ray's grid
 };
 
-__device__ __forceinline__ SegRay seg_ray(const GridK& g, const RaySpan& span, const StepK& p) {
-    SegRay sg{0, 0u};
+// log2 of the candidates per segment of a ray, computed for a wave's rays
+// lane-parallel (one ray per lane) as their spans are.
+__device__ __forceinline__ int seg_log(const GridK& g, const RaySpan& span, const StepK& p) {
     const float* o = span.o;
     const float* d = span.d;
     const float v = fmaxf(fmaxf(g.s[0] * fabsf(d[0]), g.s[1] * fabsf(d[1])), g.s[2] * fabsf(d[2]));
@@ -308,11 +309,12 @@ __device__ __forceinline__ SegRay seg_ray(const GridK& g, const RaySpan& span, c
     const float budget = static_cast<float>(kHaloReach) - slack;
     int lg = 5;
     while (lg >= kMinSegmentLog2 && !(v * ldexpf(p.dt, lg - 1) * (1.0f + 0x1p-10f) <= budget)) --lg;
-    if (lg >= kMinSegmentLog2) {
-        sg.log_g = lg;
-        sg.halo0 = span.grid * g.halo_words;
-    }
-    return sg;
+    return span.valid && lg >= kMinSegmentLog2 ? lg : 0;
+}
+
+// Lane `lane`'s ray in every lane (span: its span, already broadcast).
+__device__ __forceinline__ SegRay read_seg(int seg_logs, const RaySpan& span, const GridK& g, int lane) {
+    return SegRay{read_lane(seg_logs, lane), span.grid * g.halo_words};
 }
 
 // Halo bit of the cell holding point x (the box lookup's clamped cell

@@ -446,6 +446,7 @@ __global__ __launch_bounds__(WAVES * kWave) void count_uniform_kernel(
     if (wave + lane_id() * WAVES < per && mine < n_rays) {
         spans = ray_span<LOOKUP>(mine, rays_o, rays_d, grid_id, g, c, p);
     }
+    const int seg_logs = kSegments<LOOKUP, SKIP> ? seg_log(g, spans, p) : 0;
     int64_t total = 0;
     bool unused = false;
     for (int i = wave; i < per; i += WAVES) {
@@ -456,7 +457,7 @@ __global__ __launch_bounds__(WAVES * kWave) void count_uniform_kernel(
         const int ray_n_masks = masks != nullptr ? n_masks : 0;
         int n;
         if constexpr (kSegments<LOOKUP, SKIP>) {
-            const SegRay sg = span.valid ? seg_ray(g, span, p) : SegRay{0, 0u};
+            const SegRay sg = read_seg(seg_logs, span, g, i / WAVES);
             if (sg.log_g != 0) {
                 n = count_ray_segments(span, bits, halo, g, p, sg, seg_lists + wave * kWave,
                                        seg_masks + wave * kWave, ray_masks, ray_n_masks);

@@ -1,10 +1,12 @@
 """The sizes at which the library changes kernels, against the oracle: the
-marching count pass building halo bits of its own (or not), and listing the
-chunks of cone steps (or not)."""
+marching count pass building halo bits of its own (or not) and listing the
+chunks of cone steps (or not), the rays per wave of the uniform fill and of
+fused inference."""
 import numpy as np
 import pytest
 
 import synth
+from test_gpu_fused import _assert_same, _cuda, _nacc, _three_step
 from test_gpu_march import BOX, compare
 
 pytestmark = pytest.mark.gpu
@@ -48,3 +50,38 @@ def test_uniform_fill_rays_per_wave(n_rays, dt, cap):
         mask = synth.random_mask(16 ** 3, p_occ, 14)
         o, d = synth.rays_toward_origin(n_rays, 64)
         compare(o, d, mask, 16, BOX, 0.0, 1e10, dt, max_per_ray=cap)
+
+
+@pytest.mark.parametrize("n_rays", [3, 39999, 40000, 159999, 160000, 399999, 400000])
+def test_fused_rays_per_workgroup(n_rays):
+    """4, 8, 16 and 32 rays per workgroup of the fused inference kernel."""
+    nacc = _nacc()
+    scene = synth.blob_scene(6, 71)
+    grid = nacc.OccupancyGrid(synth.BOX_1_5, 32)
+    grid.set_occupancy(_cuda(synth.initial_occupancy(scene, 32, synth.BOX_1_5)), 0.01)
+    field = nacc.BlobField(scene)
+    o, d = (_cuda(a) for a in synth.rays_toward_origin(n_rays, 72, jitter_std=0.5))
+    ref = _three_step(nacc, field, grid, o, d, 0.0, 1e10, 0.02, 1e-4)
+    _assert_same(nacc.render_fused(field, o, d, grid, 0.0, 1e10, 0.02, 1e-4, return_kept=True), ref)
+
+
+@pytest.mark.parametrize("n_blobs,contract,odd_peak", [(1, False, None), (64, False, None), (65, False, None),
+                                                       (150, True, None), (70, False, float("inf")),
+                                                       (70, False, -3.0)])
+def test_fused_leaves_out_far_blobs(n_blobs, contract, odd_peak):
+    """Narrow blobs, most of them too far from a chunk of samples to
+    contribute; more blobs than lanes; a peak whose product is not zero where
+    its exponential is; a scene in contracted coordinates."""
+    nacc = _nacc()
+    scene = synth.blob_scene(n_blobs, 73, radius_range=(0.02, 0.3))
+    scene.contract = contract
+    grid = nacc.OccupancyGrid(synth.BOX_1_5, 64)
+    grid.set_occupancy(_cuda(synth.initial_occupancy(scene, 64, synth.BOX_1_5)), 0.01)
+    if odd_peak is not None:
+        scene.peaks[n_blobs // 2] = odd_peak
+    field = nacc.BlobField(scene)
+    o, d = synth.rays_toward_origin(2000, 74, jitter_std=0.3)
+    o, d = _cuda(o), _cuda(d * np.float32(1.7))
+    ref = _three_step(nacc, field, grid, o, d, 0.0, 1e10, 0.004, 1e-4)
+    assert int((ref["packed"][:, 1] > 0).sum()) > 100
+    _assert_same(nacc.render_fused(field, o, d, grid, 0.0, 1e10, 0.004, 1e-4, return_kept=True), ref)
