@@ -436,7 +436,8 @@ __global__ __launch_bounds__(WAVES * kWave) void count_uniform_kernel(
     __shared__ uint8_t seg_lists[kSegments<LOOKUP, SKIP> ? WAVES * kWave : 1];
     const int wave = uniform<int>(static_cast<int>(threadIdx.x) / kWave);
     // workgroup b takes part b % split of the group of kRaysPerBlock rays
-    // b / split: per = kRaysPerBlock / split rays from `first`
+    // b / split: per = kRaysPerBlock / split rays from `first`; its samples
+    // are part b of the scan
     const int per = kRaysPerBlock / split;
     const int64_t group = static_cast<int64_t>(blockIdx.x) / split;
     const int64_t first = group * kRaysPerBlock + static_cast<int64_t>(blockIdx.x % split) * per;
@@ -478,19 +479,8 @@ __global__ __launch_bounds__(WAVES * kWave) void count_uniform_kernel(
     if (threadIdx.x == 0) {
         int64_t s = 0;
         for (int w = 0; w < WAVES; ++w) s += wave_total[w];
-        if (split == 1) {
-            block_sums[group] = s;
-        } else {  // the group's parts add up (integers: exact in any order)
-            atomicAdd(reinterpret_cast<unsigned long long*>(block_sums + group), static_cast<unsigned long long>(s));
-        }
+        block_sums[blockIdx.x] = s;
     }
-}
-
-// Zeroes the per-group sums that the parts of split groups add into (a
-// kernel, not a memset node, so that captured graphs replay it faithfully).
-__global__ __launch_bounds__(256) void zero_sums_kernel(int64_t* __restrict__ sums, int64_t n) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i < n) sums[i] = 0;
 }
 
 // 32-bit value of lane `src` (per lane) through the LDS crossbar; every lane
@@ -1864,6 +1854,24 @@ int64_t candidate_bound(const nacc_grid_desc& grid, const nacc_march_params& p) 
     return std::min<int64_t>(kMaxCandidates, k + 2);
 }
 
+// Workgroups per group of kRaysPerBlock rays in the uniform-step count
+// kernel: batches that make fewer than 16,384 waves (two for every place on
+// the chip) are spread over more workgroups, so that each wave walks fewer
+// rays one after the other; results do not depend on it.  1,021 rays in 256
+// waves 15 us, in 1,021 waves 6.7 us; a call for 16,384 rays 92 us with
+// 1,024 waves, 69 us with 8,192; for 65,536 rays 114 and 109 us with 4,096
+// and 16,384, no gain from more.
+constexpr int64_t kCountWaves = 16384;
+
+int march_split(int64_t groups, int waves) {
+    int split = 1;
+    while (split * waves < kRaysPerBlock && split < 16 && groups * split * waves < kCountWaves &&
+           2 * split * groups <= kMaxParts) {
+        split *= 2;
+    }
+    return split;
+}
+
 // Workspace of the marching calls: the per-workgroup sums of the scan, then
 // n_masks 64-bit occupancy masks per ray, one per chunk of 64 candidates,
 // written by the count pass and replayed by the fill pass.  n_masks covers
@@ -1903,7 +1911,7 @@ Layout workspace_layout(int64_t n_rays, const nacc_grid_desc& grid, const nacc_m
     Layout l;
     // the workgroup sums, then the scan's scratch
     const int64_t nb = num_blocks(n_rays);
-    l.sums_bytes = align256((nb + scan_scratch_values(nb)) * static_cast<int64_t>(sizeof(int64_t)));
+    l.sums_bytes = align256((nb * march_split(nb, 1) + scan_scratch_values(nb)) * static_cast<int64_t>(sizeof(int64_t)));
     l.n_masks = 0;
     if (p.dt > 0.0f) {
         const int64_t k = candidate_bound(grid, p);
@@ -1962,12 +1970,6 @@ ConeWork cone_work(void* workspace, const Layout& l) {
     return w;
 }
 
-// Workgroups per group of kRaysPerBlock rays in the uniform-step kernels:
-// small batches are spread over more workgroups (the chip has 256 CUs), so
-// that each wave walks fewer rays one after the other; results do not
-// depend on it.
-int march_split(int64_t groups) { return groups < 256 ? 4 : (groups < 512 ? 2 : 1); }
-
 // Halo bits of a skip buffer (see halo_offset).
 const uint32_t* halo_of(const uint8_t* skip, const GridK& g) {
     return skip == nullptr ? nullptr
@@ -1979,11 +1981,7 @@ void launch_count_uniform(const uint8_t* skip, const uint32_t* halo, int64_t nb,
                           const float* d, const int32_t* gid, int64_t n, const uint32_t* bits, const GridK& g,
                           const ClipK& c, const StepK& p, int32_t* packed, int64_t* sums, uint64_t* masks,
                           int n_masks) {
-    const int split = march_split(nb);
-    if (split > 1) {
-        hipLaunchKernelGGL(zero_sums_kernel, dim3(static_cast<unsigned>((nb + 255) / 256)), dim3(256), 0, s, sums,
-                           nb);
-    }
+    const int split = march_split(nb, WAVES);
     hipLaunchKernelGGL((count_uniform_kernel<LOOKUP, SKIP, WAVES>), dim3(static_cast<unsigned>(nb * split)),
                        dim3(WAVES * kWave), 0, s, o, d, gid, n, bits, skip, halo, g, c, p, packed, sums, masks,
                        n_masks, split);
@@ -2169,15 +2167,14 @@ int march_count_launch(const float* rays_o, const float* rays_d, const int32_t* 
         st = check_launch("march count");
         if (st != NACC_OK) return st;
     }
-    scan_exclusive(sums, nb, total, sums + nb, s);
-    st = check_launch("march scan");
-    if (st != NACC_OK) return st;
-    if (nb > 0) {
-        hipLaunchKernelGGL(finalize_starts_kernel, dim3(nb), dim3(kRaysPerBlock), 0, s, sums, n_rays,
-                           packed_info);
-        st = check_launch("march starts");
+    if (nb == 0) {
+        scan_exclusive(sums, 0, total, nullptr, s);
+        return check_launch("march scan");
     }
-    return st;
+    const int split = cw != nullptr ? 1 : march_split(nb, tuning().march_waves_per_group);
+    launch_starts(sums, nb * split, kWaveLog2 - __builtin_ctz(static_cast<unsigned>(split)), n_rays, packed_info,
+                  total, s);
+    return check_launch("march starts");
 }
 
 }  // namespace

@@ -4,6 +4,7 @@ chunks of cone steps (or not), the rays per wave of the uniform fill and of
 fused inference."""
 import numpy as np
 import pytest
+import torch
 
 import synth
 from test_gpu_fused import _assert_same, _cuda, _nacc, _three_step
@@ -85,3 +86,28 @@ def test_fused_leaves_out_far_blobs(n_blobs, contract, odd_peak):
     ref = _three_step(nacc, field, grid, o, d, 0.0, 1e10, 0.004, 1e-4)
     assert int((ref["packed"][:, 1] > 0).sum()) > 100
     _assert_same(nacc.render_fused(field, o, d, grid, 0.0, 1e10, 0.004, 1e-4, return_kept=True), ref)
+
+
+@pytest.mark.parametrize("n_rays", [1, 65, 255, 256, 257, 4097, 65537, 131072, 524288, 524289])
+@pytest.mark.parametrize("waves", [1, 4, 16])
+def test_starts_and_totals(n_rays, waves):
+    """Starts and total of the marched layout at the edges of the parts their
+    sums come in (1 to 16 workgroups per 64 rays; one launch up to 8,192
+    parts, then the scan): the exclusive sums of the counts, which do not
+    depend on the launch parameters."""
+    nacc = _nacc()
+    lib = nacc._lib
+    scene = synth.blob_scene(6, 75)
+    grid = nacc.OccupancyGrid(synth.BOX_1_5, 32)
+    grid.set_occupancy(_cuda(synth.initial_occupancy(scene, 32, synth.BOX_1_5)), 0.01)
+    o, d = (_cuda(a) for a in synth.rays_toward_origin(n_rays, 76, jitter_std=0.5))
+    before = lib.get_tuning()
+    try:
+        lib.set_tuning(march_waves_per_group=waves)
+        packed, ri, ts, _ = nacc.ray_marching(o, d, grid, 0.0, 1e10, 0.02)
+    finally:
+        lib.set_tuning(**before)
+    count = packed[:, 1].long()
+    assert int(count.sum()) == ri.numel() == ts.numel()
+    assert torch.equal(packed[:, 0].long(), count.cumsum(0) - count)
+    assert torch.equal(ri.long(), torch.repeat_interleave(torch.arange(n_rays, device="cuda"), count))
