@@ -740,92 +740,267 @@ struct LaunchMse {
 // marching scan: count (keep flags + per-ray counts), scan, fill.
 // ---------------------------------------------------------------------------
 
-// One wave per ray, four waves per workgroup of kRaysPerBlock rays.
-template <bool PRUNE_FILL>
-__global__ __launch_bounds__(kRenderThreads) void prune_kernel(
+// The chunks of a wave's consecutive rays, one after the other, rays without
+// samples left out (lane i of my_start, my_n holds ray i's range): a kernel
+// that walks them requests the next chunk, also the next ray's first, before
+// it works on the present one.
+struct ChunkWalk {
+    uint64_t rays;  // rays not begun yet
+    int ray;        // of the present chunk (-1: none yet)
+    int c, n, start;
+
+    // Moves to the next chunk; false if there is none.
+    __device__ __forceinline__ bool next(int my_start, int my_n) {
+        if (ray >= 0 && c + kWave < n) {
+            c += kWave;
+            return true;
+        }
+        return next_ray(my_start, my_n);
+    }
+
+    __device__ __forceinline__ bool next_ray(int my_start, int my_n) {
+        if (rays == 0ull) return false;
+        ray = static_cast<int>(__builtin_ctzll(rays));
+        rays &= rays - 1ull;
+        c = 0;
+        n = read_lane(my_n, ray);
+        start = read_lane(my_start, ray);
+        return true;
+    }
+};
+
+struct Interval {
+    float t0, t1, sigma;
+};
+
+// The calling lane's ray's range, empty when it does not lie inside
+// [0, n_samples) (as ray_range).
+__device__ __forceinline__ void lane_range(const int32_t* __restrict__ packed_info, bool mine, int64_t r,
+                                           int64_t n_samples, int& start, int& n) {
+    start = n = 0;
+    if (!mine) return;
+    const int s0 = packed_info[2 * r], c0 = packed_info[2 * r + 1];
+    if (s0 >= 0 && c0 >= 0 && static_cast<int64_t>(s0) + c0 <= n_samples) {
+        start = s0;
+        n = c0;
+    }
+}
+
+// A wave takes `per` consecutive rays (at most 16).  Bound by HBM, or rather
+// by what the waves keep in flight: see ChunkWalk.
+// 33.0 M samples of 262,144 rays: 129 us (a ray after the other, each waiting
+// for its range and its samples) -> 111 us.
+__global__ __launch_bounds__(kRenderThreads) void prune_count_kernel(
     const int32_t* __restrict__ packed_info, int64_t n_rays, int64_t n_samples, const float* __restrict__ ts,
     const float* __restrict__ te, const float* __restrict__ sig, float eps, float alpha_thre,
-    uint8_t* __restrict__ keep, int32_t* __restrict__ packed_out, int64_t* __restrict__ block_sums,
-    int64_t capacity, int32_t* __restrict__ ri_out, float* __restrict__ ts_out, float* __restrict__ te_out,
-    float* __restrict__ sig_out, int32_t* __restrict__ status) {
-    __shared__ int64_t wave_total[kRaysPerRenderBlock];
+    uint8_t* __restrict__ keep, int32_t* __restrict__ packed_out, int64_t* __restrict__ part_sums, int per) {
+    __shared__ uint64_t part;
     const int lane = lane_id();
-    const int wave = uniform<int>(static_cast<int>(threadIdx.x) / kWave);
-    const int64_t first = static_cast<int64_t>(blockIdx.x) * kRaysPerBlock;
-    int64_t total = 0;
-    bool overflow = false;
-    for (int j = wave; j < kRaysPerBlock; j += kRaysPerRenderBlock) {
-        const int64_t r = first + j;
-        if (r >= n_rays) break;
-        int64_t start;
-        int n;
-        ray_range(packed_info, r, n_samples, start, n);
-        if (!PRUNE_FILL) {
-            double carry = 0.0;
-            int count = 0;
-            int c = 0;
-            for (; c < n; c += kWave) {
-                const int i = c + lane;
-                const bool valid = i < n;
-                const int64_t s = start + i;
-                Sample x{0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-                if (valid) {
-                    x.t0 = ts[s];
-                    x.t1 = te[s];
-                    x.sigma = sig[s];
-                }
-                const Trans t = chunk_transmittance(x, carry);
-                const int keep_n = chunk_keep(valid, t.t_in, eps);
-                const bool k = valid && lane < keep_n && alpha_of(t.tau) >= alpha_thre;
-                if (valid) keep[s] = k ? 1 : 0;
-                count += __popcll(ballot(k));
-                carry += static_cast<double>(read_lane(t.incl, 63));
-                if (keep_n < kWave) {
-                    c += kWave;
-                    break;
-                }
+    const int64_t block = xcd_grouped<16>(blockIdx.x, gridDim.x);
+    const int64_t first = (block * kRaysPerRenderBlock +
+                           uniform<int>(static_cast<int>(threadIdx.x) / kWave)) *
+                          per;
+    const bool mine = lane < per && first + lane < n_rays;
+    if (threadIdx.x == 0) part = 0ull;
+    int my_start, my_n;
+    lane_range(packed_info, mine, first + lane, n_samples, my_start, my_n);
+    int my_count = 0, count = 0;
+    double carry = 0.0;
+    // Lanes past the ray's end read its last sample: the prefix sums of the
+    // lanes before them do not see it.  Where there is no chunk the first
+    // sample of the arrays is read: the same number of loads is outstanding
+    // on every path (after a branch that may have issued none, the wait for
+    // the present chunk's would also be one for the next's).
+    auto load = [&](const ChunkWalk& w, bool any) {
+        const int64_t s = any ? static_cast<int64_t>(w.start) + w.c + min(lane, w.n - w.c - 1) : 0;
+        return Interval{ts[s], te[s], sig[s]};
+    };
+    // The flags of a chunk are stored with the next one's work, before the
+    // loads it requests: the wait for a chunk's samples then never includes
+    // a store that was just issued.  Through a span, so that one store is
+    // issued on every path (of no flags at first).
+    uint8_t held_flag = 0;
+    int64_t held_s = 0;
+    int held_n = 0;
+    auto store_flags = [&]() {
+        __builtin_amdgcn_raw_buffer_store_b8(
+            held_flag, __builtin_amdgcn_make_buffer_rsrc(keep + held_s, 0, held_n, kRawBufferWord3), lane, 0, 0);
+    };
+    ChunkWalk w{ballot(my_n > 0), -1, 0, 0, 0};
+    bool more = w.next(my_start, my_n);
+    // works on chunk w (samples x) and leaves the next chunk's in y
+    auto step = [&](const Interval& x, Interval& y) {
+        ChunkWalk v = w;
+        more = v.next(my_start, my_n);
+        store_flags();
+        y = load(v, more);
+        const Trans t = transmittance_of(x.sigma * (x.t1 - x.t0), carry);
+        const int left = w.n - w.c;
+        const int keep_n = chunk_keep_n(left, t.t_in, eps);
+        const bool k = lane < min(keep_n, left) && alpha_of(t.tau) >= alpha_thre;
+        held_flag = k ? 1 : 0;
+        held_s = static_cast<int64_t>(w.start) + w.c;
+        held_n = min(left, kWave);
+        count += static_cast<int>(__popcll(ballot(k)));
+        if (keep_n < kWave) {  // behind the cut
+            for (int c = w.c + kWave + lane; c < w.n; c += kWave) keep[static_cast<int64_t>(w.start) + c] = 0;
+            if (more && v.ray == w.ray) {
+                more = v.next_ray(my_start, my_n);
+                y = load(v, more);
             }
-            for (; c < n; c += kWave) {  // behind the cut
-                if (c + lane < n) keep[start + c + lane] = 0;
-            }
-            if (lane == 0) packed_out[2 * r + 1] = count;
-            total += count;
+        }
+        if (!more || v.ray != w.ray) {  // the ray ends
+            if (lane == w.ray) my_count = count;
+            count = 0;
+            carry = 0.0;
         } else {
-            const int64_t out0 = packed_out[2 * r];
-            const int limit = uniform<int>(packed_out[2 * r + 1]);
-            int written = 0;
-            for (int c = 0; c < n && written < limit; c += kWave) {
-                const int i = c + lane;
-                const int64_t s = start + i;
-                const bool k = i < n && keep[s] != 0;
-                const uint64_t m = ballot(k);
-                const int idx = written + bits_below(m);
-                if (k && idx < limit) {
-                    const int64_t pos = out0 + idx;
-                    if (pos >= 0 && pos < capacity) {
-                        ri_out[pos] = static_cast<int32_t>(r);
-                        ts_out[pos] = ts[s];
-                        te_out[pos] = te[s];
-                        if (sig_out != nullptr) sig_out[pos] = sig[s];
-                    } else {
-                        overflow = true;
-                    }
-                }
-                written += __popcll(m);
+            carry += static_cast<double>(read_lane(t.incl, 63));
+        }
+        w = v;
+    };
+    if (more) {
+        Interval x = load(w, more), y;
+        while (true) {
+            step(x, y);
+            if (!more) break;
+            step(y, x);
+            if (!more) break;
+        }
+        store_flags();
+    }
+    if (mine) packed_out[2 * (first + lane) + 1] = my_count;
+    __syncthreads();
+    if (my_count > 0) atomicAdd(reinterpret_cast<unsigned long long*>(&part), static_cast<unsigned long long>(my_count));
+    __syncthreads();
+    if (threadIdx.x == 0) part_sums[block] = static_cast<int64_t>(part);
+}
+
+// Samples kept by the count pass, in a pipeline of three chunks: the flags
+// of the next one are requested, then the kept samples of this one, and the
+// samples of the one before go into a ring in LDS at their output position,
+// from which whole aligned blocks of 64 positions are stored.
+// 8.5 M kept of 33.0 M samples, 262,144 rays: 138 us (a chunk's flags, then its
+// samples, then their stores, one after the other) -> 102 us.
+constexpr int kPruneRing = 2 * kWave;
+
+struct PruneRing {
+    float4 sample[kPruneRing];  // t_start, t_end, sigma, ray of the wave
+};
+
+template <bool SIGMA>
+__global__ __launch_bounds__(kRenderThreads) void prune_fill_kernel(
+    const int32_t* __restrict__ packed_info, int64_t n_rays, int64_t n_samples, const float* __restrict__ ts,
+    const float* __restrict__ te, const float* __restrict__ sig, const uint8_t* __restrict__ keep,
+    const int32_t* __restrict__ packed_out, int64_t capacity, int32_t* __restrict__ ri_out,
+    float* __restrict__ ts_out, float* __restrict__ te_out, float* __restrict__ sig_out,
+    int32_t* __restrict__ status, int per) {
+    const int lane = lane_id();
+    const int64_t first = (xcd_grouped<16>(blockIdx.x, gridDim.x) * kRaysPerRenderBlock +
+                           uniform<int>(static_cast<int>(threadIdx.x) / kWave)) *
+                          per;
+    const bool mine = lane < per && first + lane < n_rays;
+    int my_start, my_n, my_out = 0, my_limit = 0;
+    lane_range(packed_info, mine, first + lane, n_samples, my_start, my_n);
+    if (mine) {
+        my_out = packed_out[2 * (first + lane)];
+        my_limit = packed_out[2 * (first + lane) + 1];
+    }
+    if (my_limit <= 0) my_n = 0;
+    auto load_keep = [&](const ChunkWalk& w, bool any) {
+        return keep[any ? static_cast<int64_t>(w.start) + w.c + min(lane, w.n - w.c - 1) : 0];
+    };
+    __shared__ PruneRing rings[kRenderThreads / kWave];
+    PruneRing& ring = rings[uniform<int>(static_cast<int>(threadIdx.x) / kWave)];
+    int64_t head = 0, tail = 0;  // positions [head, tail) are in the ring
+    bool overflow = false;
+    // stores the ring's positions up to `end`, all in one block of 64
+    auto store_block = [&](int64_t end) {
+        wave_lds_sync();
+        const int64_t p = (head & ~static_cast<int64_t>(kWave - 1)) + lane;
+        if (p >= head && p < end) {
+            const float4 v = ring.sample[p & (kPruneRing - 1)];
+            if (p >= 0 && p < capacity) {
+                ri_out[p] = static_cast<int32_t>(first + __builtin_bit_cast(int, v.w));
+                ts_out[p] = v.x;
+                te_out[p] = v.y;
+                if (SIGMA) sig_out[p] = v.z;
+            } else {
+                overflow = true;
             }
         }
-    }
-    if (!PRUNE_FILL) {
-        if (lane == 0) wave_total[wave] = total;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int64_t sum = 0;
-            for (int w = 0; w < kRaysPerRenderBlock; ++w) sum += wave_total[w];
-            block_sums[blockIdx.x] = sum;
+        wave_lds_sync();
+        head = end;
+    };
+    // samples on their way from memory to the ring
+    struct Held {
+        Interval x;
+        uint64_t kept;  // lanes that hold one
+        int ray, n;
+        int64_t pos;  // of the first
+    };
+    Held held{{0.0f, 0.0f, 0.0f}, 0ull, 0, 0, 0};
+    auto queue_held = [&]() {
+        if (held.n == 0) return;
+        if (held.pos != tail) {  // (the rays' outputs follow each other: the wave's first)
+            if (head < tail) store_block(tail);
+            head = tail = held.pos;
         }
-    } else if (overflow && status != nullptr) {
-        *status = NACC_ECAPACITY;
+        if (__builtin_amdgcn_inverse_ballot_w64(held.kept)) {
+            ring.sample[(tail + bits_below(held.kept)) & (kPruneRing - 1)] =
+                make_float4(held.x.t0, held.x.t1, held.x.sigma, __builtin_bit_cast(float, held.ray));
+        }
+        tail += held.n;
+        const int64_t end = (head | (kWave - 1)) + 1;
+        if (tail >= end) store_block(end);
+    };
+    int written = 0;   // of the present ray
+    int64_t last = 0;  // a sample kept before: what the lanes that keep none read again
+    ChunkWalk w{ballot(my_n > 0), -1, 0, 0, 0};
+    bool more = w.next(my_start, my_n);
+    uint8_t flag = more ? load_keep(w, more) : 0;
+    while (more) {
+        ChunkWalk v = w;
+        const bool more_v = v.next(my_start, my_n);
+        const uint8_t flag_v = load_keep(v, more_v);
+        uint64_t m = ballot(flag != 0 && lane < w.n - w.c);
+        const int room = read_lane(my_limit, w.ray) - written;
+        if (static_cast<int>(__popcll(m)) > room) m &= ballot(bits_below(m) < room);
+        const int64_t s = static_cast<int64_t>(w.start) + w.c;
+        if (m != 0ull) last = s + static_cast<int64_t>(__builtin_ctzll(m));
+        const int64_t i = __builtin_amdgcn_inverse_ballot_w64(m) ? s + lane : last;
+        Held h;
+        h.x = Interval{ts[i], te[i], SIGMA ? sig[i] : 0.0f};
+        h.kept = m;
+        h.ray = w.ray;
+        h.n = static_cast<int>(__popcll(m));
+        h.pos = static_cast<int64_t>(read_lane(my_out, w.ray)) + written;
+        queue_held();
+        held = h;
+        written = more_v && v.ray == w.ray ? written + h.n : 0;
+        w = v;
+        more = more_v;
+        flag = flag_v;
     }
+    queue_held();
+    if (head < tail) store_block(tail);
+    if (overflow && status != nullptr) *status = NACC_ECAPACITY;
+}
+
+// Rays per wave of the pruning kernels, and their workgroups (each one a part
+// of the scan).  The first chunk of a wave waits for its range, so large
+// batches take several rays per wave (1, 4, 8 rays: 321, 241, 243 us a call
+// for 262,144 box rays, 265, 187, 167 us for as many unbounded ones); at
+// 65,536 rays 8 leave too few waves (107, 82, 86 and 101, 78, 91 us).  From
+// 131,073 rays on 8, then 16, so that there are at most kMaxParts parts or
+// each one is of kRaysPerBlock rays, as launch_starts wants them.
+int prune_rays(int64_t n_rays) {
+    int per = n_rays >= 32768 ? 4 : (n_rays >= 16384 ? 2 : 1);
+    while (per < kRaysPerBlock / kRaysPerRenderBlock && n_rays > kMaxParts * kRaysPerRenderBlock * per) per *= 2;
+    return per;
+}
+int64_t prune_parts(int64_t n_rays) {
+    const int64_t rays = static_cast<int64_t>(prune_rays(n_rays)) * kRaysPerRenderBlock;
+    return (n_rays + rays - 1) / rays;
 }
 
 __global__ void prune_status_kernel(int32_t* status) { *status = NACC_OK; }
@@ -1027,8 +1202,9 @@ int nacc_render_fwd_bwd_mse_noalloc(const int32_t* packed_info, int64_t n_rays, 
 
 int64_t nacc_prune_workspace_size(int64_t n_rays) {
     if (n_rays < 0) return -1;
-    const int64_t nb = num_blocks(n_rays);  // the workgroup sums, then the scan's scratch
-    return (((nb + scan_scratch_values(nb)) * static_cast<int64_t>(sizeof(int64_t)) + 255) / 256) * 256;
+    const int64_t parts = prune_parts(n_rays);  // the workgroup sums, then the scan's scratch
+    const int64_t values = parts + (parts > kMaxParts ? scan_scratch_values(parts) : 0);
+    return ((values * static_cast<int64_t>(sizeof(int64_t)) + 255) / 256) * 256;
 }
 
 int nacc_prune_count(const int32_t* packed_info, int64_t n_rays, int64_t n_samples, const float* t_starts,
@@ -1053,19 +1229,19 @@ int nacc_prune_count(const int32_t* packed_info, int64_t n_rays, int64_t n_sampl
                  "workspace of %zu bytes, need %lld", workspace_bytes, static_cast<long long>(need));
     hipStream_t s = as_stream(stream);
     int64_t* sums = static_cast<int64_t*>(workspace);
-    const int64_t nb = num_blocks(n_rays);
-    if (nb > 0) {
-        hipLaunchKernelGGL(prune_kernel<false>, dim3(static_cast<unsigned>(nb)), dim3(kRenderThreads), 0, s,
-                           packed_info, n_rays, n_samples, t_starts, t_ends, sigmas, early_stop_eps, alpha_thre, keep,
-                           packed_out, sums, 0, nullptr, nullptr, nullptr, nullptr, nullptr);
-        int st = check_launch("prune count");
-        if (st != NACC_OK) return st;
+    if (n_rays == 0) {
+        scan_exclusive(sums, 0, total, nullptr, s);
+        return check_launch("prune scan");
     }
-    scan_exclusive(sums, nb, total, sums + nb, s);
-    int st = check_launch("prune scan");
-    if (st != NACC_OK || nb == 0) return st;
-    hipLaunchKernelGGL(finalize_starts_kernel, dim3(static_cast<unsigned>(nb)), dim3(kRaysPerBlock), 0, s, sums,
-                       n_rays, packed_out);
+    const int per = prune_rays(n_rays);
+    const int64_t parts = prune_parts(n_rays);
+    hipLaunchKernelGGL(prune_count_kernel, dim3(static_cast<unsigned>(parts)), dim3(kRenderThreads), 0, s, packed_info,
+                       n_rays, n_samples, t_starts, t_ends, sigmas, early_stop_eps, alpha_thre, keep, packed_out, sums,
+                       per);
+    int st = check_launch("prune count");
+    if (st != NACC_OK) return st;
+    launch_starts(sums, parts, __builtin_ctz(static_cast<unsigned>(per * kRaysPerRenderBlock)), n_rays, packed_out,
+                  total, s);
     return check_launch("prune starts");
 }
 
@@ -1094,12 +1270,12 @@ int nacc_prune_fill(const int32_t* packed_info, int64_t n_rays, int64_t n_sample
         int st = check_launch("prune status");
         if (st != NACC_OK) return st;
     }
-    const int64_t nb = num_blocks(n_rays);
-    if (nb == 0) return NACC_OK;
-    hipLaunchKernelGGL(prune_kernel<true>, dim3(static_cast<unsigned>(nb)), dim3(kRenderThreads), 0, s, packed_info,
-                       n_rays, n_samples, t_starts, t_ends, sigmas, 0.0f, 0.0f, const_cast<uint8_t*>(keep),
-                       const_cast<int32_t*>(packed_out), nullptr, capacity, ray_indices_out, t_starts_out, t_ends_out,
-                       sigmas_out, status);
+    if (n_rays == 0) return NACC_OK;
+    const int per = prune_rays(n_rays);
+    auto kernel = sigmas_out != nullptr ? prune_fill_kernel<true> : prune_fill_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(prune_parts(n_rays))), dim3(kRenderThreads), 0, s,
+                       packed_info, n_rays, n_samples, t_starts, t_ends, sigmas, keep, packed_out, capacity,
+                       ray_indices_out, t_starts_out, t_ends_out, sigmas_out, status, per);
     return check_launch("prune fill");
 }
 

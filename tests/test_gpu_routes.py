@@ -111,3 +111,40 @@ def test_starts_and_totals(n_rays, waves):
     assert int(count.sum()) == ri.numel() == ts.numel()
     assert torch.equal(packed[:, 0].long(), count.cumsum(0) - count)
     assert torch.equal(ri.long(), torch.repeat_interleave(torch.arange(n_rays, device="cuda"), count))
+
+
+@pytest.mark.parametrize("n_rays", [1, 5, 16383, 16384, 32768, 131072, 131073, 262144, 262145, 600000])
+def test_prune_rays_per_wave(n_rays):
+    """1, 2, 4, 8 and 16 rays per wave of the pruning kernels: rays of no, one
+    and many chunks, some cut, most samples of some below the threshold;
+    against the flags' definition in plain torch on the kept samples and the
+    rendering kernel's cut."""
+    nacc = _nacc()
+    rng = np.random.default_rng(77)
+    count = rng.choice([0, 1, 63, 64, 65, 130, 200], n_rays, p=[0.4, 0.25, 0.1, 0.1, 0.05, 0.05, 0.05])
+    start = np.concatenate([[0], np.cumsum(count)[:-1]])
+    packed = _cuda(np.stack([start, count], 1).astype(np.int32))
+    e = int(count.sum())
+    g = torch.Generator(device="cuda").manual_seed(78)
+    ts = torch.rand(e, generator=g, device="cuda")
+    te = ts + 0.01
+    sig = torch.rand(e, generator=g, device="cuda") ** 4 * 200.0
+    out, ri, ts_o, te_o, sg_o = nacc.prune_samples(packed, ts, te, sig, 1e-2, 0.05)
+    kept = torch.empty(n_rays, dtype=torch.int32, device="cuda")
+    rgb = torch.zeros((e, 3), device="cuda")
+    c3, a1, d1 = (torch.empty((n_rays, k), device="cuda") for k in (3, 1, 1))
+    nacc._lib.render_fwd(packed, ts, te, sig, rgb, 1e-2, c3, a1, d1, None, kept)
+    ray = torch.repeat_interleave(torch.arange(n_rays, device="cuda"), _cuda(count))
+    alpha = -torch.expm1(-sig.double() * (te - ts).double())
+    sure = (alpha - 0.05).abs() > 1e-6  # away from the threshold
+    before_cut = torch.arange(e, device="cuda") - _cuda(start)[ray] < kept.long()[ray]
+    want = before_cut & (alpha >= 0.05)
+    if bool(sure.all()):
+        assert torch.equal(ri.long(), ray[want])
+        for got, src in ((ts_o, ts), (te_o, te), (sg_o, sig)):
+            assert torch.equal(got, src[want])
+    n_out = out[:, 1].long()
+    assert torch.equal(out[:, 0].long(), n_out.cumsum(0) - n_out) and int(n_out.sum()) == ri.numel()
+    low = torch.zeros(n_rays, dtype=torch.long, device="cuda").index_add_(0, ray, (want & sure).long())
+    high = torch.zeros(n_rays, dtype=torch.long, device="cuda").index_add_(0, ray, (want | (before_cut & ~sure)).long())
+    assert bool(((n_out >= low) & (n_out <= high)).all())
