@@ -114,16 +114,31 @@ __global__ __launch_bounds__(kThreads) void update_max_kernel(float* __restrict_
     }
 }
 
-// One lane per cell; the wave's ballot is bits [64 w, 64 w + 64).
+// A wave packs kPackRuns runs of 64 cells, one ballot each, all their loads
+// in flight together; its words are stored in one piece, lane i the run's
+// half i.  Bound by HBM: 8.4 M cells 15 us with one run per wave -> 6.1 us.
+constexpr int kPackRuns = 16;
+
 __global__ __launch_bounds__(kThreads) void pack_kernel(const float* __restrict__ occ, int64_t n_cells,
                                                          float threshold, uint32_t* __restrict__ bits) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-    const bool set = i < n_cells && occ[i] > threshold;
-    const uint64_t m = ballot(set);
     const int lane = lane_id();
-    const int64_t word = (i - lane) / 32;
-    if (lane == 0 && word < n_cells / 32) bits[word] = static_cast<uint32_t>(m);
-    if (lane == 32 && word + 1 < n_cells / 32) bits[word + 1] = static_cast<uint32_t>(m >> 32);
+    const int64_t first = (static_cast<int64_t>(blockIdx.x) * (kThreads / kWave) +
+                           uniform<int>(static_cast<int>(threadIdx.x) / kWave)) *
+                          (kPackRuns * kWave);
+    float v[kPackRuns];
+#pragma unroll
+    for (int k = 0; k < kPackRuns; ++k) {
+        const int64_t i = first + k * kWave + lane;
+        v[k] = i < n_cells ? occ[i] : threshold;  // not above the threshold
+    }
+    uint32_t word = 0u;
+#pragma unroll
+    for (int k = 0; k < kPackRuns; ++k) {
+        const uint64_t m = ballot(v[k] > threshold);
+        if (lane >> 1 == k) word = static_cast<uint32_t>((lane & 1) != 0 ? m >> 32 : m);
+    }
+    const int64_t w = first / 32 + lane;
+    if (lane < 2 * kPackRuns && w < n_cells / 32) bits[w] = word;
 }
 
 // Skip field, per grid: one byte per coarse cell of 4x4x4 fine cells (C
@@ -131,8 +146,13 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const float* __restrict_
 // nearest coarse cell that holds an occupied fine cell).  The L-infinity
 // distance separates over the axes,
 //   dist(a,b,c) = min_da max(|da|, min_db max(|db|, min_dc max(|dc|, e))),
-// e = 0 at occupied coarse cells and the cap elsewhere, so it is built by a
-// coarse-occupancy pass and one windowed pass per axis (window +-cap).
+// e = 0 at occupied coarse cells and the cap elsewhere.  Grids of up to
+// kPlaneCells coarse cells per axis (res <= 512) are built plane by plane in
+// LDS: the coarse occupancy of a plane of constant x and its distances along
+// z and y in one launch, those along x in planes of constant y in another.
+// Bound by latency (a few dependent LDS reads per cell and axis): four grids
+// of 128^3 cells 5.6 + 3.6 us, 3.3 + 3 x 5.5 us with a launch for the occupancy and
+// one per axis, each reading its window from memory; larger grids still are.
 
 // Coarse occupancy: one lane per coarse cell, 16 fine-row reads (the 4 bits
 // of a row lie in one word since 4 | res).
@@ -156,6 +176,77 @@ __global__ __launch_bounds__(kThreads) void coarse_kernel(const uint32_t* __rest
         }
     }
     out[id] = any != 0u ? 0 : NACC_SKIP_CAP;
+}
+
+// Whether the coarse cell (x, y, z) holds an occupied fine cell.
+__device__ __forceinline__ bool coarse_occupied(const uint32_t* __restrict__ fine, int res, int x, int y, int z) {
+    uint32_t any = 0u;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const uint32_t b = (static_cast<uint32_t>(4 * x + (i >> 2)) * static_cast<uint32_t>(res) +
+                            static_cast<uint32_t>(4 * y + (i & 3))) *
+                               static_cast<uint32_t>(res) +
+                           static_cast<uint32_t>(4 * z);
+        any |= fine[b >> 5] >> (b & 31u);
+    }
+    return (any & 0xFu) != 0u;
+}
+
+// One axis of the distance of a cell at position `pos` of `c`, from its value
+// and its neighbours' at +-t `stride` in LDS, kWindow values of t at a time,
+// their reads in flight together.  A neighbour past the end is replaced by
+// the last cell, which lies nearer and so never lowers the minimum.
+constexpr int kWindow = 5;
+static_assert(NACC_SKIP_CAP % kWindow == 0, "whole windows up to the cap");
+
+__device__ __forceinline__ uint8_t axis_distance(const uint8_t* plane, int i, int pos, int c, int stride) {
+    int best = plane[i];
+    for (int t0 = 1; t0 < best; t0 += kWindow) {  // best <= the cap
+        int v[kWindow];
+#pragma unroll
+        for (int k = 0; k < kWindow; ++k) {
+            const int t = t0 + k;
+            v[k] = min(static_cast<int>(plane[i - min(t, pos) * stride]),
+                       static_cast<int>(plane[i + min(t, c - 1 - pos) * stride]));
+        }
+#pragma unroll
+        for (int k = 0; k < kWindow; ++k) best = min(best, max(t0 + k, v[k]));
+    }
+    return static_cast<uint8_t>(best);
+}
+
+constexpr int kPlaneCells = 128;
+constexpr int kPlaneThreads = 1024;
+
+// Workgroup grid c + x: occupancy, then distances along z and y.
+__global__ __launch_bounds__(kPlaneThreads) void skip_planes_kernel(const uint32_t* __restrict__ bits, int res,
+                                                                    uint32_t words, uint8_t* __restrict__ out) {
+    __shared__ uint8_t a[kPlaneCells * kPlaneCells], b[kPlaneCells * kPlaneCells];
+    const int c = res / 4, n = c * c;
+    const int x = static_cast<int>(blockIdx.x) % c;
+    const uint32_t* fine = bits + static_cast<int64_t>(blockIdx.x / static_cast<unsigned>(c)) * words;
+    for (int i = threadIdx.x; i < n; i += kPlaneThreads) {
+        a[i] = coarse_occupied(fine, res, x, i / c, i % c) ? 0 : NACC_SKIP_CAP;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += kPlaneThreads) b[i] = axis_distance(a, i, i % c, c, 1);
+    __syncthreads();
+    uint8_t* dst = out + static_cast<int64_t>(blockIdx.x) * n;
+    for (int i = threadIdx.x; i < n; i += kPlaneThreads) dst[i] = axis_distance(b, i, i / c, c, c);
+}
+
+// Workgroup grid c + y: distances along x.
+__global__ __launch_bounds__(kPlaneThreads) void skip_x_kernel(const uint8_t* __restrict__ in, int c,
+                                                               uint8_t* __restrict__ out) {
+    __shared__ uint8_t a[kPlaneCells * kPlaneCells];
+    const int n = c * c;
+    const int64_t first = static_cast<int64_t>(blockIdx.x / static_cast<unsigned>(c)) * n * c +
+                          static_cast<int64_t>(blockIdx.x % static_cast<unsigned>(c)) * c;
+    for (int i = threadIdx.x; i < n; i += kPlaneThreads) a[i] = in[first + static_cast<int64_t>(i / c) * n + i % c];
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += kPlaneThreads) {
+        out[first + static_cast<int64_t>(i / c) * n + i % c] = axis_distance(a, i, i / c, c, c);
+    }
 }
 
 // One axis of the distance: out = min over |t| <= cap of max(|t|, in[cell + t
@@ -257,6 +348,19 @@ int nacc_grid_build_skip(const uint32_t* bits, const nacc_grid_desc* grid, uint8
     uint8_t* field = skip;
     uint8_t* scratch = skip + n;
     hipStream_t s = as_stream(stream);
+    uint32_t* halo = reinterpret_cast<uint32_t*>(skip + halo_offset(grid->res, grid->n_grids));
+    if (c <= kPlaneCells) {
+        const dim3 planes(static_cast<unsigned>(static_cast<int64_t>(c) * grid->n_grids));
+        hipLaunchKernelGGL(skip_planes_kernel, planes, dim3(kPlaneThreads), 0, s, bits, grid->res,
+                           static_cast<uint32_t>(cells / 32), scratch);
+        int st = check_launch("grid skip planes");
+        if (st != NACC_OK) return st;
+        hipLaunchKernelGGL(skip_x_kernel, planes, dim3(kPlaneThreads), 0, s, scratch, c, field);
+        st = check_launch("grid skip distance");
+        if (st != NACC_OK) return st;
+        launch_halo(bits, grid->res, grid->n_grids, halo, s);
+        return check_launch("grid skip halo");
+    }
     hipLaunchKernelGGL(coarse_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, s, bits, grid->res, grid->n_grids,
                        static_cast<uint32_t>(cells / 32), scratch);
     int st = check_launch("grid skip coarse");
@@ -273,8 +377,7 @@ int nacc_grid_build_skip(const uint32_t* bits, const nacc_grid_desc* grid, uint8
         src = dst;
         dst = t;
     }
-    launch_halo(bits, grid->res, grid->n_grids, reinterpret_cast<uint32_t*>(skip + halo_offset(grid->res, grid->n_grids)),
-                s);
+    launch_halo(bits, grid->res, grid->n_grids, halo, s);
     return check_launch("grid skip halo");
 }
 
@@ -284,8 +387,8 @@ int nacc_grid_pack(const float* occ, int64_t n_cells, float threshold, uint32_t*
                  static_cast<long long>(n_cells));
     NACC_REQUIRE(n_cells == 0 || (occ != nullptr && bits != nullptr), NACC_EINVAL, "arguments must be non-NULL");
     if (n_cells == 0) return NACC_OK;
-    hipLaunchKernelGGL(pack_kernel, dim3(blocks_for(n_cells)), dim3(kThreads), 0, as_stream(stream), occ, n_cells,
-                       threshold, bits);
+    hipLaunchKernelGGL(pack_kernel, dim3(blocks_for((n_cells + kPackRuns - 1) / kPackRuns)), dim3(kThreads), 0,
+                       as_stream(stream), occ, n_cells, threshold, bits);
     return check_launch("grid pack");
 }
 

@@ -148,3 +148,43 @@ def test_prune_rays_per_wave(n_rays):
     low = torch.zeros(n_rays, dtype=torch.long, device="cuda").index_add_(0, ray, (want & sure).long())
     high = torch.zeros(n_rays, dtype=torch.long, device="cuda").index_add_(0, ray, (want | (before_cut & ~sure)).long())
     assert bool(((n_out >= low) & (n_out <= high)).all())
+
+
+@pytest.mark.parametrize("res,p_occ", [(4, 0.1), (12, 0.02), (20, 0.002), (100, 1e-5), (128, 2e-6), (160, 1e-5),
+                                       (512, 1e-6), (516, 1e-7)])
+def test_skip_buffer_of_any_resolution(res, p_occ):
+    """Distances and halo bits of grids whose rows fill words, end inside
+    them, or hold several (and of the first grid that takes the passes per
+    axis): against scipy."""
+    from scipy.ndimage import distance_transform_cdt, maximum_filter
+    nacc = _nacc()
+    n = 2
+    mask = synth.random_mask(n * res ** 3, p_occ, 80 + res)
+    mask[-1] = 1
+    grid = nacc.OccupancyGrid(BOX, res, n_grids=n)
+    grid.set_occupancy(_cuda(mask.astype(np.float32)), 0.5)
+    torch.cuda.synchronize()
+    buf = grid.skip.cpu().numpy()
+    c, h = res // 4, res // 2
+    words = -(-h ** 3 // 64) * 2
+    halo = np.unpackbits(buf[-(-2 * c ** 3 * n // 256) * 256:].reshape(n, 4 * words), axis=1, bitorder="little")
+    for i in range(n):
+        m = mask[i * res ** 3:(i + 1) * res ** 3].reshape(res, res, res).astype(bool)
+        coarse = m.reshape(c, 4, c, 4, c, 4).any(axis=(1, 3, 5))
+        far = distance_transform_cdt(~coarse, metric="chessboard") if coarse.any() else np.full(coarse.shape, 15)
+        assert np.array_equal(buf[i * c ** 3:(i + 1) * c ** 3], np.minimum(far, 15).ravel()), f"distances {i}"
+        near = maximum_filter(m, size=5, mode="constant").reshape(h, 2, h, 2, h, 2).any(axis=(1, 3, 5))
+        assert np.array_equal(halo[i, :h ** 3], near.ravel()) and not halo[i, h ** 3:].any(), f"halo {i}"
+
+
+@pytest.mark.parametrize("n_cells", [32, 992, 1024, 4096, 4128, 100000])
+def test_pack_runs(n_cells):
+    """Cells short of, at and past the 1,024 of a wave and the 4,096 of a
+    workgroup; values at the threshold and NaN are not above it."""
+    lib = _nacc()._lib
+    rng = np.random.default_rng(n_cells)
+    occ = rng.choice(np.array([0.0, 0.01, 0.02, -1.0, np.nan, np.inf], np.float32), n_cells)
+    bits = torch.full((n_cells // 32 + 1,), -1, dtype=torch.int32, device="cuda")
+    lib.grid_pack(_cuda(occ), 0.01, bits[:-1])
+    got = np.unpackbits(bits.cpu().numpy().view(np.uint8), bitorder="little")
+    assert np.array_equal(got[:n_cells], occ > np.float32(0.01)) and got[n_cells:].all()
