@@ -14,6 +14,7 @@
 // channels, no background and no threshold the results are bit for bit
 // those of the colour kernels.
 #include <cmath>
+#include <utility>
 
 #include "common.h"
 #include "transmittance.h"
@@ -59,50 +60,6 @@ __device__ __forceinline__ Masked masked(const Interval& x, float alpha_thre) {
     m.on = !(alpha_thre > 0.0f) || m.alpha >= alpha_thre;
     m.tau = m.on ? tau : 0.0f;
     return m;
-}
-
-// Channels [c0, c0 + cb) of sample s (cb <= kBlock, wave-uniform), zeros
-// past cb.  VEC4: rows start 16-byte aligned and cb is a multiple of 4.
-template <bool VEC4>
-__device__ __forceinline__ void load_block(bool valid, int64_t s, const float* __restrict__ attrs, int n_ch, int c0,
-                                           int cb, float a[kBlock]) {
-    const float* row = attrs + s * n_ch + c0;
-#pragma unroll
-    for (int k = 0; k < kBlock; k += 4) {
-        if (k < cb) {
-            if (VEC4) {
-                const float4 v = valid ? *reinterpret_cast<const float4*>(row + k) : make_float4(0.f, 0.f, 0.f, 0.f);
-                a[k] = v.x;
-                a[k + 1] = v.y;
-                a[k + 2] = v.z;
-                a[k + 3] = v.w;
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) a[k + j] = (valid && k + j < cb) ? row[k + j] : 0.0f;
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) a[k + j] = 0.0f;
-        }
-    }
-}
-
-// Row s of the attribute gradient: w * g, or zeros (positive zeros, as the
-// colour kernels write) when `zero`.
-template <bool VEC4>
-__device__ __forceinline__ void store_scaled(int64_t s, float* __restrict__ g_attrs, int n_ch,
-                                             const float* __restrict__ g, float w, bool zero) {
-    float* row = g_attrs + s * n_ch;
-    if (VEC4) {
-        for (int k = 0; k < n_ch; k += 4) {
-            *reinterpret_cast<float4*>(row + k) =
-                zero ? make_float4(0.0f, 0.0f, 0.0f, 0.0f)
-                     : make_float4(w * uniform<float>(g[k]), w * uniform<float>(g[k + 1]),
-                                   w * uniform<float>(g[k + 2]), w * uniform<float>(g[k + 3]));
-        }
-    } else {
-        for (int k = 0; k < n_ch; ++k) row[k] = zero ? 0.0f : w * uniform<float>(g[k]);
-    }
 }
 
 // Rows of 4 or 8 channels, or of a multiple of 16 (16-byte aligned rows),
@@ -206,15 +163,94 @@ __device__ __forceinline__ void store_rows_staged(const Staged& g, float* __rest
     }
 }
 
-template <bool VEC4, int STAGE>
+// Other rows are read and written by their own lanes, CH <= 16 channels at a
+// time, a number known to the kernel: the compiler makes dword-aligned
+// accesses of up to four floats of them, where one access per channel visits
+// all of the wave's cache lines again for each.  Rows of up to 16 channels
+// have a kernel each (CH = n_ch); longer ones are taken four at a time, 16 to
+// a block, the last four ending with the row.
+// Bound by HBM.  4.6 M samples of 30,011 rays, 7 channels: forward 53 -> 34
+// us, backward 106 -> 75 us; forward and backward of 17 channels 484 -> 262
+// us, of 33 channels 1,665 -> 807 us, of 24 channels 480 -> 483 us.
+// (Regrouping such rows through LDS a float at a time measured slower, 7
+// channels 85 and 258 us: the index arithmetic.)
+template <int CH>
+struct __attribute__((packed, aligned(4))) Row {
+    float v[CH];
+};
+
+// Which channel a[k] holds after load_row at c0: c0 + k in rows of CH < 16
+// channels (c0 = 0), else the fours of the block from c0 on, the last of
+// which ends with the row; false where it holds none of the block or one
+// that another a[k] holds too.
+template <int CH>
+__device__ __forceinline__ bool channel_of(int k, int n_ch, int c0, int& channel) {
+    channel = c0 + k;
+    if (CH < kBlock) return true;
+    const int four = c0 + (k & ~3);
+    channel = min(four, n_ch - 4) + (k & 3);
+    return four < n_ch && channel >= four;
+}
+
+// The channels of sample s from c0 on, at most CH.
+template <int CH>
+__device__ __forceinline__ void load_row(bool valid, int64_t s, const float* __restrict__ attrs, int n_ch, int c0,
+                                         float a[kBlock]) {
+    const float* row = attrs + s * n_ch;
+    if (CH < kBlock || c0 + CH <= n_ch) {
+        Row<CH> r{};
+        if (valid) r = *reinterpret_cast<const Row<CH>*>(row + c0);
+#pragma unroll
+        for (int k = 0; k < CH; ++k) a[k] = r.v[k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < kBlock; k += 4) {
+            Row<4> r{};
+            if (c0 + k < n_ch) {
+                if (valid) r = *reinterpret_cast<const Row<4>*>(row + min(c0 + k, n_ch - 4));
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) a[k + j] = r.v[j];
+        }
+    }
+}
+
+// Row s of the attribute gradient: w g, or zeros (positive zeros, as the
+// colour kernels write) when `zero`.
+template <int CH>
+__device__ __forceinline__ void store_row(int64_t s, float* __restrict__ g_attrs, int n_ch,
+                                          const float* __restrict__ g, float w, bool zero) {
+    float* row = g_attrs + s * n_ch;
+    int c0 = 0;
+    for (; c0 + CH <= n_ch; c0 += CH) {
+        Row<CH> r;
+#pragma unroll
+        for (int k = 0; k < CH; ++k) r.v[k] = zero ? 0.0f : w * uniform<float>(g[c0 + k]);
+        *reinterpret_cast<Row<CH>*>(row + c0) = r;
+    }
+    if constexpr (CH == kBlock) {
+        auto four = [&](int c) {
+            Row<4> r;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) r.v[k] = zero ? 0.0f : w * uniform<float>(g[c + k]);
+            *reinterpret_cast<Row<4>*>(row + c) = r;
+        };
+        for (; c0 + 4 <= n_ch; c0 += 4) four(c0);
+        if (c0 < n_ch) four(n_ch - 4);
+    }
+}
+
+template <int STAGE, int CH>
 __global__ __launch_bounds__(kAttrThreads) void attrs_fwd_kernel(
     const int32_t* __restrict__ packed_info, int64_t n_rays, int64_t n_samples, const float* __restrict__ ts,
     const float* __restrict__ te, const float* __restrict__ sig, const float* __restrict__ attrs, int n_ch,
     float eps, float alpha_thre, const float* __restrict__ background, float* __restrict__ out,
     float* __restrict__ opacity, float* __restrict__ depth, float* __restrict__ weights) {
-    // STAGE 0: per-lane rows; 1: rows of one block (4, 8 or 16 channels)
-    // through LDS; 2: rows of several blocks of 16 through LDS
+    // STAGE 0: rows by their own lanes, CH channels at a time; 1: rows of one
+    // block (4, 8 or 16 channels) through LDS; 2: rows of several blocks of 16
+    // through LDS (CH = 16)
     constexpr bool STAGED = STAGE > 0, WIDE = STAGE == 2;
+    if (CH < kBlock) n_ch = CH;
     const int lane = lane_id();
     const int64_t r = xcd_grouped<16>(blockIdx.x, gridDim.x) * kAttrRays + uniform<int>(static_cast<int>(threadIdx.x) / kWave);
     if (r >= n_rays) return;
@@ -227,8 +263,7 @@ __global__ __launch_bounds__(kAttrThreads) void attrs_fwd_kernel(
     float4* stage = stage_all + (STAGED ? uniform<int>(static_cast<int>(threadIdx.x) / kWave) * kWave * 4 : 0);
     const Staged sg = staged_rows(n_ch);
     float total_a = 0.0f;
-    for (int c0 = 0; c0 < n_ch && (WIDE || c0 == 0 || !STAGED); c0 += kBlock) {
-        const int cb = min(kBlock, n_ch - c0);
+    for (int c0 = 0; c0 < n_ch && (STAGE != 1 || c0 == 0); c0 += CH) {
         const bool first = c0 == 0;
         float acc[kBlock];
 #pragma unroll
@@ -252,10 +287,10 @@ __global__ __launch_bounds__(kAttrThreads) void attrs_fwd_kernel(
             if (STAGED) {
                 exchange_rows(sg, rq, stage, a);
             } else {
-                load_block<VEC4>(valid, s, attrs, n_ch, c0, cb, a);
+                load_row<CH>(valid, s, attrs, n_ch, c0, a);
             }
 #pragma unroll
-            for (int k = 0; k < kBlock; ++k) acc[k] = __builtin_fmaf(w, a[k], acc[k]);
+            for (int k = 0; k < CH; ++k) acc[k] = __builtin_fmaf(w, a[k], acc[k]);
             if (first) {
                 acc_a += w;
                 acc_d = __builtin_fmaf(w, (x.t0 + x.t1) * 0.5f, acc_d);
@@ -281,26 +316,29 @@ __global__ __launch_bounds__(kAttrThreads) void attrs_fwd_kernel(
             }
         }
 #pragma unroll
-        for (int k = 0; k < kBlock; ++k) {
-            if (k < cb) {
+        for (int k = 0; k < CH; ++k) {
+            int ch;
+            if (channel_of<CH>(k, n_ch, c0, ch)) {
                 float v = wave_sum1(acc[k]);
-                if (background != nullptr) v += background[c0 + k] * (1.0f - total_a);
-                if (lane == 0) out[r * n_ch + c0 + k] = v;
+                if (background != nullptr) v += background[ch] * (1.0f - total_a);
+                if (lane == 0) out[r * n_ch + ch] = v;
             }
         }
     }
 }
 
-template <bool VEC4, int STAGE>
+template <int STAGE, int CH>
 __global__ __launch_bounds__(kAttrThreads) void attrs_bwd_kernel(
     const int32_t* __restrict__ packed_info, int64_t n_rays, int64_t n_samples, const float* __restrict__ ts,
     const float* __restrict__ te, const float* __restrict__ sig, const float* __restrict__ attrs, int n_ch,
     float eps, float alpha_thre, const float* __restrict__ background, const float* __restrict__ g_out,
     const float* __restrict__ g_opacity, const float* __restrict__ g_depth, float* __restrict__ g_sigmas,
     float* __restrict__ g_attrs) {
-    // STAGE 0: per-lane rows; 1: rows of one block (4, 8 or 16 channels)
-    // through LDS; 2: rows of several blocks of 16 through LDS
+    // STAGE 0: rows by their own lanes, CH channels at a time; 1: rows of one
+    // block (4, 8 or 16 channels) through LDS; 2: rows of several blocks of 16
+    // through LDS (CH = 16)
     constexpr bool STAGED = STAGE > 0, WIDE = STAGE == 2;
+    if (CH < kBlock) n_ch = CH;
     const int lane = lane_id();
     const int64_t r = xcd_grouped<16>(blockIdx.x, gridDim.x) * kAttrRays + uniform<int>(static_cast<int>(threadIdx.x) / kWave);
     if (r >= n_rays) return;
@@ -357,7 +395,7 @@ __global__ __launch_bounds__(kAttrThreads) void attrs_bwd_kernel(
         if (i < n) {
             const int64_t s = start + i;
             g_sigmas[s] = 0.0f;
-            store_scaled<VEC4>(s, g_attrs, n_ch, g, 0.0f, true);
+            store_row<(STAGED ? 4 : CH)>(s, g_attrs, n_ch, g, 0.0f, true);
         }
     }
     // backward, from the last kept chunk down
@@ -381,20 +419,37 @@ __global__ __launch_bounds__(kAttrThreads) void attrs_bwd_kernel(
         const float w = keep ? t.t_in * m.alpha : 0.0f;
         // v_i = g . a_i + (g_opacity - g . background) + g_depth m_i
         float dot = 0.0f;
-        for (int c0 = 0; c0 < n_ch && (WIDE || c0 == 0 || !STAGED); c0 += kBlock) {
-            const int cb = min(kBlock, n_ch - c0);
+        for (int c0 = 0; c0 < n_ch && (STAGE != 1 || c0 == 0); c0 += CH) {
             float a[kBlock];
             if (STAGED) {
                 if (WIDE && c0 > 0) rq = fetch_rows<WIDE>(sg, attrs, start + c, rows_read, c0);
                 exchange_rows(sg, rq, stage, a);
             } else {
-                load_block<VEC4>(i < kept, s, attrs, n_ch, c0, cb, a);
+                load_row<CH>(i < kept, s, attrs, n_ch, c0, a);
             }
+            if (CH < kBlock || c0 + CH <= n_ch) {  // a whole block: its part of g is read in one piece
 #pragma unroll
-            for (int k = 0; k < kBlock; ++k) {
-                if (k < cb) {
+                for (int k = 0; k < CH; ++k) {
                     dot = c0 + k == 0 ? uniform<float>(g[0]) * a[0]
                                       : __builtin_fmaf(uniform<float>(g[c0 + k]), a[k], dot);
+                }
+            } else {  // fours, the last one from where the row's other channels end (c0 > 0)
+#pragma unroll
+                for (int k = 0; k < CH; k += 4) {
+                    if (c0 + k + 4 <= n_ch) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            dot = __builtin_fmaf(uniform<float>(g[c0 + k + j]), a[k + j], dot);
+                        }
+                    } else if (c0 + k < n_ch) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            int ch;
+                            if (channel_of<CH>(k + j, n_ch, c0, ch)) {
+                                dot = __builtin_fmaf(uniform<float>(g[ch]), a[k + j], dot);
+                            }
+                        }
+                    }
                 }
             }
         }
@@ -413,7 +468,7 @@ __global__ __launch_bounds__(kAttrThreads) void attrs_bwd_kernel(
                 store_rows_staged<WIDE>(sg, g_attrs, start + c, min(n - c, kWave), c0, w, keep, gq);
             }
         } else if (valid) {
-            store_scaled<VEC4>(s, g_attrs, n_ch, g, w, !keep);
+            store_row<CH>(s, g_attrs, n_ch, g, w, !keep);
         }
         above = above + read_lane(incl, 0);
         p_end = p_start;
@@ -447,6 +502,20 @@ bool vec4_rows(const float* a, const float* b, int32_t n_ch) {
     return n_ch % 4 == 0 && (reinterpret_cast<uintptr_t>(a) % 16) == 0 && (reinterpret_cast<uintptr_t>(b) % 16) == 0;
 }
 
+// The kernels for rows by their own lanes: n_ch channels at a time up to
+// kBlock.
+template <int... I>
+auto attrs_fwd_rows(int n_ch, std::integer_sequence<int, I...>) {
+    constexpr decltype(&attrs_fwd_kernel<0, 1>) table[] = {attrs_fwd_kernel<0, I + 1>...};
+    return table[std::min(n_ch, kBlock) - 1];
+}
+
+template <int... I>
+auto attrs_bwd_rows(int n_ch, std::integer_sequence<int, I...>) {
+    constexpr decltype(&attrs_bwd_kernel<0, 1>) table[] = {attrs_bwd_kernel<0, I + 1>...};
+    return table[std::min(n_ch, kBlock) - 1];
+}
+
 }  // namespace
 
 extern "C" {
@@ -464,9 +533,9 @@ int nacc_render_attrs_fwd(const int32_t* packed_info, int64_t n_rays, int64_t n_
     const dim3 grid(static_cast<unsigned>((n_rays + kAttrRays - 1) / kAttrRays));
     hipStream_t s = as_stream(stream);
     const bool vec4 = vec4_rows(attrs, attrs, n_ch);
-    auto kernel = vec4 ? (n_ch <= kBlock ? (staged_width(n_ch) ? attrs_fwd_kernel<true, 1> : attrs_fwd_kernel<true, 0>)
-                                         : (staged_width(n_ch) ? attrs_fwd_kernel<true, 2> : attrs_fwd_kernel<true, 0>))
-                       : attrs_fwd_kernel<false, 0>;
+    auto kernel = !vec4 || !staged_width(n_ch) ? attrs_fwd_rows(n_ch, std::make_integer_sequence<int, kBlock>{})
+                  : n_ch <= kBlock              ? attrs_fwd_kernel<1, kBlock>
+                                                : attrs_fwd_kernel<2, kBlock>;
     hipLaunchKernelGGL(kernel, grid, dim3(kAttrThreads), 0, s, packed_info, n_rays, n_samples, t_starts, t_ends,
                        sigmas, attrs, n_ch, early_stop_eps, alpha_thre, background, out, opacity, depth, weights);
     return check_launch("render attrs fwd");
@@ -487,9 +556,9 @@ int nacc_render_attrs_bwd(const int32_t* packed_info, int64_t n_rays, int64_t n_
     const dim3 grid(static_cast<unsigned>((n_rays + kAttrRays - 1) / kAttrRays));
     hipStream_t s = as_stream(stream);
     const bool vec4 = vec4_rows(attrs, g_attrs, n_ch);
-    auto kernel = vec4 ? (n_ch <= kBlock ? (staged_width(n_ch) ? attrs_bwd_kernel<true, 1> : attrs_bwd_kernel<true, 0>)
-                                         : (staged_width(n_ch) ? attrs_bwd_kernel<true, 2> : attrs_bwd_kernel<true, 0>))
-                       : attrs_bwd_kernel<false, 0>;
+    auto kernel = !vec4 || !staged_width(n_ch) ? attrs_bwd_rows(n_ch, std::make_integer_sequence<int, kBlock>{})
+                  : n_ch <= kBlock              ? attrs_bwd_kernel<1, kBlock>
+                                                : attrs_bwd_kernel<2, kBlock>;
     hipLaunchKernelGGL(kernel, grid, dim3(kAttrThreads), 0, s, packed_info, n_rays, n_samples, t_starts, t_ends,
                        sigmas, attrs, n_ch, early_stop_eps, alpha_thre, background, g_out, g_opacity, g_depth,
                        g_sigmas, g_attrs);

@@ -188,3 +188,37 @@ def test_pack_runs(n_cells):
     lib.grid_pack(_cuda(occ), 0.01, bits[:-1])
     got = np.unpackbits(bits.cpu().numpy().view(np.uint8), bitorder="little")
     assert np.array_equal(got[:n_cells], occ > np.float32(0.01)) and got[n_cells:].all()
+
+
+@pytest.mark.parametrize("ch", list(range(1, 18)) + [20, 23, 24, 28, 31, 33, 47, 49])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_attribute_rows_of_any_width(ch, shift):
+    """Every channel of a row of any width, at 16-byte aligned addresses or
+    not, is rendered and gets its gradient as the only channel of a call of
+    its own, bit for bit; nothing beside the rows is written."""
+    nacc = _nacc()
+    packed, ts, te, sg, _ = synth.ragged_render_inputs(300, 81, mean_count=90.0)
+    packed, ts, te, sg = (_cuda(a) for a in (packed, ts, te, sg))
+    e, n = ts.numel(), packed.shape[0]
+    g = torch.Generator(device="cuda").manual_seed(82)
+    attrs = torch.randn(e * ch + shift, generator=g, device="cuda")[shift:].view(e, ch)
+    g_out = torch.randn((n, ch), generator=g, device="cuda")
+    bg = torch.rand(ch, generator=g, device="cuda")
+    lib = nacc._lib
+
+    def render(a, go, b, pad):
+        k = a.shape[1]
+        out, op, dep = (torch.empty((n, j), device="cuda") for j in (k, 1, 1))
+        lib.render_attrs_fwd(packed, ts, te, sg, a, 1e-2, 0.05, b, out, op, dep)
+        ga = torch.full((e * k + pad + 4,), 7.0, device="cuda")
+        gs = torch.empty_like(ts)
+        lib.render_attrs_bwd(packed, ts, te, sg, a, 1e-2, 0.05, b, go, None, None, gs, ga[pad:pad + e * k].view(e, k))
+        assert bool((ga[:pad] == 7.0).all()) and bool((ga[pad + e * k:] == 7.0).all())
+        return out, ga[pad:pad + e * k].view(e, k)
+
+    out, ga = render(attrs, g_out, bg, shift)
+    for k in range(ch):
+        one = render(attrs[:, k:k + 1].contiguous(), g_out[:, k:k + 1].contiguous(), bg[k:k + 1].contiguous(), 0)
+        assert torch.equal(out[:, k:k + 1].contiguous().view(torch.int32), one[0].view(torch.int32)), f"out {k}"
+        assert torch.equal(ga[:, k:k + 1].contiguous().view(torch.int32),
+                           one[1].contiguous().view(torch.int32)), f"g_attrs {k}"
