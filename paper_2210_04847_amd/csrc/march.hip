@@ -981,21 +981,52 @@ struct ConeTable {
     int n;  // entries: n_masks 8 + 1, or 0
 };
 
+// Steps of the cone recurrence, t + clamp(t * cone, dt, dt_max) in FP32,
+// from t while it is below `end`, at most `limit` of them: advances t and
+// returns their number, or -1 if one stalls (t + step == t).  t only grows,
+// so the three cases of the clamp follow each other; a loop each leaves only
+// the operations of its own case in the serial chain (2,560 steps, mostly
+// t + t * cone: 13 us with the clamp in every step, 6 us so).
+// A NaN t * cone (0 times infinity) steps by dt, a NaN dt_max is no limit,
+// as fmaxf and fminf have it.
+int64_t cone_steps(float cone, float dt, float dt_max, double end, int64_t limit, float& t) {
+    const float hi = std::isnan(dt_max) ? INFINITY : dt_max;
+    const float lo = std::fmin(dt, hi);
+    int64_t k = 0;
+    float x = t;
+    for (; k < limit && static_cast<double>(x) < end && !(x * cone > lo); ++k) {
+        const float x1 = x + lo;
+        if (!(x1 > x)) return -1;
+        x = x1;
+    }
+    for (; k < limit && static_cast<double>(x) < end; ++k) {
+        const float step = x * cone;
+        if (!(step < hi)) break;
+        const float x1 = x + step;
+        if (!(x1 > x)) return -1;
+        x = x1;
+    }
+    for (; k < limit && static_cast<double>(x) < end; ++k) {
+        const float x1 = x + hi;
+        if (!(x1 > x)) return -1;
+        x = x1;
+    }
+    t = x;
+    return k;
+}
+
 ConeTable cone_table(const StepK& p, int n_masks) {
     ConeTable tab;
     tab.n = 0;
     float t = p.near_plane;
     if (n_masks <= 0 || !std::isfinite(t)) return tab;
     const int n = n_masks * kTableStride + 1;
-    for (int i = 0; i < n; ++i) {
+    for (int i = 0; i + 1 < n; ++i) {
         tab.t[i] = t;
-        for (int u = 0; u < kConeBatch && i + 1 < n; ++u) {
-            const float step = std::fmin(std::fmax(t * p.cone, p.dt), p.dt_max);
-            const float t1 = t + step;
-            if (!(t1 > t)) return tab;  // stalls: no table
-            t = t1;
-        }
+        // stalls (or ends at infinity, as a stalled walk does): no table
+        if (cone_steps(p.cone, p.dt, p.dt_max, INFINITY, kConeBatch, t) != kConeBatch) return tab;
     }
+    tab.t[n - 1] = t;
     tab.n = n;
     return tab;
 }
@@ -1834,24 +1865,17 @@ double clip_span(const nacc_grid_desc& grid, const nacc_march_params& p) {
 // plane covers its (at most span long) range in no more steps than the
 // recurrence started at the near plane; two extra candidates absorb the
 // rounding of the sums.
-int64_t candidate_bound(const nacc_grid_desc& grid, const nacc_march_params& p) {
+// Bounds of `limit` or more are returned as `limit`.
+int64_t candidate_bound(const nacc_grid_desc& grid, const nacc_march_params& p, int64_t limit = kMaxCandidates) {
     const double span = clip_span(grid, p);
     if (!(span > 0.0)) return 0;
-    if (!std::isfinite(span)) return kMaxCandidates;
+    if (!std::isfinite(span)) return limit;
     if (p.cone == 0.0f) {
-        return std::min<int64_t>(kMaxCandidates, static_cast<int64_t>(std::ceil(span / p.dt)) + 2);
+        return std::min<int64_t>(limit, static_cast<int64_t>(std::ceil(span / p.dt)) + 2);
     }
-    const double end = static_cast<double>(p.near_plane) + span;
     float t = p.near_plane;
-    int64_t k = 0;
-    while (k < kMaxCandidates && static_cast<double>(t) < end) {
-        const float step = fminf(fmaxf(t * p.cone, p.dt), p.dt_max);
-        const float t1 = t + step;
-        if (!(t1 > t)) return kMaxCandidates;
-        t = t1;
-        ++k;
-    }
-    return std::min<int64_t>(kMaxCandidates, k + 2);
+    const int64_t k = cone_steps(p.cone, p.dt, p.dt_max, static_cast<double>(p.near_plane) + span, limit, t);
+    return k < 0 ? limit : std::min<int64_t>(limit, k + 2);
 }
 
 // Workgroups per group of kRaysPerBlock rays in the uniform-step count
@@ -1914,8 +1938,8 @@ Layout workspace_layout(int64_t n_rays, const nacc_grid_desc& grid, const nacc_m
     l.sums_bytes = align256((nb * march_split(nb, 1) + scan_scratch_values(nb)) * static_cast<int64_t>(sizeof(int64_t)));
     l.n_masks = 0;
     if (p.dt > 0.0f) {
-        const int64_t k = candidate_bound(grid, p);
-        l.n_masks = static_cast<int>(std::min<int64_t>((k + kWave - 1) / kWave, kMaxMaskChunks));
+        const int64_t k = candidate_bound(grid, p, int64_t{kMaxMaskChunks} * kWave);
+        l.n_masks = static_cast<int>((k + kWave - 1) / kWave);
     }
     l.bytes = l.sums_bytes + align256(n_rays * l.n_masks * static_cast<int64_t>(sizeof(uint64_t)));
     l.chunk_t_off = l.t_far_off = l.extra_off = l.base_off = l.seg_t_off = 0;

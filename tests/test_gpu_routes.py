@@ -222,3 +222,29 @@ def test_attribute_rows_of_any_width(ch, shift):
         assert torch.equal(out[:, k:k + 1].contiguous().view(torch.int32), one[0].view(torch.int32)), f"out {k}"
         assert torch.equal(ga[:, k:k + 1].contiguous().view(torch.int32),
                            one[1].contiguous().view(torch.int32)), f"g_attrs {k}"
+
+
+@pytest.mark.parametrize("read", [(0,), (1,), (2,), (0, 2), (1, 2)])
+@pytest.mark.parametrize("attrs", [False, True])
+def test_gradients_of_unread_outputs(read, attrs):
+    """A loss that leaves outputs out gives the gradients of one that reads
+    them times zero, exactly: zero gradients add zeros."""
+    import paper_2210_04847_amd as nacc
+    gen = torch.Generator().manual_seed(5)
+    counts = torch.tensor([0, 3, 64, 65, 200, 1])
+    starts = torch.cumsum(counts, 0) - counts
+    packed = torch.stack([starts, counts], 1).to(torch.int32).cuda()
+    e = int(counts.sum())
+    ts = torch.rand(e, generator=gen).cuda()
+    sig0, at0 = torch.rand(e, generator=gen).cuda(), torch.rand(e, 3, generator=gen).cuda()
+    grads = []
+    for zeros in (False, True):
+        sig, at = sig0.clone().requires_grad_(), at0.clone().requires_grad_()
+        outs = (nacc.render_attrs if attrs else nacc.rendering)(packed, ts, ts + 0.01, sig, at)
+        loss = sum((outs[i] ** 2).sum() for i in read)
+        if zeros:
+            loss = loss + sum((outs[i] * 0.0).sum() for i in range(3) if i not in read)
+        loss.backward()
+        grads.append((sig.grad, at.grad))
+    for a, b in zip(*grads):
+        assert torch.equal(a, b)
