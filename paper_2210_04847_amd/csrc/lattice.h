@@ -25,6 +25,7 @@ struct GridK {
     float top;         // (float)(res - 1)
     float base;        // cascade: half-extent of level 0 (a power of two)
     float inv_base;    // 1 / base (exact)
+    int wide_levels;   // cascade: base outside [2^-60, 2^60], see segment_hits
     int res;
     int n_grids;
     uint32_t words;    // 32-bit words per grid
@@ -96,15 +97,13 @@ __device__ __forceinline__ float clamp_cell(float u, float top) { return __built
 // Cascade level of a point with m = max_i |x_i|: the number of levels
 // l < n_grids - 1 with m > base 2^l, i.e. the smallest l with m <= base 2^l,
 // clamped to the last level.  q = m / base is exact (base is a power of
-// two), and the smallest l with q <= 2^l is read off q's exponent and
-// mantissa: q = 1.f 2^(e-127) gives e - 127, plus one unless f = 0.  Zero,
-// subnormal and NaN m give level 0, as the comparisons do.
+// two), and the smallest l with q <= 2^l is the exponent of the number just
+// below q, plus one: its bits less one, so that 2^l itself falls to l.  Zero
+// and NaN m give level 0 (their bits less one are taken from zero's), as the
+// comparisons do.
 __device__ __forceinline__ int cascade_level(float m, const GridK& g) {
-    const uint32_t b = __float_as_uint(m * g.inv_base);
-    const int e = static_cast<int>(b >> 23);
-    int level = e - 127 + ((b & 0x7fffffu) != 0u ? 1 : 0);
-    if (e == 0 || !(m == m)) level = 0;
-    return min(max(level, 0), g.n_grids - 1);
+    const int b = static_cast<int>(__float_as_uint(fmaxf(m * g.inv_base, 0.0f)));
+    return min(max(((b - 1) >> 23) - 126, 0), g.n_grids - 1);
 }
 
 // Where point x is looked up: the grid word and bit of its fine cell, the
@@ -410,6 +409,7 @@ void make_constants(const nacc_grid_desc& grid, const nacc_march_params& params,
     g.top = static_cast<float>(grid.res - 1);
     g.base = grid.hi[0];
     g.inv_base = 1.0f / grid.hi[0];
+    g.wide_levels = grid.hi[0] >= 0x1p-60f && grid.hi[0] <= 0x1p60f ? 0 : 1;
     g.res = grid.res;
     g.n_grids = grid.n_grids;
     g.words = static_cast<uint32_t>(static_cast<int64_t>(grid.res) * grid.res * grid.res / 32);

@@ -837,6 +837,123 @@ __device__ __forceinline__ uint32_t cone_hits(const uint32_t* __restrict__ bits,
     return hits;
 }
 
+// Levels of a cascade segment's midpoints, bounded by cone_segment_live:
+// every midpoint lies on `hi` or the level below it (`hi` alone where
+// `one`); `wide`: on more levels, or not established.
+struct SegLevels {
+    int hi;
+    bool one, wide;
+};
+
+__device__ __forceinline__ uint32_t cell_index(const GridK& g, float u0, float u1, float u2) {
+    const uint32_t j0 = static_cast<uint32_t>(static_cast<int>(clamp_cell(u0, g.top)));
+    const uint32_t j1 = static_cast<uint32_t>(static_cast<int>(clamp_cell(u1, g.top)));
+    const uint32_t j2 = static_cast<uint32_t>(static_cast<int>(clamp_cell(u2, g.top)));
+    return __umul24(j0, g.res2) + (__umul24(j1, static_cast<uint32_t>(g.res)) + j2);
+}
+
+// Occupancy bits of a segment's candidates (bit u for candidate u) from its
+// first t, those from t_far on and past a stalled step cleared; cascades: a
+// segment that is not `wide`.  The same cells as probe()'s with fewer
+// operations: a cascade level scales by a power of two, which commutes with
+// every rounding of ((x 2^-l) - lo) s, so one level costs the operations of a
+// plain box with lo 2^l and s 2^-l, and two cost a comparison and three
+// selections (wide_levels keeps the scales far from the ends of the exponent
+// range).  Contraction: the fast cells first, then the exact ones where any
+// lane needs them, four candidates at a time: all eight together hold 110
+// registers, and half the waves fit (210 us for 131,072 rays of 40 chunks
+// against 165).  The other lookups hold eight in 62 registers (262,144 rays
+// of a cascade: 129 us against 135 four at a time).
+template <int LOOKUP>
+__device__ __forceinline__ uint32_t segment_hits(__amdgpu_buffer_rsrc_t grs, const GridK& g, const StepK& p,
+                                                 uint32_t word0, const SegLevels& lv, const float o[3],
+                                                 const float d[3], float t, float t_far) {
+    float lo_a = 0.0f, lo_b = 0.0f, s_a = 0.0f, s_b = 0.0f, thr = 0.0f;
+    uint32_t w_a = word0, w_b = word0;
+    if (LOOKUP == NACC_LOOKUP_CASCADE) {
+        const int la = lv.one ? lv.hi : max(lv.hi - 1, 0);
+        lo_a = ldexpf(g.lo[0], la);
+        lo_b = ldexpf(g.lo[0], lv.hi);
+        s_a = ldexpf(g.s[0], -la);
+        s_b = ldexpf(g.s[0], -lv.hi);
+        thr = ldexpf(g.base, la);
+        w_a = static_cast<uint32_t>(la) * g.words;
+        w_b = static_cast<uint32_t>(lv.hi) * g.words;
+    }
+    constexpr int kHitBatch = LOOKUP == NACC_LOOKUP_CONTRACT ? 4 : kConeBatch;
+    uint32_t hits = 0u;
+#pragma unroll 1
+    for (int u0 = 0; u0 < kConeBatch; u0 += kHitBatch) {
+        float tb[kHitBatch + 1];
+        tb[0] = t;
+#pragma unroll
+        for (int u = 0; u < kHitBatch; ++u) {
+            tb[u + 1] = tb[u] + __builtin_amdgcn_fmed3f(tb[u] * p.cone, p.dt, p.dt_max);
+        }
+        t = tb[kHitBatch];
+        uint32_t cell[kHitBatch], w[kHitBatch];
+        bool need[kHitBatch], any_need = false;
+#pragma unroll
+        for (int u = 0; u < kHitBatch; ++u) {
+            const float tm = (tb[u] + tb[u + 1]) * 0.5f;
+            const float x0 = o[0] + d[0] * tm, x1 = o[1] + d[1] * tm, x2 = o[2] + d[2] * tm;
+            if (LOOKUP == NACC_LOOKUP_CASCADE) {
+                const bool up = fmaxf(fmaxf(fabsf(x0), fabsf(x1)), fabsf(x2)) > thr;
+                const float lo = up ? lo_b : lo_a, sc = up ? s_b : s_a;
+                cell[u] = cell_index(g, (x0 - lo) * sc, (x1 - lo) * sc, (x2 - lo) * sc);
+                w[u] = grid_word(grs, (up ? w_b : w_a) + (cell[u] >> 5));
+            } else if (LOOKUP == NACC_LOOKUP_CONTRACT) {
+                // see probe(); times 1 is exact where |x| is not contracted
+                const float na = __builtin_amdgcn_sqrtf((x0 * x0 + x1 * x1) + x2 * x2);
+                const float ia = __builtin_amdgcn_rcpf(na);
+                const bool far = na > 1.0f;
+                const float fa = far ? (2.0f - ia) * ia : 1.0f;
+                const float v0 = (x0 * fa - g.lo[0]) * g.s[0];
+                const float v1 = (x1 * fa - g.lo[1]) * g.s[1];
+                const float v2 = (x2 * fa - g.lo[2]) * g.s[2];
+                const float near =
+                    fminf(fminf(fabsf(v0 - rintf(v0)), fabsf(v1 - rintf(v1))), fabsf(v2 - rintf(v2)));
+                need[u] = (far && near <= g.contract_delta) || fabsf(na - 1.0f) <= 0x1p-20f;
+                any_need = any_need || need[u];
+                cell[u] = cell_index(g, v0, v1, v2);
+            } else {
+                cell[u] = cell_index(g, (x0 - g.lo[0]) * g.s[0], (x1 - g.lo[1]) * g.s[1], (x2 - g.lo[2]) * g.s[2]);
+                w[u] = grid_word(grs, word0 + (cell[u] >> 5));
+            }
+        }
+        if (LOOKUP == NACC_LOOKUP_CONTRACT) {
+            if (ballot(any_need) != 0ull) {
+#pragma unroll
+                for (int u = 0; u < kHitBatch; ++u) {
+                    if (need[u]) {
+                        const float tm = (tb[u] + tb[u + 1]) * 0.5f;
+                        float x0 = o[0] + d[0] * tm, x1 = o[1] + d[1] * tm, x2 = o[2] + d[2] * tm;
+                        const float n = sqrtf((x0 * x0 + x1 * x1) + x2 * x2);
+                        if (n > 1.0f) {
+                            const float f = (2.0f - 1.0f / n) / n;
+                            x0 = x0 * f;
+                            x1 = x1 * f;
+                            x2 = x2 * f;
+                        }
+                        cell[u] =
+                            cell_index(g, (x0 - g.lo[0]) * g.s[0], (x1 - g.lo[1]) * g.s[1], (x2 - g.lo[2]) * g.s[2]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kHitBatch; ++u) w[u] = grid_word(grs, word0 + (cell[u] >> 5));
+        }
+        // a stalled step repeats its t, which is then the last
+        const float t_stop = fminf(t_far, t);
+#pragma unroll
+        for (int u = 0; u < kHitBatch; ++u) {
+            const uint32_t bit = __builtin_amdgcn_ubfe(w[u], cell[u] & 31u, 1u);
+            hits |= (tb[u] < t_stop ? bit : 0u) << (u0 + u);
+        }
+    }
+    return hits;
+}
+
 // One ray, cone steps, one lane, traversing the grid: the fill pass when no
 // count-pass workspace is given (the same samples as the chunk-parallel
 // passes, for checking them and for callers that keep no workspace).
@@ -902,31 +1019,34 @@ __device__ __forceinline__ ConeHalo cone_halo_ray(const GridK& g, const float o[
     return k;
 }
 
-// Whether a segment of candidates whose midpoints lie in [ta, tb] may hold
-// samples (see above): false only when the centre's halo bit is clear and
-// the bound holds.  Branch-free, so the segments' halo words are all in
-// flight together.
+// Where a segment of candidates whose midpoints lie in [ta, tb] is looked
+// up: its centre (on its level, contracted) and `dev`, the bound of the cell
+// coordinates' distance from the centre's on every axis.  False: no bound.
 template <int LOOKUP>
-__device__ __forceinline__ bool cone_segment_live(const GridK& g, __amdgpu_buffer_rsrc_t hrs, uint32_t grid,
-                                                  const float o[3], const float d[3], const ConeHalo& k, float ta,
-                                                  float tb) {
+__device__ __forceinline__ bool cone_segment_cells(const GridK& g, const float o[3], const float d[3],
+                                                   const ConeHalo& k, float ta, float tb, SegLevels& lv, float x[3],
+                                                   float& dev) {
     const float tc = (ta + tb) * 0.5f;
     const float h = (tb - ta) * 0.5f + fabsf(tb) * 0x1p-20f;  // half-extent, with the rounding of the t values
-    float x0 = o[0] + d[0] * tc, x1 = o[1] + d[1] * tc, x2 = o[2] + d[2] * tc;
+    float &x0 = x[0], &x1 = x[1], &x2 = x[2];
+    x0 = o[0] + d[0] * tc;
+    x1 = o[1] + d[1] * tc;
+    x2 = o[2] + d[2] * tc;
     // the rounding of positions (a few ulps of the largest coordinate
     // reached, for both points) and of cell coordinates, generously
     const float slack_x = (k.omax + k.dmax * fabsf(tb) + 1.0f) * 0x1p-19f;
     const float cell_slack = static_cast<float>(g.res) * 0x1p-17f;
-    float dev;  // bound of |u_i(midpoint) - u_i(centre)| in cells
     bool open = false;  // the bound cannot be established
-    uint32_t hgrid = grid;
     if (LOOKUP == NACC_LOOKUP_CASCADE) {
         const float m = fmaxf(fmaxf(fabsf(x0), fabsf(x1)), fabsf(x2));
         const float dm = k.dmax * h + slack_x;
-        const int l_lo = cascade_level(fmaxf(m - dm, 0.0f), g);
+        const float m_lo = m - dm;
         const int l_hi = cascade_level(m + dm, g);
-        open = l_lo != l_hi;  // a midpoint may lie on another level
-        hgrid = static_cast<uint32_t>(l_hi);
+        const float below = ldexpf(g.base, l_hi - 1);  // the largest |x_i| of the level below
+        lv.hi = l_hi;
+        lv.one = l_hi == 0 || m_lo > below;
+        lv.wide = !(lv.one || l_hi == 1 || m_lo > below * 0.5f) || !(dm < INFINITY) || g.wide_levels != 0;
+        open = !lv.one;  // a midpoint may lie on another level
         x0 = ldexpf(x0, -l_hi);
         x1 = ldexpf(x1, -l_hi);
         x2 = ldexpf(x2, -l_hi);
@@ -960,8 +1080,21 @@ __device__ __forceinline__ bool cone_segment_live(const GridK& g, __amdgpu_buffe
     } else {
         dev = k.v * h + k.smax * slack_x + cell_slack;
     }
-    open = open || !(dev <= static_cast<float>(kHaloReach) * (1.0f - 0x1p-10f));
-    const bool hb = halo_bit(hrs, g, hgrid * g.halo_words, x0, x1, x2);  // loaded in every case
+    return !open;
+}
+
+// Whether such a segment may hold samples (see above): false only when the
+// centre's halo bit is clear and the bound holds.  Branch-free, so that the
+// segments' halo words are all in flight together.
+template <int LOOKUP>
+__device__ __forceinline__ bool cone_segment_live(const GridK& g, __amdgpu_buffer_rsrc_t hrs, uint32_t grid,
+                                                  const float o[3], const float d[3], const ConeHalo& k, float ta,
+                                                  float tb, SegLevels& lv) {
+    float x[3], dev;
+    const bool bound = cone_segment_cells<LOOKUP>(g, o, d, k, ta, tb, lv, x, dev);
+    const bool open = !bound || !(dev <= static_cast<float>(kHaloReach) * (1.0f - 0x1p-10f));
+    const uint32_t hgrid = LOOKUP == NACC_LOOKUP_CASCADE ? static_cast<uint32_t>(lv.hi) : grid;
+    const bool hb = halo_bit(hrs, g, hgrid * g.halo_words, x[0], x[1], x[2]);  // loaded in every case
     return open | hb;
 }
 
@@ -1031,8 +1164,9 @@ ConeTable cone_table(const StepK& p, int n_masks) {
     return tab;
 }
 
-// Chunk-parallel cone marching.  The recurrence itself is cheap (four FP32
-// operations per candidate) but serial; the grid lookups are not.  A
+// Chunk-parallel cone marching, for calls without halo bits.  The recurrence
+// itself is cheap (four FP32 operations per candidate) but serial; the grid
+// lookups are not.  A
 // pre-pass walks each ray's recurrence once, one lane per ray, and records
 // t at the start of every chunk of 64 candidates; the count and fill passes
 // then take one lane per (ray, chunk), so a launch has ~12 times as many
@@ -1040,122 +1174,47 @@ ConeTable cone_table(const StepK& p, int n_masks) {
 // chunk-major (task = chunk * n_rays + ray): a wave's loads and stores of
 // the per-chunk arrays are contiguous.  A ray longer than the stored chunks
 // is finished by the task of its last stored chunk.
-// CULL (contraction lookup with halo bits): a chunk whose candidates all
-// provably map into halo-clear cells (one test of the chunk's whole extent,
-// see cone_segment_live) is marked by a NaN start, which the segment count
-// and fill passes take for a chunk without samples.  Far from the scene the
-// contraction maps a whole chunk of candidates into a fraction of a cell.
-// The last stored chunk is never marked: the passes continue the ray from it.
-template <int LOOKUP, bool CULL>
 __global__ __launch_bounds__(kRaysPerBlock) void cone_starts_kernel(
     const float* __restrict__ rays_o, const float* __restrict__ rays_d, const int32_t* __restrict__ grid_id,
-    int64_t n_rays, GridK g, ClipK c, StepK p, int n_masks, float* __restrict__ chunk_t,
-    float* __restrict__ t_far_out, int32_t* __restrict__ extra, const uint32_t* __restrict__ halo,
-    uint64_t* __restrict__ live_chunks, int64_t* __restrict__ task_sums, ConeTable tab) {
+    int64_t n_rays, bool has_grid_id, GridK g, ClipK c, StepK p, int n_masks, float* __restrict__ chunk_t,
+    float* __restrict__ t_far_out, int32_t* __restrict__ extra, ConeTable tab) {
     const int64_t r = static_cast<int64_t>(blockIdx.x) * kRaysPerBlock + threadIdx.x;
-    uint64_t listed = 0ull;  // CULL: chunks with candidates that may hold samples
-    if (r < n_rays) {
-        float o[3], d[3];
+    if (r >= n_rays) return;
+    float o[3], d[3];
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            o[i] = rays_o[3 * r + i];
-            d[i] = rays_d[3 * r + i];
-        }
-        uint32_t word0;
-        float t_near = 0.0f, t_far = 0.0f;
-        bool live = grid_of_ray<LOOKUP>(grid_id, r, g, word0);
-        live = clip_ray(o, d, c, p.near_plane, p.far_plane, t_near, t_far) && live;
-        t_far_out[r] = live ? t_far : -INFINITY;
-        extra[r] = 0;
-        const ConeHalo k = cone_halo_ray(g, o, d);  // (unused unless CULL)
-        const __amdgpu_buffer_rsrc_t hrs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint32_t*>(halo), 0, static_cast<int>(g.halo_bytes), kBufferWord3);
-        float t = t_near;
-        const bool tabled = tab.n > 0 && t_near == tab.t[0];  // starts at the near plane
-        const bool all_tabled = __builtin_amdgcn_ballot_w64(live && !tabled) == 0ull;
-        if (all_tabled) {
-            // every live ray of the wave follows the table: eight chunks at
-            // a time, so that their culling tests' loads are in flight
-            // together
-            for (int j0 = 0; j0 < n_masks; j0 += 8) {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int j = j0 + u;
-                    if (j < n_masks) {
-                        const float ta = tab.t[kTableStride * j];
-                        const bool has = live && ta < t_far;
-                        float start = has ? ta : INFINITY;
-                        if (CULL && has && j < n_masks - 1 &&
-                            !cone_segment_live<LOOKUP>(g, hrs, word0 / g.words, o, d, k, ta,
-                                                       tab.t[kTableStride * (j + 1)])) {
-                            start = __builtin_nanf("");
-                        }
-                        if (CULL && start < INFINITY) listed |= 1ull << j;
-                        chunk_t[static_cast<int64_t>(j) * n_rays + r] = start;
-                    }
-                }
-            }
-        }
-        for (int j = 0; j < (all_tabled ? 0 : n_masks); ++j) {
-            live = live && t < t_far;  // the chunk's first candidate exists
-            const float ta = t;
-            const bool has = live;
-            if (__builtin_amdgcn_ballot_w64(live && !tabled) == 0ull) {
-                // the wave's live rays all follow the table (or have all
-                // ended): the next chunk's start, past the ray's end too
-                if (tabled) t = tab.t[kTableStride * (j + 1)];
-            } else if (p.no_stall) {
-                // every step advances, so the candidates inside the ray are a
-                // prefix: the steps are taken without tests (past the ray's
-                // end t runs on; the next chunk's test sees that)
-#pragma unroll 8
-                for (int u = 0; u < kWave; ++u) t = t + __builtin_amdgcn_fmed3f(t * p.cone, p.dt, p.dt_max);
-            } else {
-                // 64 steps without branches: a ray that ends keeps its last t
-#pragma unroll 8
-                for (int u = 0; u < kWave; ++u) {
-                    const float t1 = t + __builtin_amdgcn_fmed3f(t * p.cone, p.dt, p.dt_max);
-                    live = live && t < t_far && t1 > t;
-                    t = live ? t1 : t;
-                }
-            }
-            float start = has ? ta : INFINITY;
-            if (CULL && has && j < n_masks - 1 &&
-                !cone_segment_live<LOOKUP>(g, hrs, word0 / g.words, o, d, k, ta, t)) {
-                start = __builtin_nanf("");
-            }
-            if (CULL && start < INFINITY) listed |= 1ull << j;
-            chunk_t[static_cast<int64_t>(j) * n_rays + r] = start;
-        }
-        if (CULL) live_chunks[r] = listed;
+    for (int i = 0; i < 3; ++i) {
+        o[i] = rays_o[3 * r + i];
+        d[i] = rays_d[3 * r + i];
     }
-    if (CULL) {
-        // the workgroup's (one wave of 64 rays) listed rays per chunk,
-        // chunk-major ([chunk][workgroup]), for the scan that places the
-        // tasks in the list chunk by chunk, rays in order within a chunk
-        for (int j = 0; j < n_masks; ++j) {
-            const uint64_t b = __builtin_amdgcn_ballot_w64(((listed >> j) & 1ull) != 0ull);
-            if (threadIdx.x == 0) task_sums[static_cast<int64_t>(j) * gridDim.x + blockIdx.x] = __popcll(b);
-        }
-    }
-}
-
-// The task list of the segment passes under CULL: the listed chunks, chunk
-// by chunk, rays in order within a chunk (task = j n_rays + r), so that
-// neighbouring tasks read and write neighbouring entries of the per-chunk
-// arrays.  offsets: the exclusive scan of the per-(chunk, workgroup) counts.
-__global__ __launch_bounds__(kRaysPerBlock) void task_list_kernel(const int64_t* __restrict__ offsets,
-                                                                  int64_t n_rays, int n_masks,
-                                                                  const uint64_t* __restrict__ live_chunks,
-                                                                  int32_t* __restrict__ task_list) {
-    const int64_t r = static_cast<int64_t>(blockIdx.x) * kRaysPerBlock + threadIdx.x;
-    const uint64_t m = r < n_rays ? live_chunks[r] : 0ull;
+    float t_near = 0.0f, t_far = 0.0f;
+    const int gid = has_grid_id ? grid_id[r] : 0;
+    bool live = gid >= 0 && gid < g.n_grids;
+    live = clip_ray(o, d, c, p.near_plane, p.far_plane, t_near, t_far) && live;
+    t_far_out[r] = live ? t_far : -INFINITY;
+    extra[r] = 0;
+    float t = t_near;
+    const bool tabled = tab.n > 0 && t_near == tab.t[0];  // starts at the near plane
     for (int j = 0; j < n_masks; ++j) {
-        const bool on = ((m >> j) & 1ull) != 0ull;
-        const uint64_t b = __builtin_amdgcn_ballot_w64(on);
-        if (on) {
-            const int64_t pos = offsets[static_cast<int64_t>(j) * gridDim.x + blockIdx.x] + bits_below(b);
-            task_list[pos] = static_cast<int32_t>(static_cast<int64_t>(j) * n_rays + r);
+        live = live && t < t_far;  // the chunk's first candidate exists
+        chunk_t[static_cast<int64_t>(j) * n_rays + r] = live ? t : INFINITY;
+        if (__builtin_amdgcn_ballot_w64(live && !tabled) == 0ull) {
+            // the wave's live rays all follow the table (or have all
+            // ended): the next chunk's start, past the ray's end too
+            if (tabled) t = tab.t[kTableStride * (j + 1)];
+        } else if (p.no_stall) {
+            // every step advances, so the candidates inside the ray are a
+            // prefix: the steps are taken without tests (past the ray's
+            // end t runs on; the next chunk's test sees that)
+#pragma unroll 8
+            for (int u = 0; u < kWave; ++u) t = t + __builtin_amdgcn_fmed3f(t * p.cone, p.dt, p.dt_max);
+        } else {
+            // 64 steps without branches: a ray that ends keeps its last t
+#pragma unroll 8
+            for (int u = 0; u < kWave; ++u) {
+                const float t1 = t + __builtin_amdgcn_fmed3f(t * p.cone, p.dt, p.dt_max);
+                live = live && t < t_far && t1 > t;
+                t = live ? t1 : t;
+            }
         }
     }
 }
@@ -1229,52 +1288,18 @@ __global__ __launch_bounds__(kTaskThreads) void count_cone_chunks_kernel(
 }
 
 // Per-ray counts from the chunk masks (capped at max_per_ray) and the
-// workgroup sums of the scan.  For the segment fill (nullable): the samples
-// of each ray before each chunk, and per ray the bits of the chunks holding
-// samples (sample_chunks may be live_chunks itself: each ray's word is read
-// before it is written).
+// workgroup sums of the scan.
 __global__ __launch_bounds__(kRaysPerBlock) void cone_counts_kernel(int64_t n_rays, int n_masks, int max_per_ray,
                                                                     const uint64_t* __restrict__ masks,
                                                                     const int32_t* __restrict__ extra,
                                                                     int32_t* __restrict__ packed_info,
-                                                                    int64_t* __restrict__ block_sums,
-                                                                    int32_t* __restrict__ chunk_base,
-                                                                    const uint64_t* live_chunks,
-                                                                    uint64_t* sample_chunks) {
+                                                                    int64_t* __restrict__ block_sums) {
     const int64_t r = static_cast<int64_t>(blockIdx.x) * kRaysPerBlock + threadIdx.x;
     int n = 0;
     if (r < n_rays) {
-        // with a task list, the chunks left out of it hold no samples (their
-        // masks were not written)
-        const uint64_t listed = live_chunks != nullptr ? live_chunks[r] : ~0ull;
-        uint64_t holding = 0ull;
-        int64_t total = 0;
-        // eight chunks' masks loaded together, then taken in order
-        constexpr int kGroup = 8;
-        for (int j0 = 0; j0 < n_masks; j0 += kGroup) {
-            uint64_t mg[kGroup];
-#pragma unroll
-            for (int u = 0; u < kGroup; ++u) {
-                const int j = j0 + u;
-                mg[u] = j < n_masks && ((listed >> j) & 1ull) != 0ull ? masks[static_cast<int64_t>(j) * n_rays + r]
-                                                                       : 0ull;
-            }
-#pragma unroll
-            for (int u = 0; u < kGroup; ++u) {
-                const int j = j0 + u;
-                const uint64_t m = mg[u];
-                // samples of the ray before chunk j, for the segment fill,
-                // which reads it for the chunks holding samples and the last
-                if (chunk_base != nullptr && j < n_masks && (m != 0ull || j == n_masks - 1)) {
-                    chunk_base[static_cast<int64_t>(j) * n_rays + r] =
-                        static_cast<int32_t>(min(total, static_cast<int64_t>(kMaxCandidates)));
-                }
-                total += __popcll(m);
-                if (m != 0ull) holding |= 1ull << j;
-            }
-        }
-        if (sample_chunks != nullptr) sample_chunks[r] = holding;
-        total += extra[r];
+        int64_t total = extra[r];
+#pragma unroll 8
+        for (int j = 0; j < n_masks; ++j) total += __popcll(masks[static_cast<int64_t>(j) * n_rays + r]);
         if (max_per_ray > 0) total = min(total, static_cast<int64_t>(max_per_ray));
         n = static_cast<int>(min(total, static_cast<int64_t>(kMaxCandidates)));
         packed_info[2 * r + 1] = n;
@@ -1359,16 +1384,13 @@ __global__ __launch_bounds__(kTaskThreads) void fill_cone_chunks_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Cone steps with the halo bits of the skip buffer.  A chunk's 64 candidates
-// form 8 segments of kConeBatch; the count pass walks the chunk's recurrence
-// once (one lane per chunk) and tests one halo bit per segment at its
-// centre.  The segments that may hold samples are queued per wave in LDS
-// and then looked up 64 at a time, one segment per lane, so that the lanes
-// stay busy although only a few segments of a chunk are live.  Each looked-up
-// segment's 8 occupancy bits are ORed into its chunk's mask (byte s of the
-// mask, as in the plain passes), and the t at the start of every segment
-// holding samples is stored, so the fill pass writes them without walking
-// the recurrence again.
+// Cone steps with halo bits (the skip buffer's, or built for the call).  A
+// chunk's 64 candidates form 8 segments of kConeBatch; the count pass tests
+// one halo bit per segment at its centre, and looks up, one segment per
+// lane, those that may hold samples.  A segment's 8 occupancy bits are byte s
+// of its chunk's mask (the mask of the plain passes), and the t at the start
+// of every segment holding samples is stored, so the fill pass writes them
+// without walking the recurrence again.
 //
 // A clear halo bit proves a segment empty when all its midpoints provably
 // map within kHaloReach cells of the centre's cell in the grid the centre is
@@ -1383,179 +1405,392 @@ constexpr int kSegsPerChunk = kWave / kConeBatch;
 constexpr int kTaskWaves = kTaskThreads / kWave;
 constexpr int kSegQueue = kWave * kSegsPerChunk;  // every segment of a wave's chunks
 
+// Whether a chunk whose midpoints lie in [ta, tb] may hold samples, by the
+// distance field of the skip buffer (box and cascade lookups): as
+// cone_segment_live, with the coarse cells closer than the centre's distance
+// in place of the halo's reach.
 template <int LOOKUP>
-__global__ __launch_bounds__(kTaskThreads) void count_cone_segments_kernel(
+__device__ __forceinline__ bool cone_chunk_live(const GridK& g, const uint8_t* __restrict__ dist, uint32_t word0,
+                                                const float o[3], const float d[3], const ConeHalo& k, float ta,
+                                                float tb) {
+    const float tc = (ta + tb) * 0.5f;
+    const float h = (tb - ta) * 0.5f + fabsf(tb) * 0x1p-20f;
+    const float x0 = o[0] + d[0] * tc, x1 = o[1] + d[1] * tc, x2 = o[2] + d[2] * tc;
+    const float slack_x = (k.omax + k.dmax * fabsf(tb) + 1.0f) * 0x1p-19f;
+    const Probe q = probe<LOOKUP>(g, word0, x0, x1, x2);
+    // the coarse cells less than D cells from the centre's are empty: every
+    // fine cell up to 4 (D - 1) cells from the centre's
+    const float reach = 4.0f * static_cast<float>(static_cast<int>(dist[q.coarse]) - 1) * (1.0f - 0x1p-10f);
+    float dev = k.v * h + k.smax * slack_x;
+    bool open = false;
+    if (LOOKUP == NACC_LOOKUP_CASCADE) {
+        const float dm = k.dmax * h + slack_x;
+        const int l_hi = cascade_level(q.m + dm, g);
+        open = l_hi != 0 && !(q.m - dm > ldexpf(g.base, l_hi - 1));
+        dev = ldexpf(dev, -q.level);
+    }
+    return open || !(dev + static_cast<float>(g.res) * 0x1p-17f <= reach);
+}
+
+// The cells a segment's candidates can map to, from its centre and bound:
+// all empty, all occupied, or undecided (also where they are more than two
+// rows on an axis, or a row of them lies in two words).
+enum class Cells { kEmpty, kOccupied, kUndecided };
+
+__device__ __forceinline__ Cells cells_within(__amdgpu_buffer_rsrc_t grs, const GridK& g, uint32_t word0,
+                                              const float x[3], float dev) {
+    uint32_t a[3], b[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const float u = (x[i] - g.lo[i]) * g.s[i];
+        a[i] = static_cast<uint32_t>(static_cast<int>(clamp_cell(u - dev, g.top)));
+        b[i] = static_cast<uint32_t>(static_cast<int>(clamp_cell(u + dev, g.top)));
+    }
+    const uint32_t nz = b[2] - a[2];
+    bool whole = b[0] - a[0] <= 1u && b[1] - a[1] <= 1u;
+    uint32_t w[4], cell[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        cell[i] = __umul24(i < 2 ? a[0] : b[0], g.res2) +
+                  (__umul24((i & 1) == 0 ? a[1] : b[1], static_cast<uint32_t>(g.res)) + a[2]);
+        w[i] = grid_word(grs, word0 + (cell[i] >> 5));
+        whole = whole && (cell[i] & 31u) + nz <= 31u;
+    }
+    uint32_t any = 0u, all = ~0u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t row = w[i] >> (cell[i] & 31u);
+        any |= row;
+        all &= row;
+    }
+    const uint32_t m = (2u << (nz & 31u)) - 1u;
+    if (!whole) return Cells::kUndecided;
+    return (any & m) == 0u ? Cells::kEmpty : (all & m) == m ? Cells::kOccupied : Cells::kUndecided;
+}
+
+// The LDS of the segment count for `rays` rays a workgroup.
+constexpr int kConeRaysMax = kRaysPerBlock;
+constexpr int kConeRayFloats = 20;  // 16-byte fields, 16 different ones in different banks
+constexpr int kChunkQueue = kWave + kSegsPerChunk;
+constexpr int kSegStack = 2 * kWave;
+// A queued segment: its number (bits 0 to 2), chunk (3 to 8), ray (9 to 14)
+// and levels.
+constexpr uint32_t kSegOneLevel = 1u << 15, kSegWide = 1u << 16;
+constexpr int kSegLevelShift = 17;
+struct ConeLds {
+    int tab, masks, starts, seg_t, seg_id, near_t, near_end, near_id, chunks, bytes;  // byte offsets, after the rays
+};
+__host__ __device__ inline int cone_mask_stride(int n_masks) { return (n_masks | 1) * 8; }  // bytes a ray
+__host__ __device__ inline ConeLds cone_lds(int rays, int n_masks, bool walks, bool ranges) {
+    ConeLds l;
+    l.masks = rays * kConeRayFloats * 4;
+    l.tab = l.masks + rays * cone_mask_stride(n_masks);
+    l.starts = l.tab + (n_masks * kTableStride + 1) * 4;
+    l.seg_t = l.starts + (walks ? rays * (n_masks + 1) * 4 : 0);
+    l.seg_id = l.seg_t + kTaskWaves * kSegStack * 4;
+    l.near_t = l.seg_id + kTaskWaves * kSegStack * 4;
+    const int near = ranges ? kTaskWaves * kSegStack * 4 : 0;
+    l.near_end = l.near_t + near;
+    l.near_id = l.near_end + near;
+    l.chunks = l.near_id + near;
+    l.bytes = l.chunks + kTaskWaves * kChunkQueue * 2;
+    return l;
+}
+
+// Count pass of the cone steps with halo bits, one launch.  A workgroup takes
+// `rays` consecutive rays, a quarter of them a wave.  Each wave works
+// through three stages, 64 items at a time, one per lane: chunks of its rays
+// that begin before the ray ends, kept if they may hold samples (by the
+// halo bit of the chunk's centre under contraction, by the distance field
+// otherwise; without one all are kept); the eight segments of the kept
+// chunks, kept by their halo bits; and the candidates of the kept segments,
+// looked up.  What a stage keeps goes on a stack in LDS, and a later stage
+// runs as soon as it can fill the wave, so that every stage but the last
+// of each wave runs with full lanes whatever the share of items kept.  The
+// hits, a byte a segment, make the chunk masks in LDS; the first wave then
+// counts each ray's samples and writes the masks and the counts before
+// each chunk for the fill pass.
+// Chunks and segments of a ray that starts at the near plane read their
+// starts from the table; other rays' chunk starts are walked at the beginning,
+// one ray per lane (`walks`: the lookup has a clip box, or there is no
+// table), and their segment starts from them.  A stalled step repeats t:
+// the lookups find no candidate there.
+// Bound by VALU issue (95% of the cycles).  262,144 rays of a cascade of 15
+// chunks (92 segments inside the ray, 55 of kept chunks, 19 looked up, 10
+// holding samples): 129 us, where a pass for the chunk starts, one lane per
+// chunk with the wave's segments looked up together, and one for the counts
+// took 7.5 + 166 + 11.  131,071 rays of 39 contracted chunks (42 segments
+// near occupied cells, most of them decided by cells_within): 137 us, where
+// the starts with culling, the scan of a task list, the list, the segments
+// and the counts took 27 + 18 + 17 + 136 + 15.
+template <int LOOKUP>
+__global__ __launch_bounds__(kTaskThreads) void count_cone_kernel(
     const float* __restrict__ rays_o, const float* __restrict__ rays_d, const int32_t* __restrict__ grid_id,
-    int64_t n_rays, const uint32_t* __restrict__ bits, const uint32_t* __restrict__ halo, GridK g, StepK p,
-    int n_masks, const float* __restrict__ chunk_t, const float* __restrict__ t_far_in,
-    uint64_t* __restrict__ masks, int32_t* __restrict__ extra, float* __restrict__ seg_t,
-    const int32_t* __restrict__ task_list, const int64_t* __restrict__ task_total, ConeTable tab) {
-    __shared__ float q_t[kTaskWaves][kSegQueue];
-    __shared__ uint16_t q_id[kTaskWaves][kSegQueue];
-    __shared__ uint64_t q_mask[kTaskWaves][kWave];
+    int64_t n_rays, const uint32_t* __restrict__ bits, const uint32_t* __restrict__ halo,
+    const uint8_t* __restrict__ dist, GridK g, ClipK c, StepK p, int n_masks, int rays, int walks,
+    int32_t* __restrict__ packed_info, int64_t* __restrict__ block_sums, uint64_t* __restrict__ masks,
+    int32_t* __restrict__ chunk_base, float* __restrict__ seg_t, float* __restrict__ t_more,
+    float* __restrict__ t_far_out, uint64_t* __restrict__ sample_chunks, ConeTable tab) {
+    extern __shared__ float4 lds4[];
+    char* const lds = reinterpret_cast<char*>(lds4);
+    constexpr bool kRanges = LOOKUP == NACC_LOOKUP_CONTRACT;
+    const ConeLds l = cone_lds(rays, n_masks, walks != 0, kRanges);
+    const int stride = cone_mask_stride(n_masks);
+    float* const s_tab = reinterpret_cast<float*>(lds + l.tab);
+    float* const s_starts = reinterpret_cast<float*>(lds + l.starts);
     const int lane = lane_id();
     const int wave = uniform<int>(static_cast<int>(threadIdx.x) / kWave);
-    // task = chunk j n_rays + ray r; lane i of the launch takes task i, or,
-    // with a task list, its i-th entry
-    const int64_t first_idx = static_cast<int64_t>(blockIdx.x) * kTaskThreads + wave * kWave;
-    const int64_t idx = first_idx + lane;
-    bool in_range;
-    int64_t task = idx;
-    if (task_list != nullptr) {
-        in_range = idx < *task_total;
-        if (in_range) task = task_list[idx];
-    } else {
-        in_range = idx < static_cast<int64_t>(n_masks) * n_rays;
-    }
-    int j = 0;
-    int64_t r = 0;
-    float t = INFINITY;
-    if (in_range) {
-        j = static_cast<int>(task / n_rays);
-        r = task - static_cast<int64_t>(j) * n_rays;
-        t = chunk_t[task];
-    }
-    const bool active = t < INFINITY;  // (NaN: a chunk the starts pass proved empty)
-    if (ballot(active) == 0ull) {     // the whole wave: nothing to look up
-        if (in_range) masks[task] = 0ull;
-        return;
-    }
-    float o[3] = {0.0f, 0.0f, 0.0f}, d[3] = {0.0f, 0.0f, 0.0f};
-    float t_far = -INFINITY;
-    uint32_t word0 = 0;
-    if (active) {
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            o[i] = rays_o[3 * r + i];
-            d[i] = rays_d[3 * r + i];
-        }
-        t_far = t_far_in[r];
-        grid_of_ray<LOOKUP>(grid_id, r, g, word0);  // valid: the ray has candidates
-    }
-    // walk the chunk's recurrence once; test each segment's halo bit
-    const ConeHalo k = cone_halo_ray(g, o, d);
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * rays;
     const __amdgpu_buffer_rsrc_t hrs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint32_t*>(halo), 0, static_cast<int>(g.halo_bytes), kBufferWord3);
-    const uint32_t grid = word0 / g.words;
-    float st[kSegsPerChunk];
-    uint32_t live = 0u;
-    bool alive = active;
-    // a chunk that starts on the near-plane lattice (not the last stored
-    // one, whose end the continuation needs) reads its segment starts; the
-    // wave's tasks are chunk-major, so they nearly always share one chunk
-    // index, whose entries are then read with scalar loads
-    const int j0 = uniform<int>(j);
-    const bool tabled = tab.n > 0 && active && j == j0 && j0 < n_masks - 1 && t == tab.t[kTableStride * j0];
-    if (ballot(active && !tabled) == 0ull) {
+    const __amdgpu_buffer_rsrc_t grs = grid_rsrc(bits, g);
+    for (int i = threadIdx.x; i < tab.n; i += kTaskThreads) s_tab[i] = tab.t[i];
+    for (int i = threadIdx.x; i < rays * stride / 8; i += kTaskThreads) {
+        reinterpret_cast<uint64_t*>(lds + l.masks)[i] = 0ull;
+    }
+    // the rays, one per lane of the first wave
+    float t_far = -INFINITY, t_end = INFINITY;  // t_end: t after the stored chunks, where the ray goes on
+    float o[3] = {0.0f, 0.0f, 0.0f}, d[3] = {0.0f, 0.0f, 0.0f};
+    uint32_t word0 = 0;
+    const int64_t r = first + threadIdx.x;
+    const bool mine = static_cast<int>(threadIdx.x) < rays && r < n_rays;
+    if (static_cast<int>(threadIdx.x) < rays) {
+        float t = 0.0f;
+        bool tabled = true;
+        if (mine) {
 #pragma unroll
-        for (int s = 0; s < kSegsPerChunk; ++s) {
-            const float ta = tabled ? tab.t[kTableStride * j0 + s] : t;
-            const float tb = tabled ? tab.t[kTableStride * j0 + s + 1] : t;
-            st[s] = ta;
-            const bool any = active && ta < t_far;
-            live |= static_cast<uint32_t>(cone_segment_live<LOOKUP>(g, hrs, grid, o, d, k, ta, tb) & any) << s;
-        }
-    } else if (p.no_stall) {
-        // every step advances: a segment holds candidates inside the ray iff
-        // its first t lies before t_far; its extent is taken past the ray's
-        // end (a larger interval only weakens the test)
-        float t_last = t;  // t of the chunk's last candidate
-#pragma unroll
-        for (int s = 0; s < kSegsPerChunk; ++s) {
-            const float ta = t;
-#pragma unroll
-            for (int u = 0; u < kConeBatch; ++u) {
-                t_last = t;
-                t = t + __builtin_amdgcn_fmed3f(t * p.cone, p.dt, p.dt_max);
+            for (int i = 0; i < 3; ++i) {
+                o[i] = rays_o[3 * r + i];
+                d[i] = rays_d[3 * r + i];
             }
-            st[s] = ta;
-            const bool any = active && ta < t_far;
-            live |= static_cast<uint32_t>(cone_segment_live<LOOKUP>(g, hrs, grid, o, d, k, ta, t) & any) << s;
+            bool live = grid_of_ray<LOOKUP>(grid_id, r, g, word0);
+            live = clip_ray(o, d, c, p.near_plane, p.far_plane, t, t_far) && live;
+            if (!live) t_far = -INFINITY;
+            tabled = !live || (tab.n > 0 && t == tab.t[0]);
         }
-        alive = active && t_last < t_far;
-    } else {
-#pragma unroll
-        for (int s = 0; s < kSegsPerChunk; ++s) {
-            const float ta = t;
-            bool any = false;  // some candidate of the segment lies inside the ray
-#pragma unroll
-            for (int u = 0; u < kConeBatch; ++u) {
-                const float t1 = t + __builtin_amdgcn_fmed3f(t * p.cone, p.dt, p.dt_max);
-                alive = alive && t < t_far && t1 > t;
-                any = any || alive;
-                t = alive ? t1 : t;
+        const ConeHalo k = cone_halo_ray(g, o, d);
+        float4* const ray = lds4 + threadIdx.x * (kConeRayFloats / 4);
+        ray[0] = make_float4(o[0], o[1], o[2], t_far);
+        ray[1] = make_float4(d[0], d[1], d[2], __uint_as_float(word0));
+        ray[2] = make_float4(k.v, k.omax, k.dmax, k.dnorm);
+        ray[3] = make_float4(k.onorm, tabled ? 1.0f : 0.0f, __uint_as_float(word0 / g.words), 0.0f);
+        if (tabled) {
+            const float te = tab.n > 0 ? tab.t[kTableStride * n_masks] : INFINITY;
+            if (te < t_far) t_end = te;
+        }
+        if (walks != 0 && __builtin_amdgcn_ballot_w64(!tabled) != 0ull) {
+            float* const starts = s_starts + threadIdx.x * (n_masks + 1);
+            for (int j = 0; j < n_masks; ++j) {
+                starts[j] = t < t_far ? t : INFINITY;
+#pragma unroll 8
+                for (int u = 0; u < kWave; ++u) t = t + __builtin_amdgcn_fmed3f(t * p.cone, p.dt, p.dt_max);
             }
-            st[s] = ta;
-            live |= static_cast<uint32_t>(cone_segment_live<LOOKUP>(g, hrs, grid, o, d, k, ta, t) & any) << s;
+            starts[n_masks] = t < t_far ? t : INFINITY;
+            if (!tabled && t < t_far) t_end = t;
         }
+        if (mine) t_far_out[r] = t_far;
     }
-    const bool ended = !alive;
-    // queue the live segments of the wave's chunks in LDS, in lane order
-    const int n_items = __popc(live);
-    const int before = wave_inclusive_sum(n_items) - n_items;
-    const int total = read_lane(before + n_items, kWave - 1);
-    {
-        int pos = before;
+    __syncthreads();
+
+    uint16_t* const c_id = reinterpret_cast<uint16_t*>(lds + l.chunks) + wave * kChunkQueue;
+    float* const q_t = reinterpret_cast<float*>(lds + l.seg_t) + wave * kSegStack;
+    uint32_t* const q_id = reinterpret_cast<uint32_t*>(lds + l.seg_id) + wave * kSegStack;
+    float* const r_t = reinterpret_cast<float*>(lds + l.near_t) + wave * kSegStack;
+    float* const r_end = reinterpret_cast<float*>(lds + l.near_end) + wave * kSegStack;
+    uint32_t* const r_id = reinterpret_cast<uint32_t*>(lds + l.near_id) + wave * kSegStack;
+    const int per = rays / kTaskWaves;  // the wave's rays
+    const int n_flat = per * n_masks;   // its chunks, ray by ray; f / n_masks by this reciprocal (f < 1,024)
+    const uint32_t inv = 65536u / static_cast<uint32_t>(n_masks) + 1u;
+    ConeHalo k;
+    k.smax = fmaxf(fmaxf(g.s[0], g.s[1]), g.s[2]);
+    int f0 = 0, n_chunks = 0, n_near = 0, n_segs = 0;  // chunks taken; entries of the stacks
+    for (;;) {
+        const bool listed = n_chunks == 0 && f0 >= n_flat;  // no more segments come
+        if (n_segs >= kWave || (n_segs > 0 && n_near == 0 && listed)) {
+            // look 64 segments up
+            const int n = min(n_segs, kWave);
+            n_segs -= n;
+            const bool has = lane < n;
+            const int i = n_segs + (has ? lane : 0);
+            const float t0 = q_t[i];
+            const uint32_t id = q_id[i];
+            const int s = static_cast<int>(id & (kSegsPerChunk - 1));
+            const int j = static_cast<int>((id >> 3) & 63u);
+            const int rl = static_cast<int>((id >> 9) & 63u);
+            const SegLevels lv{static_cast<int>(id >> kSegLevelShift), (id & kSegOneLevel) != 0u, (id & kSegWide) != 0u};
+            const float4 a = lds4[rl * (kConeRayFloats / 4)], b = lds4[rl * (kConeRayFloats / 4) + 1];
+            const float so[3] = {a.x, a.y, a.z}, sd[3] = {b.x, b.y, b.z};
+            const float s_far = has ? a.w : -INFINITY;
+            uint32_t hits;
+            if (LOOKUP == NACC_LOOKUP_CASCADE && ballot(lv.wide) != 0ull) {
+                SkipRay sk{};
+                float skip_end = -INFINITY;
+                float tb[kConeBatch + 1];
+                const int n_valid = cone_steps(t0, s_far, p, tb);
+                hits = cone_hits<LOOKUP, false>(bits, nullptr, g, sk, skip_end, __float_as_uint(b.w), so, sd, tb,
+                                                n_valid) &
+                       ((1u << n_valid) - 1u);
+            } else {
+                hits = segment_hits<LOOKUP>(grs, g, p, __float_as_uint(b.w), lv, so, sd, t0, s_far);
+            }
+            if (hits != 0u) {
+                lds[l.masks + rl * stride + j * kSegsPerChunk + s] = static_cast<char>(hits);
+                seg_t[(static_cast<int64_t>(j) * n_rays + first + rl) * kSegsPerChunk + s] = t0;
+            }
+        } else if (kRanges && (n_near >= kWave || (n_near > 0 && listed))) {
+            // 64 segments by the cells within their bounds
+            const int n = min(n_near, kWave);
+            n_near -= n;
+            const bool has = lane < n;
+            const int i = n_near + (has ? lane : 0);
+            const float ta = r_t[i], te = r_end[i];
+            const uint32_t id = r_id[i];
+            const int rl = static_cast<int>((id >> 9) & 63u);
+            const float4* const ray = lds4 + rl * (kConeRayFloats / 4);
+            const float4 a = ray[0], b = ray[1], kc = ray[2], kd = ray[3];
+            const float so[3] = {a.x, a.y, a.z}, sd[3] = {b.x, b.y, b.z};
+            k.v = kc.x, k.omax = kc.y, k.dmax = kc.z, k.dnorm = kc.w, k.onorm = kd.x;
+            SegLevels lv;
+            float x[3], dev;
+            const bool bound = cone_segment_cells<LOOKUP>(g, so, sd, k, ta, te, lv, x, dev);
+            Cells cells = cells_within(grs, g, __float_as_uint(b.w), x, bound ? dev : 0.0f);
+            // all candidates are samples only if all lie inside the ray (the
+            // table's steps never stall)
+            const bool inside = (p.no_stall != 0 || kd.y != 0.0f) && te <= a.w;
+            if (!(bound && dev <= static_cast<float>(kHaloReach)) || (cells == Cells::kOccupied && !inside)) {
+                cells = Cells::kUndecided;
+            }
+            if (has && cells == Cells::kOccupied) {
+                const int j = static_cast<int>((id >> 3) & 63u), s = static_cast<int>(id & (kSegsPerChunk - 1));
+                lds[l.masks + rl * stride + j * kSegsPerChunk + s] = static_cast<char>(0xff);
+                seg_t[(static_cast<int64_t>(j) * n_rays + first + rl) * kSegsPerChunk + s] = ta;
+            }
+            const bool left = has && cells == Cells::kUndecided;
+            const uint64_t m = ballot(left);
+            if (left) {
+                const int pos = n_segs + bits_below(m);
+                q_t[pos] = ta;
+                q_id[pos] = id;
+            }
+            n_segs += static_cast<int>(__popcll(m));
+        } else if (n_chunks >= kWave / kSegsPerChunk || (n_chunks > 0 && f0 >= n_flat)) {
+            // the segments of 8 chunks
+            const int n = min(n_chunks, kWave / kSegsPerChunk);
+            n_chunks -= n;
+            const int e = lane / kSegsPerChunk, s = lane % kSegsPerChunk;
+            bool live = e < n;
+            const uint32_t id = c_id[n_chunks + (live ? e : 0)];
+            const int j = static_cast<int>(id & 63u);
+            const int rl = static_cast<int>(id >> 6);
+            const float4* const ray = lds4 + rl * (kConeRayFloats / 4);
+            const float4 a = ray[0], b = ray[1], kc = ray[2], kd = ray[3];
+            float ta = s_tab[kTableStride * j + s], te = s_tab[kTableStride * j + s + 1];
+            if (walks != 0 && ballot(kd.y == 0.0f) != 0ull) {
+                float t = s_starts[rl * (n_masks + 1) + j], t0 = t;
+                for (int v = 0; v < kSegsPerChunk; ++v) {
+                    if (v <= s) t0 = t;
 #pragma unroll
-        for (int s = 0; s < kSegsPerChunk; ++s) {
-            if (((live >> s) & 1u) != 0u) {
-                q_t[wave][pos] = st[s];
-                q_id[wave][pos] = static_cast<uint16_t>(lane | (s << kWaveLog2));
-                ++pos;
+                    for (int u = 0; u < kConeBatch; ++u) t = t + __builtin_amdgcn_fmed3f(t * p.cone, p.dt, p.dt_max);
+                    if (kd.y == 0.0f && v == s) {
+                        ta = t0;
+                        te = t;
+                    }
+                }
+            }
+            const float so[3] = {a.x, a.y, a.z}, sd[3] = {b.x, b.y, b.z};
+            k.v = kc.x, k.omax = kc.y, k.dmax = kc.z, k.dnorm = kc.w, k.onorm = kd.x;
+            live = live && ta < a.w;
+            SegLevels lv{0, true, false};
+            live &= cone_segment_live<LOOKUP>(g, hrs, __float_as_uint(kd.z), so, sd, k, ta, te, lv);
+            const uint64_t m = ballot(live);
+            const int pos = (kRanges ? n_near : n_segs) + bits_below(m);
+            const uint32_t seg = (id << 3) | static_cast<uint32_t>(s);
+            if (kRanges) {
+                if (live) {
+                    r_t[pos] = ta;
+                    r_end[pos] = te;
+                    r_id[pos] = seg;
+                }
+                n_near += static_cast<int>(__popcll(m));
+            } else {
+                if (live) {
+                    q_t[pos] = ta;
+                    q_id[pos] = seg | (lv.one ? kSegOneLevel : 0u) | (lv.wide ? kSegWide : 0u) |
+                                (static_cast<uint32_t>(lv.hi) << kSegLevelShift);
+                }
+                n_segs += static_cast<int>(__popcll(m));
+            }
+        } else if (f0 < n_flat) {
+            // 64 chunks
+            const int f = f0 + lane;
+            bool live = f < n_flat;
+            int rl = static_cast<int>((static_cast<uint32_t>(live ? f : 0) * inv) >> 16);
+            const int j = live ? f - rl * n_masks : 0;
+            rl += wave * per;
+            f0 += kWave;
+            const float4* const ray = lds4 + rl * (kConeRayFloats / 4);
+            const float4 a = ray[0], b = ray[1], kc = ray[2], kd = ray[3];
+            float ta = s_tab[kTableStride * j], te = s_tab[kTableStride * (j + 1)];
+            if (walks != 0 && kd.y == 0.0f) {
+                ta = s_starts[rl * (n_masks + 1) + j];
+                te = s_starts[rl * (n_masks + 1) + j + 1];
+            }
+            const float so[3] = {a.x, a.y, a.z}, sd[3] = {b.x, b.y, b.z};
+            k.v = kc.x, k.omax = kc.y, k.dmax = kc.z, k.dnorm = kc.w, k.onorm = kd.x;
+            live = live && ta < a.w;
+            if (LOOKUP == NACC_LOOKUP_CONTRACT) {
+                SegLevels lv;
+                live &= cone_segment_live<LOOKUP>(g, hrs, __float_as_uint(kd.z), so, sd, k, ta, te, lv);
+            } else if (dist != nullptr) {
+                live = live && cone_chunk_live<LOOKUP>(g, dist, __float_as_uint(b.w), so, sd, k, ta, te);
+            }
+            const uint64_t m = ballot(live);
+            if (live) c_id[n_chunks + bits_below(m)] = static_cast<uint16_t>((rl << 6) | j);
+            n_chunks += static_cast<int>(__popcll(m));
+        } else {
+            break;
+        }
+        wave_lds_sync();
+    }
+    __syncthreads();
+
+    if (wave != 0) return;
+    int n = 0;
+    if (mine) {
+        int64_t total = 0;
+        uint64_t holding = 0ull;
+        const uint64_t* const mm = reinterpret_cast<const uint64_t*>(lds + l.masks + threadIdx.x * stride);
+#pragma unroll 4
+        for (int j = 0; j < n_masks; ++j) {
+            const uint64_t m = mm[j];
+            // read by the fill pass for the chunks holding samples, and
+            // for the last one of a ray that goes on past it
+            if (m != 0ull || (j == n_masks - 1 && t_end < INFINITY)) {
+                masks[static_cast<int64_t>(j) * n_rays + r] = m;
+                chunk_base[static_cast<int64_t>(j) * n_rays + r] = static_cast<int32_t>(total);
+            }
+            if (m != 0ull) holding |= 1ull << j;
+            total += __popcll(m);
+        }
+        sample_chunks[r] = holding;
+        t_more[r] = t_end;
+        if (t_end < INFINITY) {
+            // past the stored chunks: count the rest of the ray here
+            SkipRay sk{};
+            float skip_end = -INFINITY;
+            bool ended = false;
+            float t = t_end;
+            for (int k0 = n_masks * kWave; k0 < kMaxCandidates && !ended; k0 += kWave) {
+                total += __popcll(cone_chunk_bits<LOOKUP, false>(bits, nullptr, g, sk, skip_end, word0, o, d, t,
+                                                                 t_far, p, ended));
             }
         }
+        if (p.max_per_ray > 0) total = min(total, static_cast<int64_t>(p.max_per_ray));
+        n = static_cast<int>(min(total, static_cast<int64_t>(kMaxCandidates)));
+        packed_info[2 * r + 1] = n;
     }
-    q_mask[wave][lane] = 0ull;
-    wave_lds_sync();
-    // look the queued segments up, one per lane
-    for (int base = 0; base < total; base += kWave) {
-        const int i = base + lane;
-        const bool has = i < total;
-        const float t0 = has ? q_t[wave][i] : 0.0f;
-        const int id = has ? static_cast<int>(q_id[wave][i]) : 0;
-        const int src = id & (kWave - 1);
-        const int s = id >> kWaveLog2;
-        float so[3], sd[3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            so[c] = lane_value(o[c], src);
-            sd[c] = lane_value(d[c], src);
-        }
-        // every lane takes part in the crossbar reads (a lane left out would
-        // not provide its value to the lanes reading it)
-        const float src_far = lane_value(t_far, src);
-        const float s_far = has ? src_far : -INFINITY;
-        const uint32_t s_word0 = static_cast<uint32_t>(lane_value(static_cast<int>(word0), src));
-        float tb[kConeBatch + 1];
-        const int n_valid = cone_steps(t0, s_far, p, tb);
-        SkipRay sk{};
-        float skip_end = -INFINITY;
-        const uint32_t hits =
-            cone_hits<LOOKUP, false>(bits, nullptr, g, sk, skip_end, s_word0, so, sd, tb, n_valid) &
-            ((1u << n_valid) - 1u);
-        const int64_t s_task =
-            task_list != nullptr ? static_cast<int64_t>(lane_value(static_cast<int>(task), src)) : first_idx + src;
-        if (has && hits != 0u) {
-            __hip_atomic_fetch_or(&q_mask[wave][src], static_cast<uint64_t>(hits) << (s * kConeBatch),
-                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-            seg_t[s_task * kSegsPerChunk + s] = t0;
-        }
-    }
-    wave_lds_sync();
-    if (in_range) masks[task] = q_mask[wave][lane];
-    if (active && j == n_masks - 1 && !ended) {
-        // past the stored chunks: count the rest of the ray here
-        SkipRay sk{};
-        float skip_end = -INFINITY;
-        bool e2 = false;
-        int count = 0;
-        for (int k0 = n_masks * kWave; k0 < kMaxCandidates; k0 += kWave) {
-            count += __popcll(cone_chunk_bits<LOOKUP, false>(bits, nullptr, g, sk, skip_end, word0, o, d, t, t_far,
-                                                             p, e2));
-            if (e2) break;
-        }
-        extra[r] = count;
-    }
+    const int sum = wave_sum(n);  // <= 64 * 2^24 fits int32
+    if (lane == 0) block_sums[blockIdx.x] = sum;
 }
 
 // Fill pass of the segment count, ray-major with staged stores.  A wave
@@ -1581,7 +1816,7 @@ template <int LOOKUP>
 __global__ __launch_bounds__(kTaskThreads) void fill_cone_rays_kernel(
     const float* __restrict__ rays_o, const float* __restrict__ rays_d, const int32_t* __restrict__ grid_id,
     int64_t n_rays, const uint32_t* __restrict__ bits, GridK g, StepK p, int n_masks,
-    const float* __restrict__ chunk_t, const float* __restrict__ t_far_in, const uint64_t* __restrict__ masks,
+    const float* __restrict__ t_more, const float* __restrict__ t_far_in, const uint64_t* __restrict__ masks,
     const int32_t* __restrict__ chunk_base, const float* __restrict__ seg_t,
     const uint64_t* __restrict__ sample_chunks, const int32_t* __restrict__ packed_info, int64_t capacity,
     int32_t* __restrict__ ray_indices, float* __restrict__ t_starts, float* __restrict__ t_ends,
@@ -1607,8 +1842,7 @@ __global__ __launch_bounds__(kTaskThreads) void fill_cone_rays_kernel(
             nz = sample_chunks[ray];
         }
     }
-    // a ray whose last stored chunk exists may go on past the stored chunks
-    const float t_last = limit > 0 ? chunk_t[static_cast<int64_t>(n_masks - 1) * n_rays + ray] : INFINITY;
+    const float t_end = limit > 0 ? t_more[ray] : INFINITY;  // where the ray goes on past the stored chunks
     const int n_tasks = static_cast<int>(__popcll(nz));
     const int t_before = wave_inclusive_sum(n_tasks) - n_tasks;
     const int t_total = read_lane(t_before + n_tasks, kWave - 1);
@@ -1746,22 +1980,14 @@ __global__ __launch_bounds__(kTaskThreads) void fill_cone_rays_kernel(
             wave_lds_sync();  // the queue and the slots are written again next round
         }
     }
-    if (t_last < INFINITY) {
-        // the last stored chunk: walk it, then look the rest of the ray up
-        // again (rays of more than n_masks chunks of candidates, rare)
+    if (t_end < INFINITY) {
+        // look the rest of the ray up again (rays of more than n_masks
+        // chunks of candidates, rare)
         const int64_t last = static_cast<int64_t>(n_masks - 1) * n_rays + ray;
-        const uint64_t m = masks[last];
-        int idx = chunk_base[last] + static_cast<int>(__popcll(m));
+        int idx = chunk_base[last] + static_cast<int>(__popcll(masks[last]));
         const float t_far = t_far_in[ray];
-        float t = t_last;
-        bool ended = false;
-        for (int s = 0; s < kSegsPerChunk && !ended; ++s) {
-            float tb[kConeBatch + 1];
-            const int n_valid = cone_steps(t, t_far, p, tb);
-            ended = n_valid < kConeBatch;
-            t = tb[kConeBatch];
-        }
-        if (!ended && idx < limit) {
+        float t = t_end;
+        if (idx < limit) {
             float o[3], d[3];
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
@@ -1896,6 +2122,16 @@ int march_split(int64_t groups, int waves) {
     return split;
 }
 
+// Rays per workgroup of the segment count: 64, or 32 where their masks
+// would leave too few workgroups to a CU (contraction, 600,000 rays of 40
+// chunks: 611 us a call with 64), and fewer for small batches, so that every
+// CU has eight workgroups.
+int cone_rays(int64_t n_rays, int n_masks) {
+    int rays = n_masks > 24 ? 32 : kConeRaysMax;
+    while (rays > kTaskWaves && n_rays < static_cast<int64_t>(rays) * 2048) rays /= 2;
+    return rays;
+}
+
 // Workspace of the marching calls: the per-workgroup sums of the scan, then
 // n_masks 64-bit occupancy masks per ray, one per chunk of 64 candidates,
 // written by the count pass and replayed by the fill pass.  n_masks covers
@@ -1908,7 +2144,7 @@ struct Layout {
     int n_masks;
     int64_t chunk_t_off, t_far_off, extra_off;  // cone steps only (0 otherwise)
     int64_t base_off, seg_t_off;                // cone steps, segment passes
-    int64_t live_off, tsum_off, tlist_off;      // cone steps, the task list of the segment passes
+    int64_t holding_off;                        // cone steps, segment passes: chunks holding samples
     int64_t halo_off;                           // halo bits built by the count pass (0: none)
     int64_t bytes;
 };
@@ -1921,9 +2157,9 @@ int64_t align256(int64_t b) { return ((b + 255) / 256) * 256; }
 // Uniform steps through the box gain 0.3 ns a ray (128^3: 110 -> 106 us a
 // call at 32,768 rays, 317 -> 243 us at 262,144; even at 16,384, 64 grids
 // even near 200,000).  Cone steps gain from the smallest batches on (they
-// also lose a separate expansion of the ray indices; cascades 96 -> 88 us at
-// 256 rays, 544 -> 281 us at 262,144; contraction 132 -> 124 and 1,391 ->
-// 480 us) unless a few rays are spread over many grids.
+// also lose a separate expansion of the ray indices; cascades 94 -> 55 us at
+// 256 rays, 434 -> 175 us at 262,144; contraction 135 -> 63 and 1,281 ->
+// 258 us) unless a few rays are spread over many grids.
 bool builds_halo(int64_t n_rays, int n_masks, const nacc_grid_desc& grid, const nacc_march_params& p) {
     if (n_masks == 0) return false;
     const int64_t words = halo_words(grid.res) * grid.n_grids;
@@ -1935,27 +2171,25 @@ Layout workspace_layout(int64_t n_rays, const nacc_grid_desc& grid, const nacc_m
     Layout l;
     // the workgroup sums, then the scan's scratch
     const int64_t nb = num_blocks(n_rays);
-    l.sums_bytes = align256((nb * march_split(nb, 1) + scan_scratch_values(nb)) * static_cast<int64_t>(sizeof(int64_t)));
     l.n_masks = 0;
     if (p.dt > 0.0f) {
         const int64_t k = candidate_bound(grid, p, int64_t{kMaxMaskChunks} * kWave);
         l.n_masks = static_cast<int>((k + kWave - 1) / kWave);
     }
+    const int64_t split = p.cone > 0.0f ? kRaysPerBlock / cone_rays(n_rays, l.n_masks) : march_split(nb, 1);
+    l.sums_bytes = align256((nb * split + scan_scratch_values(nb * split)) * static_cast<int64_t>(sizeof(int64_t)));
     l.bytes = l.sums_bytes + align256(n_rays * l.n_masks * static_cast<int64_t>(sizeof(uint64_t)));
     l.chunk_t_off = l.t_far_off = l.extra_off = l.base_off = l.seg_t_off = 0;
-    l.live_off = l.tsum_off = l.tlist_off = 0;
+    l.holding_off = 0;
     if (p.cone > 0.0f) {
         l.chunk_t_off = l.bytes;
         l.t_far_off = l.chunk_t_off + align256(n_rays * l.n_masks * static_cast<int64_t>(sizeof(float)));
         l.extra_off = l.t_far_off + align256(n_rays * static_cast<int64_t>(sizeof(float)));
         l.base_off = l.extra_off + align256(n_rays * static_cast<int64_t>(sizeof(int32_t)));
         l.seg_t_off = l.base_off + align256(n_rays * l.n_masks * static_cast<int64_t>(sizeof(int32_t)));
-        l.live_off = l.seg_t_off + align256(n_rays * l.n_masks * kSegsPerChunk * static_cast<int64_t>(sizeof(float)));
-        l.tsum_off = l.live_off + align256(n_rays * static_cast<int64_t>(sizeof(uint64_t)));
-        const int64_t n_sums = nb * l.n_masks;  // per (chunk, workgroup), the total, the scan's scratch
-        l.tlist_off = l.tsum_off + align256((n_sums + 1 + scan_scratch_values(n_sums)) *
-                                            static_cast<int64_t>(sizeof(int64_t)));
-        l.bytes = l.tlist_off + align256(n_rays * l.n_masks * static_cast<int64_t>(sizeof(int32_t)));
+        l.holding_off =
+            l.seg_t_off + align256(n_rays * l.n_masks * kSegsPerChunk * static_cast<int64_t>(sizeof(float)));
+        l.bytes = l.holding_off + align256(n_rays * static_cast<int64_t>(sizeof(uint64_t)));
     }
     l.halo_off = 0;
     if (builds_halo(n_rays, l.n_masks, grid, p)) {
@@ -1972,9 +2206,7 @@ struct ConeWork {
     int32_t* extra;       // [n_rays]
     int32_t* chunk_base;  // [n_masks][n_rays]: samples of the ray before each chunk
     float* seg_t;         // [n_masks][n_rays][kSegsPerChunk]: t at the start of segments holding samples
-    uint64_t* live_chunks;  // [n_rays]: chunks in the task list (contraction lookup)
-    int64_t* task_sums;     // [n_masks][workgroups] + 1: scan of the task counts, then the total
-    int32_t* task_list;     // [n_masks * n_rays]
+    uint64_t* sample_chunks;  // [n_rays]: bits of the chunks holding samples
     int n_masks;
 };
 
@@ -1987,12 +2219,13 @@ ConeWork cone_work(void* workspace, const Layout& l) {
     w.extra = reinterpret_cast<int32_t*>(b + l.extra_off);
     w.chunk_base = reinterpret_cast<int32_t*>(b + l.base_off);
     w.seg_t = reinterpret_cast<float*>(b + l.seg_t_off);
-    w.live_chunks = reinterpret_cast<uint64_t*>(b + l.live_off);
-    w.task_sums = reinterpret_cast<int64_t*>(b + l.tsum_off);
-    w.task_list = reinterpret_cast<int32_t*>(b + l.tlist_off);
+    w.sample_chunks = reinterpret_cast<uint64_t*>(b + l.holding_off);
     w.n_masks = l.n_masks;
     return w;
 }
+
+// Whether a cone-stepped call marches by segments (halo bits given).
+bool cone_segments(const ConeWork& cw, const uint32_t* halo) { return cw.n_masks > 0 && halo != nullptr; }
 
 // Halo bits of a skip buffer (see halo_offset).
 const uint32_t* halo_of(const uint8_t* skip, const GridK& g) {
@@ -2036,49 +2269,30 @@ unsigned task_blocks(int n_masks, int64_t n_rays) {
     return static_cast<unsigned>((static_cast<int64_t>(n_masks) * n_rays + kTaskThreads - 1) / kTaskThreads);
 }
 
-// The segment passes run over a task list of the chunks the starts pass
-// could not prove empty: contraction lookup, task ids within int32.  The
-// culling and the list's scan cost 60 us, the segment passes they save take
-// less up to 4 million chunks (40 chunks a ray: 126 against 168 us a call at
-// 4,096 rays, 220 against 226 us at 65,536, 582 against 480 us at 262,144).
-constexpr int64_t kMinListedTasks = int64_t{1} << 22;
-
 template <int LOOKUP>
-bool cone_task_list(const ConeWork& cw, int64_t n_rays) {
-    const int64_t tasks = static_cast<int64_t>(cw.n_masks) * n_rays;
-    return LOOKUP == NACC_LOOKUP_CONTRACT && tasks >= kMinListedTasks && tasks <= INT32_MAX;
-}
-
-template <int LOOKUP>
-void launch_count_cone(const ConeWork& cw, const uint32_t* halo, int64_t nb, hipStream_t s, const float* o,
-                       const float* d, const int32_t* gid, int64_t n, const uint32_t* bits, const GridK& g,
-                       const ClipK& c, const StepK& p, int32_t* packed, int64_t* sums, uint64_t*, int) {
-    const bool segments = halo != nullptr;
-    const bool listed = segments && cone_task_list<LOOKUP>(cw, n);
+void launch_count_cone(const ConeWork& cw, const uint8_t* skip, const uint32_t* halo, int64_t nb, hipStream_t s,
+                       const float* o, const float* d, const int32_t* gid, int64_t n, const uint32_t* bits,
+                       const GridK& g, const ClipK& c, const StepK& p, int32_t* packed, int64_t* sums, uint64_t*,
+                       int) {
     const ConeTable tab = cone_table(p, cw.n_masks);
-    if (listed) {
-        hipLaunchKernelGGL((cone_starts_kernel<LOOKUP, true>), dim3(nb), dim3(kRaysPerBlock), 0, s, o, d, gid, n, g, c,
-                           p, cw.n_masks, cw.chunk_t, cw.t_far, cw.extra, halo, cw.live_chunks, cw.task_sums, tab);
-        const int64_t n_sums = nb * cw.n_masks;
-        scan_exclusive(cw.task_sums, n_sums, cw.task_sums + n_sums, cw.task_sums + n_sums + 1, s);
-        hipLaunchKernelGGL(task_list_kernel, dim3(nb), dim3(kRaysPerBlock), 0, s, cw.task_sums, n, cw.n_masks,
-                           cw.live_chunks, cw.task_list);
-    } else {
-        hipLaunchKernelGGL((cone_starts_kernel<LOOKUP, false>), dim3(nb), dim3(kRaysPerBlock), 0, s, o, d, gid, n, g,
-                           c, p, cw.n_masks, cw.chunk_t, cw.t_far, cw.extra, nullptr, nullptr, nullptr, tab);
+    if (cone_segments(cw, halo)) {
+        const int rays = cone_rays(n, cw.n_masks);
+        const bool walks = LOOKUP != NACC_LOOKUP_CONTRACT || tab.n == 0;
+        hipLaunchKernelGGL((count_cone_kernel<LOOKUP>), dim3(static_cast<unsigned>((n + rays - 1) / rays)),
+                           dim3(kTaskThreads), cone_lds(rays, cw.n_masks, walks, LOOKUP == NACC_LOOKUP_CONTRACT).bytes, s, o, d, gid, n, bits, halo,
+                           skip, g, c, p, cw.n_masks, rays, walks ? 1 : 0, packed, sums, cw.masks, cw.chunk_base,
+                           cw.seg_t, cw.chunk_t, cw.t_far, cw.sample_chunks, tab);
+        return;
     }
-    if (cw.n_masks > 0 && segments) {
-        hipLaunchKernelGGL((count_cone_segments_kernel<LOOKUP>), dim3(task_blocks(cw.n_masks, n)), dim3(kTaskThreads),
-                           0, s, o, d, gid, n, bits, halo, g, p, cw.n_masks, cw.chunk_t, cw.t_far, cw.masks, cw.extra,
-                           cw.seg_t, listed ? cw.task_list : nullptr,
-                           listed ? cw.task_sums + nb * cw.n_masks : nullptr, tab);
-    } else if (cw.n_masks > 0) {
+    hipLaunchKernelGGL(cone_starts_kernel, dim3(nb), dim3(kRaysPerBlock), 0, s, o, d, gid, n,
+                       gid != nullptr && LOOKUP != NACC_LOOKUP_CASCADE, g, c, p, cw.n_masks, cw.chunk_t, cw.t_far,
+                       cw.extra, tab);
+    if (cw.n_masks > 0) {
         hipLaunchKernelGGL((count_cone_chunks_kernel<LOOKUP>), dim3(task_blocks(cw.n_masks, n)), dim3(kTaskThreads), 0,
                            s, o, d, gid, n, bits, g, p, cw.n_masks, cw.chunk_t, cw.t_far, cw.masks, cw.extra);
     }
     hipLaunchKernelGGL(cone_counts_kernel, dim3(nb), dim3(kRaysPerBlock), 0, s, n, cw.n_masks, p.max_per_ray, cw.masks,
-                       cw.extra, packed, sums, segments ? cw.chunk_base : nullptr,
-                       listed ? cw.live_chunks : nullptr, segments ? cw.live_chunks : nullptr);
+                       cw.extra, packed, sums);
 }
 
 template <int LOOKUP, bool SKIP, typename... A>
@@ -2104,7 +2318,7 @@ void launch_fill_cone(const uint8_t* skip, bool segments, const ConeWork* cw, in
         const unsigned blocks = static_cast<unsigned>((n + per_block - 1) / per_block);
         hipLaunchKernelGGL((fill_cone_rays_kernel<LOOKUP>), dim3(blocks), dim3(kTaskThreads), 0, s, o, d, gid, n, bits,
                            g, p, cw->n_masks, cw->chunk_t, cw->t_far, cw->masks, cw->chunk_base, cw->seg_t,
-                           cw->live_chunks, packed, capacity, ri, ts, te, status);
+                           cw->sample_chunks, packed, capacity, ri, ts, te, status);
         return;
     }
     if (cw != nullptr && cw->n_masks > 0) {  // replay the count pass's chunks, one lane per chunk
@@ -2130,7 +2344,7 @@ using Lookup = std::integral_constant<int, LOOKUP>;
 template <int LOOKUP, typename... A>
 void dispatch_count(const uint8_t* skip, const uint32_t* halo, const ConeWork* cw, A&&... a) {
     if (cw != nullptr) {
-        launch_count_cone<LOOKUP>(*cw, halo, a...);
+        launch_count_cone<LOOKUP>(*cw, skip, halo, a...);
     } else if (LOOKUP == NACC_LOOKUP_AABB ? halo != nullptr : skip != nullptr) {
         launch_count_waves<LOOKUP, true>(skip, halo, a...);
     } else {
@@ -2171,6 +2385,7 @@ int march_count_launch(const float* rays_o, const float* rays_d, const int32_t* 
     const int64_t nb = num_blocks(n_rays);
     const uint8_t* skip = usable_skip(grid_skip, *grid);
     int st = NACC_OK;
+    bool by_segments = false;
     if (nb > 0) {
         const uint32_t* halo = halo_of(skip, g);
         if (halo == nullptr && own_halo != nullptr) {
@@ -2179,6 +2394,7 @@ int march_count_launch(const float* rays_o, const float* rays_d, const int32_t* 
             if (st != NACC_OK) return st;
             halo = own_halo;
         }
+        by_segments = cw != nullptr && cone_segments(*cw, halo);
         auto run = [&](auto lookup) {
             dispatch_count<decltype(lookup)::value>(skip, halo, cw, nb, s, rays_o, rays_d, grid_id, n_rays, grid_bits,
                                                     g, c, p, packed_info, sums, masks, n_masks);
@@ -2195,9 +2411,11 @@ int march_count_launch(const float* rays_o, const float* rays_d, const int32_t* 
         scan_exclusive(sums, 0, total, nullptr, s);
         return check_launch("march scan");
     }
-    const int split = cw != nullptr ? 1 : march_split(nb, tuning().march_waves_per_group);
-    launch_starts(sums, nb * split, kWaveLog2 - __builtin_ctz(static_cast<unsigned>(split)), n_rays, packed_info,
-                  total, s);
+    int part_rays = kRaysPerBlock;  // rays of a sum
+    if (cw == nullptr) part_rays /= march_split(nb, tuning().march_waves_per_group);
+    else if (by_segments) part_rays = cone_rays(n_rays, cw->n_masks);
+    launch_starts(sums, (n_rays + part_rays - 1) / part_rays, __builtin_ctz(static_cast<unsigned>(part_rays)), n_rays,
+                  packed_info, total, s);
     return check_launch("march starts");
 }
 

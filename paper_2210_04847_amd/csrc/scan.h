@@ -95,16 +95,18 @@ inline void scan_exclusive(int64_t* v, int64_t n, int64_t* total, int64_t* scrat
                        scratch, total);
 }
 
-// packed_info[r].start = offset of r's workgroup + exclusive scan of the
-// counts inside it (one wave = the workgroup's 64 rays).  Starts that do
-// not fit int32 saturate; the fill pass then reports NACC_ECAPACITY.
+// packed_info[r].start = offset of r's part (of `1 << log_part` rays, at most
+// 64) + exclusive scan of the counts inside it (one wave = 64 rays).  Starts
+// that do not fit int32 saturate; the fill pass then reports NACC_ECAPACITY.
 __global__ __launch_bounds__(kRaysPerBlock) void finalize_starts_kernel(
-    const int64_t* __restrict__ block_offsets, int64_t n_rays, int32_t* __restrict__ packed_info) {
+    const int64_t* __restrict__ part_offsets, int log_part, int64_t n_rays, int32_t* __restrict__ packed_info) {
     const int64_t r = static_cast<int64_t>(blockIdx.x) * kRaysPerBlock + threadIdx.x;
     const int n = r < n_rays ? packed_info[2 * r + 1] : 0;
-    const int incl = wave_inclusive_sum(n);
-    const int64_t start = block_offsets[blockIdx.x] + (incl - n);
-    if (r < n_rays) packed_info[2 * r] = static_cast<int32_t>(min(start, static_cast<int64_t>(INT32_MAX)));
+    const int before = wave_inclusive_sum(n) - n;
+    const int part_before = __builtin_amdgcn_ds_bpermute(((lane_id() >> log_part) << log_part) << 2, before);
+    if (r >= n_rays) return;
+    const int64_t start = part_offsets[r >> log_part] + (before - part_before);
+    packed_info[2 * r] = static_cast<int32_t>(min(start, static_cast<int64_t>(INT32_MAX)));
 }
 
 // The same and the total in one launch, for up to kMaxParts sums of
@@ -157,9 +159,8 @@ __global__ __launch_bounds__(kStartsThreads) void starts_kernel(const int64_t* _
 }
 
 // Starts and total from the counts in packed_info and their sums over parts
-// of `1 << log_part` consecutive rays (n_rays >= 1).  More than kMaxParts
-// parts must be of kRaysPerBlock rays; `sums` is then followed by the scan's
-// scratch and overwritten.
+// of `1 << log_part` consecutive rays (n_rays >= 1).  `sums` is followed by
+// the scan's scratch, and overwritten, if there are more than kMaxParts.
 inline void launch_starts(int64_t* sums, int64_t n_parts, int log_part, int64_t n_rays, int32_t* packed_info,
                           int64_t* total, hipStream_t s) {
     if (n_parts <= kMaxParts) {
@@ -169,8 +170,8 @@ inline void launch_starts(int64_t* sums, int64_t n_parts, int log_part, int64_t 
         return;
     }
     scan_exclusive(sums, n_parts, total, sums + n_parts, s);
-    hipLaunchKernelGGL(finalize_starts_kernel, dim3(static_cast<unsigned>(n_parts)), dim3(kRaysPerBlock), 0, s, sums,
-                       n_rays, packed_info);
+    hipLaunchKernelGGL(finalize_starts_kernel, dim3(static_cast<unsigned>((n_rays + kRaysPerBlock - 1) / kRaysPerBlock)),
+                       dim3(kRaysPerBlock), 0, s, sums, log_part, n_rays, packed_info);
 }
 
 inline int64_t num_blocks(int64_t n_rays) { return (n_rays + kRaysPerBlock - 1) / kRaysPerBlock; }

@@ -1,7 +1,7 @@
 """The sizes at which the library changes kernels, against the oracle: the
-marching count pass building halo bits of its own (or not) and listing the
-chunks of cone steps (or not), the rays per wave of the uniform fill and of
-fused inference."""
+marching count pass building halo bits of its own (or not), the rays per
+workgroup of cone steps, the rays per wave of the uniform fill and of fused
+inference."""
 import numpy as np
 import pytest
 import torch
@@ -32,12 +32,55 @@ def test_cone_many_grids(n_grids, n_rays):
 
 
 @pytest.mark.parametrize("n_rays", [104857, 104858])
-def test_contraction_task_list(n_rays):
-    """2,512 candidates, 40 chunks a ray: listed from 104,858 rays on."""
+def test_contraction_many_chunks(n_rays):
+    """2,512 candidates, 40 chunks a ray, 4.2 million chunks."""
     mask = synth.random_mask(64 ** 3, 0.01, 13)
     o, d = synth.rays_unbounded(n_rays, 63)
     compare(o, d, mask, 64, np.array(synth.CONTRACT_BOX, np.float32), 0.2, 1e4, synth.STEP_1024,
             cone=1 / 256, lookup=2, max_per_ray=64)
+
+
+@pytest.mark.parametrize("n_rays", [1, 5, 8191, 8192, 16384, 32768, 65536, 131072])
+def test_cone_rays_per_workgroup(n_rays):
+    """4 to 64 rays a workgroup; rays that start at the near plane (inside
+    the box), outside it, and both in a wave."""
+    mask = synth.random_mask(16 ** 3, 0.05, 21)
+    o, d = synth.rays_toward_origin(n_rays, 65)
+    for step in (1, 2):
+        o[::step] *= 0.1
+        compare(o, d, mask, 16, BOX, 0.05, 1e10, 0.02, cone=1 / 64, dt_max=0.2)
+        o[::step] *= 10.0
+
+
+@pytest.mark.parametrize("base,levels,dt,cone", [
+    (1.0, 5, 0.02, 1 / 256),       # a level or two per segment of 8 steps
+    (0.0625, 9, 0.2, 1 / 16),      # many levels per segment
+    (2.0 ** -62, 3, 2.0 ** -66, 0.01),  # scales near the end of the exponent range
+    (2.0 ** -40, 3, 2.0 ** -44, 0.01),
+])
+def test_cone_cascade_levels(base, levels, dt, cone):
+    res = 16
+    mask = synth.random_mask(levels * res ** 3, 0.2, 22)
+    o, d = synth.rays_toward_origin(700, 66)
+    o = (o * np.float32(0.3 * base)).astype(np.float32)
+    box = np.array([-base] * 3 + [base] * 3, np.float32)
+    compare(o, d, mask, res, box, 0.01 * base, base * 2.0 ** levels, dt, cone=cone, n_grids=levels, lookup=1)
+
+
+@pytest.mark.parametrize("res,p_occ", [(4, 0.5), (12, 0.5), (12, 0.95), (20, 1.0), (32, 0.5), (64, 0.97), (64, 0.002)])
+@pytest.mark.parametrize("near,far,dt,cone", [
+    (0.2, 1e4, 0.01, 1 / 256),
+    (0.0, 1e10, 0.005, 1 / 128),   # steps that may stall by their size alone
+    (0.2, 3.0, 0.02, 1 / 256),     # rays ending inside a segment
+    (0.2, 40.0, 0.0005, 1 / 4096),  # past the stored chunks
+    (40000.0, 1e6, 0.001, 1e-9),   # stalled from the start
+])
+def test_cone_contraction_cells(res, p_occ, near, far, dt, cone):
+    """Segments decided by the cells within their bounds, and not: sparse,
+    ragged and full grids, rows of cells that cross words."""
+    mask = synth.random_mask(res ** 3, p_occ, 23)
+    o, d = synth.rays_unbounded(150, 67)
+    compare(o, d, mask, res, np.array(synth.CONTRACT_BOX, np.float32), near, far, dt, cone=cone, lookup=2)
 
 
 @pytest.mark.parametrize("n_rays,dt", [(1, 0.0137), (63, 0.0137), (2049, 0.0137), (4095, 0.0025),
@@ -248,3 +291,10 @@ def test_gradients_of_unread_outputs(read, attrs):
         grads.append((sig.grad, at.grad))
     for a, b in zip(*grads):
         assert torch.equal(a, b)
+
+
+def test_cone_starts_past_one_launch():
+    """More than 8,192 parts of 32 rays: scanned, a wave placing two."""
+    mask = synth.random_mask(8 ** 3, 0.05, 24)
+    o, d = synth.rays_unbounded(262144 + 33, 68)
+    compare(o, d, mask, 8, np.array(synth.CONTRACT_BOX, np.float32), 0.2, 20.0, 0.012, cone=1e-6, lookup=2)
