@@ -549,15 +549,34 @@ struct FillLds {
     int32_t taken[kFillRaysMax];
 };
 
+// Times of the sample `code`: uniform steps from the ray's t_near, or (cone
+// steps) entries of the near-plane lattice, in LDS.
+struct UniformTimes {
+    const float* t_near;
+    float dt;
+    __device__ __forceinline__ float start(uint32_t code) const {
+        return t_near[code >> kCodeRayShift] + static_cast<float>(code & ((1u << kCodeRayShift) - 1u)) * dt;
+    }
+    __device__ __forceinline__ float end(uint32_t code) const {
+        const float k = static_cast<float>(code & ((1u << kCodeRayShift) - 1u));
+        return t_near[code >> kCodeRayShift] + (k + 1.0f) * dt;  // k + 1 is exact
+    }
+};
+
+struct TableTimes {
+    const float* t;
+    __device__ __forceinline__ float start(uint32_t code) const { return t[code & ((1u << kCodeRayShift) - 1u)]; }
+    __device__ __forceinline__ float end(uint32_t code) const { return t[(code & ((1u << kCodeRayShift) - 1u)) + 1u]; }
+};
+
 // Stores the sample of `code` at position p = b + lane.
-__device__ __forceinline__ void store_sample(const FillOut& out, const FillLds& q, float dt, int64_t first_ray, int b,
+template <typename Times>
+__device__ __forceinline__ void store_sample(const FillOut& out, const Times& times, int64_t first_ray, int b,
                                              uint32_t code) {
     const uint32_t off = static_cast<uint32_t>(lane_id());
-    const float t_near = q.t_near[code >> kCodeRayShift];
-    const float k = static_cast<float>(code & ((1u << kCodeRayShift) - 1u));
     (out.ray_indices + b)[off] = static_cast<int32_t>(first_ray + (code >> kCodeRayShift));
-    (out.t_starts + b)[off] = t_near + k * dt;
-    (out.t_ends + b)[off] = t_near + (k + 1.0f) * dt;  // k + 1 is exact
+    (out.t_starts + b)[off] = times.start(code);
+    (out.t_ends + b)[off] = times.end(code);
 }
 
 // Expands the first n <= 64 queued halves into the list from position `pos`
@@ -566,8 +585,9 @@ __device__ __forceinline__ void store_sample(const FillOut& out, const FillLds& 
 // end of the wave's first block, if it does not begin it).  The incomplete
 // last block moves to the list's front.  Returns the position after the
 // last sample.
-__device__ __forceinline__ int store_halves(const FillOut& out, FillLds& q, int n, float dt, int64_t first_ray,
-                                            int head_end, int pos, int& block) {
+template <typename Times>
+__device__ __forceinline__ int store_halves(const FillOut& out, FillLds& q, int n, const Times& times,
+                                            int64_t first_ray, int head_end, int pos, int& block) {
     const int lane = lane_id();
     uint32_t m = lane < n ? q.queue_mask[lane] : 0u;
     const uint32_t code = lane < n ? q.queue_code[lane] : 0u;
@@ -587,7 +607,7 @@ __device__ __forceinline__ int store_halves(const FillOut& out, FillLds& q, int 
         q.head[lane] = q.codes[lane];
         b += kWave;
     }
-    for (; b + kWave <= end; b += kWave) store_sample(out, q, dt, first_ray, b, q.codes[b - block + lane]);
+    for (; b + kWave <= end; b += kWave) store_sample(out, times, first_ray, b, q.codes[b - block + lane]);
     if (b > block) {
         const uint16_t c = q.codes[b - block + lane];
         wave_lds_sync();
@@ -596,6 +616,80 @@ __device__ __forceinline__ int store_halves(const FillOut& out, FillLds& q, int 
     }
     wave_lds_sync();
     return end;
+}
+
+// The list of a wave: it holds the positions [block, pos); `queued` halves
+// wait for it; head_end: see store_halves.
+struct FillList {
+    int pos, block, head_end, queued;
+};
+
+__device__ __forceinline__ FillList begin_list(int pos) {
+    FillList l;
+    l.pos = pos;
+    l.block = pos & ~(kWave - 1);
+    l.head_end = l.block == pos ? -1 : l.block + kWave;
+    l.queued = 0;
+    return l;
+}
+
+// Queues the samples of 64 chunks, a lane's mask and the code of its first
+// candidate, in lane order, and lists and stores what fills the wave (`last`:
+// everything).
+template <typename Times>
+__device__ __forceinline__ void queue_chunks(const FillOut& out, FillLds& q, const Times& times, uint64_t m,
+                                             uint32_t code, bool last, int64_t first_ray, FillList& list) {
+    const int lane = lane_id();
+    const uint32_t lo = static_cast<uint32_t>(m), hi = static_cast<uint32_t>(m >> 32);
+    const uint64_t has_lo = ballot(lo != 0u), has_hi = ballot(hi != 0u);
+    int at = list.queued + bits_below(has_lo) + bits_below(has_hi);
+    if (lo != 0u) {
+        q.queue_mask[at] = lo;
+        q.queue_code[at++] = static_cast<uint16_t>(code);
+    }
+    if (hi != 0u) {
+        q.queue_mask[at] = hi;
+        q.queue_code[at] = static_cast<uint16_t>(code + 32u);
+    }
+    list.queued += static_cast<int>(__popcll(has_lo)) + static_cast<int>(__popcll(has_hi));
+    wave_lds_sync();
+    while (list.queued >= kWave || (last && list.queued > 0)) {
+        const int n = min(list.queued, kWave);
+        list.pos = store_halves(out, q, n, times, first_ray, list.head_end, list.pos, list.block);
+        list.queued -= n;
+        if (list.queued > 0) {  // at most 127 halves move up
+            const uint32_t m0 = q.queue_mask[kWave + lane], m1 = q.queue_mask[2 * kWave + lane];
+            const uint16_t c0 = q.queue_code[kWave + lane], c1 = q.queue_code[2 * kWave + lane];
+            wave_lds_sync();
+            q.queue_mask[lane] = m0;
+            q.queue_mask[kWave + lane] = m1;
+            q.queue_code[lane] = c0;
+            q.queue_code[kWave + lane] = c1;
+            wave_lds_sync();
+        }
+    }
+}
+
+// The ends of a wave's samples, after the workgroup's barrier.
+template <typename Times>
+__device__ __forceinline__ void end_list(const FillOut& out, const FillLds& q, const Times& times, int64_t first_ray,
+                                         int pos0, const FillList& list) {
+    const int lane = lane_id();
+    if (list.head_end >= 0 && list.head_end <= list.pos && lane >= (pos0 & (kWave - 1))) {
+        store_sample(out, times, first_ray, list.head_end - kWave, q.head[lane]);
+    }
+    if (list.block + lane < list.pos && list.block + lane >= pos0) {
+        store_sample(out, times, first_ray, list.block, q.codes[lane]);
+    }
+}
+
+// The part of a chunk's mask that its ray's limit leaves it; in_ray: the
+// ray's samples before the chunk.
+__device__ __forceinline__ uint64_t capped_mask(uint64_t m, int in_ray, int limit) {
+    const int take = limit - in_ray;
+    if (take <= 0) return 0ull;
+    if (take < static_cast<int>(__popcll(m))) m &= (1ull << nth_set_bit(m, take)) - 1ull;
+    return m;
 }
 
 // The samples of the stored chunks of one ray (lane j of `mine` holds chunk
@@ -684,13 +778,12 @@ __global__ __launch_bounds__(kFillThreads) void fill_uniform_kernel(
     // every ray's samples are those of its stored chunks (the first `limit`
     // of them), and they lie side by side inside the output
     const bool simple = ballot(lane < n_mine && (limit > stored || (limit > 0 && start != pos0 + before))) == 0ull &&
-                        pos0 >= 0 && static_cast<int64_t>(pos0) + n_out <= capacity;
+                        pos0 >= 0 && static_cast<int64_t>(pos0) + n_out <= min(capacity, static_cast<int64_t>(INT32_MAX));
     const bool capped = ballot(limit < stored) != 0ull;
-    int pos = pos0, block = pos0 & ~(kWave - 1);  // the list holds the positions [block, pos)
-    const int head_end = block == pos0 ? -1 : block + kWave;
+    FillList list = begin_list(pos0);
+    const UniformTimes times{q.t_near, p.dt};
     bool overflow = false;
     if (simple) {
-        int queued = 0;
         int carried = 0;  // samples in earlier groups of the ray that group i begins with
         const int groups = (n_flat + kWave - 1) / kWave;
         for (int i = 0; i < groups; ++i) {
@@ -706,42 +799,10 @@ __global__ __launch_bounds__(kFillThreads) void fill_uniform_kernel(
                 const int ray_lane = static_cast<int>(ray) * n_masks - i * kWave;  // of the ray's first chunk
                 const int base = lane_value(excl, max(ray_lane, 0));
                 const int in_ray = ray_lane >= 0 ? excl - base : excl + carried;
-                const int take = lane_value(limit, static_cast<int>(min(ray, 63u))) - in_ray;
                 carried = read_lane(in_ray + count, kWave - 1);
-                if (take <= 0) {
-                    m = 0ull;
-                } else if (take < count) {
-                    m &= (1ull << nth_set_bit(m, take)) - 1ull;
-                }
+                m = capped_mask(m, in_ray, lane_value(limit, static_cast<int>(min(ray, 63u))));
             }
-            const uint32_t lo = static_cast<uint32_t>(m), hi = static_cast<uint32_t>(m >> 32);
-            const uint64_t has_lo = ballot(lo != 0u), has_hi = ballot(hi != 0u);
-            int at = queued + bits_below(has_lo) + bits_below(has_hi);
-            if (lo != 0u) {
-                q.queue_mask[at] = lo;
-                q.queue_code[at++] = static_cast<uint16_t>(code);
-            }
-            if (hi != 0u) {
-                q.queue_mask[at] = hi;
-                q.queue_code[at] = static_cast<uint16_t>(code + 32u);
-            }
-            queued += static_cast<int>(__popcll(has_lo)) + static_cast<int>(__popcll(has_hi));
-            wave_lds_sync();
-            while (queued >= kWave || (i + 1 == groups && queued > 0)) {
-                const int n = min(queued, kWave);
-                pos = store_halves(out, q, n, p.dt, first, head_end, pos, block);
-                queued -= n;
-                if (queued > 0) {  // at most 127 halves move up
-                    const uint32_t m0 = q.queue_mask[kWave + lane], m1 = q.queue_mask[2 * kWave + lane];
-                    const uint16_t c0 = q.queue_code[kWave + lane], c1 = q.queue_code[2 * kWave + lane];
-                    wave_lds_sync();
-                    q.queue_mask[lane] = m0;
-                    q.queue_mask[kWave + lane] = m1;
-                    q.queue_code[lane] = c0;
-                    q.queue_code[kWave + lane] = c1;
-                    wave_lds_sync();
-                }
-            }
+            queue_chunks(out, q, times, m, code, i + 1 == groups, first, list);
         }
     }
     // rays going on past the stored chunks or not fitting the output, ray by
@@ -763,12 +824,7 @@ __global__ __launch_bounds__(kFillThreads) void fill_uniform_kernel(
     }
     if (overflow && status != nullptr) *status = NACC_ECAPACITY;
     __syncthreads();
-    if (simple && head_end >= 0 && head_end <= pos && lane >= (pos0 & (kWave - 1))) {
-        store_sample(out, q, p.dt, first, head_end - kWave, q.head[lane]);
-    }
-    if (simple && block + lane < pos && block + lane >= pos0) {
-        store_sample(out, q, p.dt, first, block, q.codes[lane]);
-    }
+    if (simple) end_list(out, q, times, first, pos0, list);
 }
 
 // Cone steps: the lattice is a recurrence in t, t_{k+1} = t_k +
@@ -1388,9 +1444,10 @@ __global__ __launch_bounds__(kTaskThreads) void fill_cone_chunks_kernel(
 // chunk's 64 candidates form 8 segments of kConeBatch; the count pass tests
 // one halo bit per segment at its centre, and looks up, one segment per
 // lane, those that may hold samples.  A segment's 8 occupancy bits are byte s
-// of its chunk's mask (the mask of the plain passes), and the t at the start
-// of every segment holding samples is stored, so the fill pass writes them
-// without walking the recurrence again.
+// of its chunk's mask (the mask of the plain passes).  The fill pass does not
+// walk the recurrence again: its times are on the near-plane lattice, or
+// follow from the t at the start of their segment, which is stored for rays
+// that do not start at the near plane.
 //
 // A clear halo bit proves a segment empty when all its midpoints provably
 // map within kHaloReach cells of the centre's cell in the grid the centre is
@@ -1473,10 +1530,11 @@ constexpr int kConeRaysMax = kRaysPerBlock;
 constexpr int kConeRayFloats = 20;  // 16-byte fields, 16 different ones in different banks
 constexpr int kChunkQueue = kWave + kSegsPerChunk;
 constexpr int kSegStack = 2 * kWave;
-// A queued segment: its number (bits 0 to 2), chunk (3 to 8), ray (9 to 14)
-// and levels.
+// A queued segment: its number (bits 0 to 2), chunk (3 to 8), ray (9 to 14),
+// levels and whether its ray is not on the table.
 constexpr uint32_t kSegOneLevel = 1u << 15, kSegWide = 1u << 16;
-constexpr int kSegLevelShift = 17;
+constexpr uint32_t kSegOwnLattice = 1u << 17;
+constexpr int kSegLevelShift = 18;
 struct ConeLds {
     int tab, masks, starts, seg_t, seg_id, near_t, near_end, near_id, chunks, bytes;  // byte offsets, after the rays
 };
@@ -1497,6 +1555,9 @@ __host__ __device__ inline ConeLds cone_lds(int rays, int n_masks, bool walks, b
     return l;
 }
 
+// In a ray's count of stored samples: the ray is not on the table.
+constexpr uint32_t kOwnLattice = 1u << 31;
+
 // Count pass of the cone steps with halo bits, one launch.  A workgroup takes
 // `rays` consecutive rays, a quarter of them a wave.  Each wave works
 // through three stages, 64 items at a time, one per lane: chunks of its rays
@@ -1508,8 +1569,8 @@ __host__ __device__ inline ConeLds cone_lds(int rays, int n_masks, bool walks, b
 // runs as soon as it can fill the wave, so that every stage but the last
 // of each wave runs with full lanes whatever the share of items kept.  The
 // hits, a byte a segment, make the chunk masks in LDS; the first wave then
-// counts each ray's samples and writes the masks and the counts before
-// each chunk for the fill pass.
+// counts each ray's samples and writes the masks that are not empty for the
+// fill pass.
 // Chunks and segments of a ray that starts at the near plane read their
 // starts from the table; other rays' chunk starts are walked at the beginning,
 // one ray per lane (`walks`: the lookup has a clip box, or there is no
@@ -1529,7 +1590,7 @@ __global__ __launch_bounds__(kTaskThreads) void count_cone_kernel(
     int64_t n_rays, const uint32_t* __restrict__ bits, const uint32_t* __restrict__ halo,
     const uint8_t* __restrict__ dist, GridK g, ClipK c, StepK p, int n_masks, int rays, int walks,
     int32_t* __restrict__ packed_info, int64_t* __restrict__ block_sums, uint64_t* __restrict__ masks,
-    int32_t* __restrict__ chunk_base, float* __restrict__ seg_t, float* __restrict__ t_more,
+    uint32_t* __restrict__ ray_stored, float* __restrict__ seg_t, float* __restrict__ t_more,
     float* __restrict__ t_far_out, uint64_t* __restrict__ sample_chunks, ConeTable tab) {
     extern __shared__ float4 lds4[];
     char* const lds = reinterpret_cast<char*>(lds4);
@@ -1549,6 +1610,7 @@ __global__ __launch_bounds__(kTaskThreads) void count_cone_kernel(
         reinterpret_cast<uint64_t*>(lds + l.masks)[i] = 0ull;
     }
     // the rays, one per lane of the first wave
+    bool own_lattice = false;
     float t_far = -INFINITY, t_end = INFINITY;  // t_end: t after the stored chunks, where the ray goes on
     float o[3] = {0.0f, 0.0f, 0.0f}, d[3] = {0.0f, 0.0f, 0.0f};
     uint32_t word0 = 0;
@@ -1567,6 +1629,7 @@ __global__ __launch_bounds__(kTaskThreads) void count_cone_kernel(
             live = clip_ray(o, d, c, p.near_plane, p.far_plane, t, t_far) && live;
             if (!live) t_far = -INFINITY;
             tabled = !live || (tab.n > 0 && t == tab.t[0]);
+            own_lattice = !tabled;
         }
         const ConeHalo k = cone_halo_ray(g, o, d);
         float4* const ray = lds4 + threadIdx.x * (kConeRayFloats / 4);
@@ -1635,7 +1698,9 @@ __global__ __launch_bounds__(kTaskThreads) void count_cone_kernel(
             }
             if (hits != 0u) {
                 lds[l.masks + rl * stride + j * kSegsPerChunk + s] = static_cast<char>(hits);
-                seg_t[(static_cast<int64_t>(j) * n_rays + first + rl) * kSegsPerChunk + s] = t0;
+                if ((id & kSegOwnLattice) != 0u) {
+                    seg_t[(static_cast<int64_t>(j) * n_rays + first + rl) * kSegsPerChunk + s] = t0;
+                }
             }
         } else if (kRanges && (n_near >= kWave || (n_near > 0 && listed))) {
             // 64 segments by the cells within their bounds
@@ -1663,7 +1728,9 @@ __global__ __launch_bounds__(kTaskThreads) void count_cone_kernel(
             if (has && cells == Cells::kOccupied) {
                 const int j = static_cast<int>((id >> 3) & 63u), s = static_cast<int>(id & (kSegsPerChunk - 1));
                 lds[l.masks + rl * stride + j * kSegsPerChunk + s] = static_cast<char>(0xff);
-                seg_t[(static_cast<int64_t>(j) * n_rays + first + rl) * kSegsPerChunk + s] = ta;
+                if ((id & kSegOwnLattice) != 0u) {
+                    seg_t[(static_cast<int64_t>(j) * n_rays + first + rl) * kSegsPerChunk + s] = ta;
+                }
             }
             const bool left = has && cells == Cells::kUndecided;
             const uint64_t m = ballot(left);
@@ -1704,7 +1771,7 @@ __global__ __launch_bounds__(kTaskThreads) void count_cone_kernel(
             live &= cone_segment_live<LOOKUP>(g, hrs, __float_as_uint(kd.z), so, sd, k, ta, te, lv);
             const uint64_t m = ballot(live);
             const int pos = (kRanges ? n_near : n_segs) + bits_below(m);
-            const uint32_t seg = (id << 3) | static_cast<uint32_t>(s);
+            const uint32_t seg = (id << 3) | static_cast<uint32_t>(s) | (kd.y == 0.0f ? kSegOwnLattice : 0u);
             if (kRanges) {
                 if (live) {
                     r_t[pos] = ta;
@@ -1763,16 +1830,14 @@ __global__ __launch_bounds__(kTaskThreads) void count_cone_kernel(
 #pragma unroll 4
         for (int j = 0; j < n_masks; ++j) {
             const uint64_t m = mm[j];
-            // read by the fill pass for the chunks holding samples, and
-            // for the last one of a ray that goes on past it
-            if (m != 0ull || (j == n_masks - 1 && t_end < INFINITY)) {
+            if (m != 0ull) {  // the fill pass reads no others
                 masks[static_cast<int64_t>(j) * n_rays + r] = m;
-                chunk_base[static_cast<int64_t>(j) * n_rays + r] = static_cast<int32_t>(total);
+                holding |= 1ull << j;
             }
-            if (m != 0ull) holding |= 1ull << j;
             total += __popcll(m);
         }
         sample_chunks[r] = holding;
+        ray_stored[r] = static_cast<uint32_t>(total) | (own_lattice ? kOwnLattice : 0u);
         t_more[r] = t_end;
         if (t_end < INFINITY) {
             // past the stored chunks: count the rest of the ray here
@@ -1793,62 +1858,113 @@ __global__ __launch_bounds__(kTaskThreads) void count_cone_kernel(
     if (lane == 0) block_sums[blockIdx.x] = sum;
 }
 
-// Fill pass of the segment count, ray-major with staged stores.  A wave
-// takes kFillRays consecutive rays and lists their (ray, chunk) tasks for the
-// chunks that hold samples (cone_counts_kernel leaves their bits per ray),
-// ray by ray, chunk by chunk, so the segments that hold samples, queued in
-// that order, are in the order of their samples in the output.  The queue
-// is written 64 segments at a time: one lane per segment runs its 8
-// recurrence steps from the stored t at its start and puts its samples
-// (t_start, t_end) into this wave's LDS slots in output order; then the
-// wave stores the slots, 64 consecutive positions at a time, with the ray
-// indices, so every store is coalesced (each segment's samples stored from
-// its own lane scatter 4-byte writes over as many cache lines as lanes).
-// A ray longer than the stored chunks is finished past them by its lane.
+// Fill pass of the segment count.  A wave takes up to kFillRays consecutive
+// rays, whose chunks holding samples (the count pass leaves their bits per
+// ray) are its tasks, ray by ray, chunk by chunk, so in the order of their
+// samples in the output.
+// Rays that start at the near plane (and end within the stored chunks)
+// share one lattice, whose times the workgroup expands from the table into
+// LDS: their masks are listed and stored in whole blocks as in the uniform
+// fill, a sample's times two LDS reads away.
+// Other waves queue the segments that hold samples, 64 at a time: one lane
+// per segment runs its 8 recurrence steps from the stored t at its start and
+// puts its samples (t_start, t_end) into this wave's LDS slots in output
+// order; then the wave stores the slots, 64 consecutive positions at a time
+// (each segment's samples stored from its own lane scatter 4-byte writes
+// over as many cache lines as lanes).  A ray longer than the stored chunks is
+// finished past them by its lane.
+// Bound by the write path: 262,144 rays of a cascade, 19.2 M samples, 56 us
+// (4.1 TB/s) listed, 97 us by segments; 131,071 contracted rays, 13.0 M
+// samples, 44 us and 71 us.  Not storing the segments' starts took 15 and 8
+// us off the list (72 and 52 us): the count's scattered writes drain
+// meanwhile.  8 rays a wave: the same; 4: 99 and 65 us.
 constexpr int kFillSlots = kWave * kConeBatch;  // the samples of 64 segments at most
-// Rays per wave: their tasks still spread over all 64 lanes, and more,
-// shorter waves hide the latency of each round's permutes, LDS round trips
-// and stores better (contraction lookup: 111 -> 94 us at 262,144 rays; 8
-// rays per wave lose again).
-constexpr int kFillRays = 16;
+constexpr int kFillRays = 16;  // the code of a sample holds 4 bits of ray
+
+struct SlotLds {
+    int64_t e_pos[kWave];      // output position of an entry's first sample
+    float t0[kFillSlots];  // the end is a step from the start
+    int32_t e_slot[kWave];     // an entry's first slot
+    int32_t e_ray[kWave];
+    uint16_t q_id[kSegQueue];
+    uint8_t entry[kFillSlots];  // the queue entry (of this round) a slot belongs to
+};
+
+union ConeFillLds {
+    FillLds list;
+    SlotLds slots;
+};
+
+// Floats of the lattice in LDS, and bytes of all.
+__host__ __device__ inline int cone_fill_times(int n_masks) { return n_masks * kWave + 4; }
+__host__ __device__ inline int cone_fill_lds(int n_masks) {
+    return cone_fill_times(n_masks) * 4 + kTaskWaves * static_cast<int>(sizeof(ConeFillLds));
+}
 
 template <int LOOKUP>
-__global__ __launch_bounds__(kTaskThreads) void fill_cone_rays_kernel(
+__global__ __launch_bounds__(kTaskThreads, 6) void fill_cone_rays_kernel(
     const float* __restrict__ rays_o, const float* __restrict__ rays_d, const int32_t* __restrict__ grid_id,
-    int64_t n_rays, const uint32_t* __restrict__ bits, GridK g, StepK p, int n_masks,
+    int64_t n_rays, const uint32_t* __restrict__ bits, GridK g, StepK p, int n_masks, int per,
     const float* __restrict__ t_more, const float* __restrict__ t_far_in, const uint64_t* __restrict__ masks,
-    const int32_t* __restrict__ chunk_base, const float* __restrict__ seg_t,
+    const uint32_t* __restrict__ ray_stored, const float* __restrict__ seg_t,
     const uint64_t* __restrict__ sample_chunks, const int32_t* __restrict__ packed_info, int64_t capacity,
     int32_t* __restrict__ ray_indices, float* __restrict__ t_starts, float* __restrict__ t_ends,
-    int32_t* __restrict__ status) {
-    __shared__ uint16_t q_id[kTaskWaves][kSegQueue];
-    __shared__ float s_t0[kTaskWaves][kFillSlots];
-    __shared__ float s_t1[kTaskWaves][kFillSlots];
-    __shared__ uint8_t s_entry[kTaskWaves][kFillSlots];  // the queue entry (of this round) a slot belongs to
-    __shared__ int64_t e_pos[kTaskWaves][kWave];         // output position of an entry's first sample
-    __shared__ int32_t e_slot[kTaskWaves][kWave];        // its first slot
-    __shared__ int32_t e_ray[kTaskWaves][kWave];
+    int32_t* __restrict__ status, ConeTable tab) {
+    extern __shared__ float4 lds4[];
+    float* const s_times = reinterpret_cast<float*>(lds4);
     const int lane = lane_id();
     const int wave = uniform<int>(static_cast<int>(threadIdx.x) / kWave);
+    ConeFillLds& lds = reinterpret_cast<ConeFillLds*>(s_times + cone_fill_times(n_masks))[wave];
+    const int64_t first = (xcd_grouped<16>(blockIdx.x, gridDim.x) * kTaskWaves + wave) * per;
     // lane i: ray first + i
-    const int64_t ray = (static_cast<int64_t>(blockIdx.x) * kTaskWaves + wave) * kFillRays + lane;
+    const int64_t ray = first + lane;
     int limit = 0;
     int64_t start = 0;
     uint64_t nz = 0ull;
-    if (lane < kFillRays && ray < n_rays) {
+    uint32_t stored = 0u;
+    float t_end = INFINITY;  // where the ray goes on past the stored chunks
+    if (lane < per && ray < n_rays) {
         limit = packed_info[2 * ray + 1];
-        if (limit > 0) {
-            start = packed_info[2 * ray];
-            nz = sample_chunks[ray];
-        }
+        start = packed_info[2 * ray];
+        nz = sample_chunks[ray];
+        stored = ray_stored[ray];
+        t_end = t_more[ray];
     }
-    const float t_end = limit > 0 ? t_more[ray] : INFINITY;  // where the ray goes on past the stored chunks
+    if (limit <= 0) {
+        limit = 0;
+        nz = 0ull;
+        t_end = INFINITY;
+    }
+    for (int i = threadIdx.x; i + 1 < tab.n; i += kTaskThreads) {
+        float t = tab.t[i];
+#pragma unroll
+        for (int u = 0; u < kConeBatch; ++u) {
+            s_times[i * kConeBatch + u] = t;
+            t = t + __builtin_amdgcn_fmed3f(t * p.cone, p.dt, p.dt_max);
+        }
+        if (i + 2 == tab.n) s_times[(i + 1) * kConeBatch] = t;
+    }
+    __syncthreads();
     const int n_tasks = static_cast<int>(__popcll(nz));
     const int t_before = wave_inclusive_sum(n_tasks) - n_tasks;
     const int t_total = read_lane(t_before + n_tasks, kWave - 1);
+    // the wave's samples are on the table, in its stored chunks, and lie side
+    // by side inside the output
+    const int before = wave_inclusive_sum(limit) - limit;
+    const int pos0 = static_cast<int>(read_lane(static_cast<int>(start), 0));
+    const int n_out = read_lane(before + limit, kWave - 1);
+    const bool on_table = limit == 0 || (stored < kOwnLattice && !(t_end < INFINITY) &&
+                                         static_cast<uint32_t>(limit) <= stored &&
+                                         start == static_cast<int64_t>(pos0) + before);
+    const bool simple =
+        ballot(!on_table) == 0ull && pos0 >= 0 && static_cast<int64_t>(pos0) + n_out <= min(capacity, static_cast<int64_t>(INT32_MAX));
+    const FillOut out{ray_indices, t_starts, t_ends};
+    const TableTimes times{s_times};
+    FillList list = begin_list(pos0);
     bool overflow = false;
     const int start_lo = static_cast<int>(start), start_hi = static_cast<int>(start >> 32);
     const int nz_lo = static_cast<int>(nz), nz_hi = static_cast<int>(nz >> 32);
+    int carried = 0;  // samples in earlier rounds of the ray that a round begins with
     for (int tb0 = 0; tb0 < t_total; tb0 += kWave) {
         // task i of the wave: the ray lane L whose tasks hold it, and its
         // (i - first task of L)-th chunk holding samples
@@ -1864,20 +1980,32 @@ __global__ __launch_bounds__(kTaskThreads) void fill_cone_rays_kernel(
                               static_cast<uint32_t>(lane_value(nz_lo, L));
         const int l_first = lane_value(t_before, L);
         const int l_limit = lane_value(limit, L);
+        const int64_t r = first + L;
+        uint64_t m = 0ull;
+        int j = 0;
+        if (has_task) {
+            j = nth_set_bit(l_nz, i - l_first);
+            m = masks[static_cast<int64_t>(j) * n_rays + r];
+        }
+        // the ray's samples before the chunk
+        const int count = static_cast<int>(__popcll(m));
+        const int excl = wave_inclusive_sum(count) - count;
+        const int ray_base = lane_value(excl, max(l_first - tb0, 0));
+        const int in_ray = l_first >= tb0 ? excl - ray_base : excl + carried;
+        carried = read_lane(in_ray + count, kWave - 1);
+        if (simple) {
+            queue_chunks(out, lds.list, times, capped_mask(m, in_ray, l_limit),
+                         (static_cast<uint32_t>(L) << kCodeRayShift) | static_cast<uint32_t>(j << kWaveLog2),
+                         tb0 + kWave >= t_total, first, list);
+            continue;
+        }
+        SlotLds& z = lds.slots;
+        const int64_t task = static_cast<int64_t>(j) * n_rays + r;
+        const int base = in_ray;
         const int64_t l_start = (static_cast<int64_t>(lane_value(start_hi, L)) << 32) |
                                 static_cast<uint32_t>(lane_value(start_lo, L));
-        const int64_t r = (static_cast<int64_t>(blockIdx.x) * kTaskWaves + wave) * kFillRays + L;
-        uint64_t m = 0ull;
-        int base = 0;
-        int64_t task = 0;
-        float t_far = -INFINITY;
-        if (has_task) {
-            const int j = nth_set_bit(l_nz, i - l_first);
-            task = static_cast<int64_t>(j) * n_rays + r;
-            m = masks[task];
-            base = chunk_base[task];
-            t_far = t_far_in[r];
-        }
+        const float t_far = has_task ? t_far_in[r] : -INFINITY;
+        const int l_own = lane_value(stored >= kOwnLattice ? 1 : 0, L);
         // segments holding samples that fall before the ray's limit
         uint32_t todo = 0u;
 #pragma unroll
@@ -1894,7 +2022,7 @@ __global__ __launch_bounds__(kTaskThreads) void fill_cone_rays_kernel(
 #pragma unroll
             for (int s = 0; s < kSegsPerChunk; ++s) {
                 if (((todo >> s) & 1u) != 0u) {
-                    q_id[wave][pos] = static_cast<uint16_t>(lane | (s << kWaveLog2));
+                    z.q_id[pos] = static_cast<uint16_t>(lane | (s << kWaveLog2));
                     ++pos;
                 }
             }
@@ -1913,17 +2041,22 @@ __global__ __launch_bounds__(kTaskThreads) void fill_cone_rays_kernel(
             if (k * kWave < total) {
                 const int q = k * kWave + lane;
                 const bool has = q < total;
-                const int id = has ? static_cast<int>(q_id[wave][q]) : 0;
+                const int id = has ? static_cast<int>(z.q_id[q]) : 0;
                 const int src = id & (kWave - 1);
                 const int64_t s_task = (static_cast<int64_t>(lane_value(task_hi, src)) << 32) |
                                        static_cast<uint32_t>(lane_value(task_lo, src));
-                if (has) t_seg[k] = seg_t[s_task * kSegsPerChunk + (id >> kWaveLog2)];
+                const int s_chunk = lane_value(j, src);
+                const bool own = lane_value(l_own, src) != 0;
+                if (has) {
+                    const int s = id >> kWaveLog2;
+                    t_seg[k] = own ? seg_t[s_task * kSegsPerChunk + s] : s_times[s_chunk * kWave + s * kConeBatch];
+                }
             }
         }
         for (int qb = 0; qb < total; qb += kWave) {
             const int q = qb + lane;
             const bool has = q < total;
-            const int id = has ? static_cast<int>(q_id[wave][q]) : 0;
+            const int id = has ? static_cast<int>(z.q_id[q]) : 0;
             const int src = id & (kWave - 1);
             const int s = id >> kWaveLog2;
             const float seg_t0 = t_seg[0];
@@ -1951,28 +2084,28 @@ __global__ __launch_bounds__(kTaskThreads) void fill_cone_rays_kernel(
             const int slot0 = wave_inclusive_sum(n_out) - n_out;
             const int n_slots = read_lane(slot0 + n_out, kWave - 1);
             if (has) {
-                e_pos[wave][lane] = s_start + first;
-                e_slot[wave][lane] = slot0;
-                e_ray[wave][lane] = s_ray;
+                z.e_pos[lane] = s_start + first;
+                z.e_slot[lane] = slot0;
+                z.e_ray[lane] = s_ray;
                 int k = 0;
 #pragma unroll
                 for (int u = 0; u < kConeBatch; ++u) {
                     if (((hits >> u) & 1u) != 0u && k < n_out) {
-                        s_t0[wave][slot0 + k] = tb[u];
-                        s_t1[wave][slot0 + k] = tb[u + 1];
-                        s_entry[wave][slot0 + k] = static_cast<uint8_t>(lane);
+                        z.t0[slot0 + k] = tb[u];
+                        z.entry[slot0 + k] = static_cast<uint8_t>(lane);
                         ++k;
                     }
                 }
             }
             wave_lds_sync();
             for (int k = lane; k < n_slots; k += kWave) {
-                const int e = s_entry[wave][k];
-                const int64_t pos = e_pos[wave][e] + (k - e_slot[wave][e]);
+                const int e = z.entry[k];
+                const float t0 = z.t0[k];
+                const int64_t pos = z.e_pos[e] + (k - z.e_slot[e]);
                 if (pos >= 0 && pos < capacity) {
-                    t_starts[pos] = s_t0[wave][k];
-                    t_ends[pos] = s_t1[wave][k];
-                    ray_indices[pos] = e_ray[wave][e];
+                    t_starts[pos] = t0;
+                    t_ends[pos] = t0 + __builtin_amdgcn_fmed3f(t0 * p.cone, p.dt, p.dt_max);
+                    ray_indices[pos] = z.e_ray[e];
                 } else {
                     overflow = true;
                 }
@@ -1983,8 +2116,7 @@ __global__ __launch_bounds__(kTaskThreads) void fill_cone_rays_kernel(
     if (t_end < INFINITY) {
         // look the rest of the ray up again (rays of more than n_masks
         // chunks of candidates, rare)
-        const int64_t last = static_cast<int64_t>(n_masks - 1) * n_rays + ray;
-        int idx = chunk_base[last] + static_cast<int>(__popcll(masks[last]));
+        int idx = static_cast<int>(stored & ~kOwnLattice);
         const float t_far = t_far_in[ray];
         float t = t_end;
         if (idx < limit) {
@@ -2024,6 +2156,8 @@ __global__ __launch_bounds__(kTaskThreads) void fill_cone_rays_kernel(
         }
     }
     if (overflow && status != nullptr) *status = NACC_ECAPACITY;
+    __syncthreads();
+    if (simple) end_list(out, lds.list, times, first, pos0, list);
 }
 
 template <int LOOKUP, bool SKIP>
@@ -2143,7 +2277,7 @@ struct Layout {
     int64_t sums_bytes;
     int n_masks;
     int64_t chunk_t_off, t_far_off, extra_off;  // cone steps only (0 otherwise)
-    int64_t base_off, seg_t_off;                // cone steps, segment passes
+    int64_t stored_off, seg_t_off;              // cone steps, segment passes
     int64_t holding_off;                        // cone steps, segment passes: chunks holding samples
     int64_t halo_off;                           // halo bits built by the count pass (0: none)
     int64_t bytes;
@@ -2179,14 +2313,14 @@ Layout workspace_layout(int64_t n_rays, const nacc_grid_desc& grid, const nacc_m
     const int64_t split = p.cone > 0.0f ? kRaysPerBlock / cone_rays(n_rays, l.n_masks) : march_split(nb, 1);
     l.sums_bytes = align256((nb * split + scan_scratch_values(nb * split)) * static_cast<int64_t>(sizeof(int64_t)));
     l.bytes = l.sums_bytes + align256(n_rays * l.n_masks * static_cast<int64_t>(sizeof(uint64_t)));
-    l.chunk_t_off = l.t_far_off = l.extra_off = l.base_off = l.seg_t_off = 0;
+    l.chunk_t_off = l.t_far_off = l.extra_off = l.stored_off = l.seg_t_off = 0;
     l.holding_off = 0;
     if (p.cone > 0.0f) {
         l.chunk_t_off = l.bytes;
         l.t_far_off = l.chunk_t_off + align256(n_rays * l.n_masks * static_cast<int64_t>(sizeof(float)));
         l.extra_off = l.t_far_off + align256(n_rays * static_cast<int64_t>(sizeof(float)));
-        l.base_off = l.extra_off + align256(n_rays * static_cast<int64_t>(sizeof(int32_t)));
-        l.seg_t_off = l.base_off + align256(n_rays * l.n_masks * static_cast<int64_t>(sizeof(int32_t)));
+        l.stored_off = l.extra_off + align256(n_rays * static_cast<int64_t>(sizeof(int32_t)));
+        l.seg_t_off = l.stored_off + align256(n_rays * static_cast<int64_t>(sizeof(uint32_t)));
         l.holding_off =
             l.seg_t_off + align256(n_rays * l.n_masks * kSegsPerChunk * static_cast<int64_t>(sizeof(float)));
         l.bytes = l.holding_off + align256(n_rays * static_cast<int64_t>(sizeof(uint64_t)));
@@ -2204,8 +2338,9 @@ struct ConeWork {
     float* chunk_t;       // [n_masks][n_rays]
     float* t_far;         // [n_rays]
     int32_t* extra;       // [n_rays]
-    int32_t* chunk_base;  // [n_masks][n_rays]: samples of the ray before each chunk
-    float* seg_t;         // [n_masks][n_rays][kSegsPerChunk]: t at the start of segments holding samples
+    uint32_t* ray_stored;  // [n_rays]: samples in the stored chunks, and kOwnLattice
+    float* seg_t;         // [n_masks][n_rays][kSegsPerChunk]: t at the start of segments holding
+                          // samples, for rays not on the table
     uint64_t* sample_chunks;  // [n_rays]: bits of the chunks holding samples
     int n_masks;
 };
@@ -2217,7 +2352,7 @@ ConeWork cone_work(void* workspace, const Layout& l) {
     w.chunk_t = reinterpret_cast<float*>(b + l.chunk_t_off);
     w.t_far = reinterpret_cast<float*>(b + l.t_far_off);
     w.extra = reinterpret_cast<int32_t*>(b + l.extra_off);
-    w.chunk_base = reinterpret_cast<int32_t*>(b + l.base_off);
+    w.ray_stored = reinterpret_cast<uint32_t*>(b + l.stored_off);
     w.seg_t = reinterpret_cast<float*>(b + l.seg_t_off);
     w.sample_chunks = reinterpret_cast<uint64_t*>(b + l.holding_off);
     w.n_masks = l.n_masks;
@@ -2280,7 +2415,7 @@ void launch_count_cone(const ConeWork& cw, const uint8_t* skip, const uint32_t* 
         const bool walks = LOOKUP != NACC_LOOKUP_CONTRACT || tab.n == 0;
         hipLaunchKernelGGL((count_cone_kernel<LOOKUP>), dim3(static_cast<unsigned>((n + rays - 1) / rays)),
                            dim3(kTaskThreads), cone_lds(rays, cw.n_masks, walks, LOOKUP == NACC_LOOKUP_CONTRACT).bytes, s, o, d, gid, n, bits, halo,
-                           skip, g, c, p, cw.n_masks, rays, walks ? 1 : 0, packed, sums, cw.masks, cw.chunk_base,
+                           skip, g, c, p, cw.n_masks, rays, walks ? 1 : 0, packed, sums, cw.masks, cw.ray_stored,
                            cw.seg_t, cw.chunk_t, cw.t_far, cw.sample_chunks, tab);
         return;
     }
@@ -2306,6 +2441,14 @@ void launch_count_waves(A&&... a) {
     }
 }
 
+// Rays per wave of the cone fill, fewer for small batches, so that every SIMD
+// has two waves.
+int cone_fill_rays(int64_t n) {
+    int per = kFillRays;
+    while (per > 1 && n < static_cast<int64_t>(per) * 2048) per /= 2;
+    return per;
+}
+
 template <int LOOKUP, bool SKIP>
 void launch_fill_cone(const uint8_t* skip, bool segments, const ConeWork* cw, int64_t nb, hipStream_t s,
                       const float* o, const float* d, const int32_t* gid, int64_t n, const uint32_t* bits,
@@ -2314,11 +2457,13 @@ void launch_fill_cone(const uint8_t* skip, bool segments, const ConeWork* cw, in
     if (cw != nullptr && cw->n_masks > 0 && segments) {
         // the segment count's masks, segment starts and chunks holding
         // samples, ray-major (the ray indices written with the samples)
-        const int64_t per_block = static_cast<int64_t>(kTaskWaves) * kFillRays;
+        const int per = cone_fill_rays(n);
+        const int64_t per_block = static_cast<int64_t>(kTaskWaves) * per;
         const unsigned blocks = static_cast<unsigned>((n + per_block - 1) / per_block);
-        hipLaunchKernelGGL((fill_cone_rays_kernel<LOOKUP>), dim3(blocks), dim3(kTaskThreads), 0, s, o, d, gid, n, bits,
-                           g, p, cw->n_masks, cw->chunk_t, cw->t_far, cw->masks, cw->chunk_base, cw->seg_t,
-                           cw->sample_chunks, packed, capacity, ri, ts, te, status);
+        hipLaunchKernelGGL((fill_cone_rays_kernel<LOOKUP>), dim3(blocks), dim3(kTaskThreads),
+                           cone_fill_lds(cw->n_masks), s, o, d, gid, n, bits, g, p, cw->n_masks, per, cw->chunk_t,
+                           cw->t_far, cw->masks, cw->ray_stored, cw->seg_t, cw->sample_chunks, packed, capacity, ri, ts,
+                           te, status, cone_table(p, cw->n_masks));
         return;
     }
     if (cw != nullptr && cw->n_masks > 0) {  // replay the count pass's chunks, one lane per chunk

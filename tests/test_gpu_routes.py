@@ -298,3 +298,16 @@ def test_cone_starts_past_one_launch():
     mask = synth.random_mask(8 ** 3, 0.05, 24)
     o, d = synth.rays_unbounded(262144 + 33, 68)
     compare(o, d, mask, 8, np.array(synth.CONTRACT_BOX, np.float32), 0.2, 20.0, 0.012, cone=1e-6, lookup=2)
+
+
+@pytest.mark.parametrize("n_rays", [1, 15, 2048, 4097, 8192, 32768])
+@pytest.mark.parametrize("cap", [0, 9, 100])
+def test_cone_fill_rays_per_wave(n_rays, cap):
+    """1 to 16 rays a wave, listed in whole blocks (rays from the near plane)
+    or by segments; rays cut by the cap; more than 64 tasks a wave."""
+    for p_occ in (0.05, 1.0):
+        mask = synth.random_mask(16 ** 3, p_occ, 25)
+        o, d = synth.rays_toward_origin(n_rays, 69)
+        for scale in (0.1, 1.0):
+            compare((o * np.float32(scale)).astype(np.float32), d, mask, 16, BOX, 0.05, 1e10, 0.01, cone=1 / 512,
+                    max_per_ray=cap)
