@@ -147,7 +147,8 @@ const char* nacc_version(void);
  * set them before launching, not concurrently with launches.
  *   march_waves_per_group  wavefronts sharing each group of 64 rays in the
  *                          uniform-step count kernel: 1, 2, 4, 8 or 16 (4;
- *                          more waves suit small batches).
+ *                          more waves suit small batches; the box lookup's
+ *                          count by halo bits always uses 4).
  *   render_cached_chunks   chunks of 64 samples per ray kept in registers
  *                          between the forward and the backward pass: 1..4
  *                          (4).

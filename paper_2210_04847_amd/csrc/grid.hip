@@ -358,7 +358,7 @@ int nacc_grid_build_skip(const uint32_t* bits, const nacc_grid_desc* grid, uint8
         hipLaunchKernelGGL(skip_x_kernel, planes, dim3(kPlaneThreads), 0, s, scratch, c, field);
         st = check_launch("grid skip distance");
         if (st != NACC_OK) return st;
-        launch_halo(bits, grid->res, grid->n_grids, halo, s);
+        launch_halo(bits, grid->res, grid->n_grids, halo, nullptr, s);
         return check_launch("grid skip halo");
     }
     hipLaunchKernelGGL(coarse_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, s, bits, grid->res, grid->n_grids,
@@ -377,7 +377,7 @@ int nacc_grid_build_skip(const uint32_t* bits, const nacc_grid_desc* grid, uint8
         src = dst;
         dst = t;
     }
-    launch_halo(bits, grid->res, grid->n_grids, halo, s);
+    launch_halo(bits, grid->res, grid->n_grids, halo, nullptr, s);
     return check_launch("grid skip halo");
 }
 

@@ -1,6 +1,8 @@
 // Halo bits of a bit-packed occupancy grid (layout in common.h), built by
 // nacc_grid_build_skip into the skip buffer and by the marching count pass
-// into its workspace when the caller passes no skip buffer.
+// into its workspace when the caller passes no skip buffer; and hole bits,
+// the halo of the empty cells (a clear bit: every cell within kHaloReach is
+// occupied), built by the count pass.
 #pragma once
 
 #include "common.h"
@@ -27,12 +29,12 @@ struct __attribute__((packed, aligned(4))) Words4 {
 };
 
 // ORs the bits [z0, z0 + 96) of the fine rows (x, y) for 3 values of x from
-// x0 and kHaloReach rows of y on either side of the block's two; rows are
-// clamped into the grid (a clamped row is one of the others).  WHOLE: every
-// row's four words lie inside the grid.
+// x0 and kHaloReach rows of y on either side of the block's two (`w`), and
+// their complements (`e`); rows are clamped into the grid (a clamped row is
+// one of the others).  WHOLE: every row's four words lie inside the grid.
 template <bool WHOLE>
 __device__ __forceinline__ void or_rows(const uint32_t* __restrict__ fine, uint32_t last, int res, int x0, int cy,
-                                        uint32_t z0, uint32_t w[3]) {
+                                        uint32_t z0, uint32_t w[3], uint32_t e[3]) {
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         const int x = min(max(x0 + i, 0), res - 1);
@@ -49,9 +51,35 @@ __device__ __forceinline__ void or_rows(const uint32_t* __restrict__ fine, uint3
                 for (int j = 0; j < 4; ++j) v.v[j] = fine[min(q + j, last)];
             }
 #pragma unroll
-            for (int j = 0; j < 3; ++j) w[j] |= __builtin_amdgcn_alignbit(v.v[j + 1], v.v[j], a);  // a's low 5 bits
+            for (int j = 0; j < 3; ++j) {
+                const uint32_t row = __builtin_amdgcn_alignbit(v.v[j + 1], v.v[j], a);  // a's low 5 bits
+                w[j] |= row;
+                e[j] |= ~row;
+            }
         }
     }
+}
+
+// The run of halo cells from cz0 on: the rows' pairs of bits folded and spread
+// by one cell either way.  The other lane of the word holds the other half
+// of the rows.
+__device__ __forceinline__ uint32_t halo_run(uint32_t w[3], uint32_t cz0, uint32_t h, uint32_t len) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {  // the other lane's rows (quad permutation 1, 0, 3, 2)
+        w[j] |=
+            static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(w[j]), 0xB1, 0xf, 0xf, false));
+    }
+    // pairs cz0 - 1 .. cz0 + 32 of the row (none before its first cell,
+    // none past its end)
+    uint64_t pairs = static_cast<uint64_t>(even_bits(w[0] | (w[0] >> 1))) |
+                     (static_cast<uint64_t>(even_bits(w[1] | (w[1] >> 1))) << 16) |
+                     (static_cast<uint64_t>(even_bits(w[2] | (w[2] >> 1))) << 32);
+    if (cz0 == 0u) pairs <<= 1;
+    const uint32_t n = h - cz0 + 1u;
+    if (n < 34u) pairs &= (1ull << n) - 1ull;
+    uint32_t run = static_cast<uint32_t>(pairs | (pairs >> 1) | (pairs >> 2));
+    if (len < 32u) run &= (1u << len) - 1u;
+    return run;
 }
 
 // Two lanes per word of the halo bits (32 consecutive cells in C order,
@@ -63,9 +91,11 @@ __device__ __forceinline__ void or_rows(const uint32_t* __restrict__ fine, uint3
 // dwordx4 each and all of a lane's in flight together.
 // Four 128^3 grids: 35.5 us with a lane per cell and early exits, 8.6 us
 // with a lane per word and a load per fine word, 4.5 us so.
+// HALO and HOLES: which of the two to write.
+template <bool HALO, bool HOLES>
 __global__ __launch_bounds__(kHaloThreads) void halo_kernel(const uint32_t* __restrict__ bits, int res, int n_grids,
                                                             uint32_t words, uint32_t out_words,
-                                                            uint32_t* __restrict__ out) {
+                                                            uint32_t* __restrict__ out, uint32_t* __restrict__ holes) {
     const int64_t lane = static_cast<int64_t>(blockIdx.x) * kHaloThreads + threadIdx.x;
     const int64_t id = lane >> 1;
     const int half = static_cast<int>(lane & 1);
@@ -75,7 +105,7 @@ __global__ __launch_bounds__(kHaloThreads) void halo_kernel(const uint32_t* __re
     const uint32_t* fine = bits + grid * words;
     const uint32_t h = static_cast<uint32_t>(res) >> 1;
     const uint32_t cells = h * h * h, last = words - 1u;
-    uint32_t word = 0u;
+    uint32_t word = 0u, hole_word = 0u;
     // every lane takes every step (the two lanes of a word exchange their
     // halves): a step is a run of cells within one row
     uint32_t b = 0u;
@@ -89,42 +119,39 @@ __global__ __launch_bounds__(kHaloThreads) void halo_kernel(const uint32_t* __re
         const int x0 = 2 * cx - kHaloReach + 3 * half;
         const int xl = min(max(x0 + 2, 0), res - 1), yl = min(2 * cy + 1 + kHaloReach, res - 1);
         const uint32_t end = static_cast<uint32_t>(xl * res + yl) * static_cast<uint32_t>(res) + z0;
-        uint32_t w[3] = {0u, 0u, 0u};
+        uint32_t w[3] = {0u, 0u, 0u}, e[3] = {0u, 0u, 0u};
         if (ballot((end >> 5) + 3u > last) == 0ull) {
-            or_rows<true>(fine, last, res, x0, cy, z0, w);
+            or_rows<true>(fine, last, res, x0, cy, z0, w, e);
         } else {
-            or_rows<false>(fine, last, res, x0, cy, z0, w);
+            or_rows<false>(fine, last, res, x0, cy, z0, w, e);
         }
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {  // the other lane's rows (quad permutation 1, 0, 3, 2)
-            w[j] |= static_cast<uint32_t>(
-                __builtin_amdgcn_update_dpp(0, static_cast<int>(w[j]), 0xB1, 0xf, 0xf, false));
-        }
-        // pairs cz0 - 1 .. cz0 + 32 of the row (none before its first cell,
-        // none past its end)
-        uint64_t pairs = static_cast<uint64_t>(even_bits(w[0] | (w[0] >> 1))) |
-                         (static_cast<uint64_t>(even_bits(w[1] | (w[1] >> 1))) << 16) |
-                         (static_cast<uint64_t>(even_bits(w[2] | (w[2] >> 1))) << 32);
-        if (cz0 == 0u) pairs <<= 1;
-        const uint32_t n = h - cz0 + 1u;
-        if (n < 34u) pairs &= (1ull << n) - 1ull;
-        uint32_t run = static_cast<uint32_t>(pairs | (pairs >> 1) | (pairs >> 2));
-        if (len < 32u) run &= (1u << len) - 1u;
+        const uint32_t run = HALO ? halo_run(w, cz0, h, len) : 0u;
+        const uint32_t hole_run = HOLES ? halo_run(e, cz0, h, len) : 0u;
         if (on) {
             word |= run << b;
+            hole_word |= hole_run << b;
             b += len;
         }
     }
-    if (mine && half == 0) out[id] = word;
+    if (mine && half == 0) {
+        if (HALO) out[id] = word;
+        if (HOLES) holes[id] = hole_word;
+    }
 }
 
-// Halo bits of every grid (res % 4 == 0), on stream s.
-inline void launch_halo(const uint32_t* bits, int res, int n_grids, uint32_t* out, hipStream_t s) {
+// Halo bits of every grid (res % 4 == 0) into `out` and hole bits into
+// `holes`, either of them nullptr, on stream s.
+inline void launch_halo(const uint32_t* bits, int res, int n_grids, uint32_t* out, uint32_t* holes, hipStream_t s) {
     const int64_t words = static_cast<int64_t>(res) * res * res / 32;
     const int64_t n = halo_words(res) * n_grids;
-    hipLaunchKernelGGL(halo_kernel, dim3(static_cast<unsigned>((2 * n + kHaloThreads - 1) / kHaloThreads)),
-                       dim3(kHaloThreads), 0, s, bits, res, n_grids, static_cast<uint32_t>(words),
-                       static_cast<uint32_t>(halo_words(res)), out);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((2 * n + kHaloThreads - 1) / kHaloThreads)),
+                           dim3(kHaloThreads), 0, s, bits, res, n_grids, static_cast<uint32_t>(words),
+                           static_cast<uint32_t>(halo_words(res)), out, holes);
+    };
+    if (holes == nullptr) launch(halo_kernel<true, false>);
+    else if (out == nullptr) launch(halo_kernel<false, true>);
+    else launch(halo_kernel<true, true>);
 }
 
 }  // namespace

@@ -263,13 +263,14 @@ __device__ __forceinline__ RaySpan read_span(const RaySpan& s, int lane) {
 }
 
 // ---------------------------------------------------------------------------
-// Uniform steps through the box lookup with the halo bits of the skip
-// buffer.  A ray's candidates are grouped into segments of G consecutive
-// ones (segment j: candidates [j G, j G + G)); a wave tests 64 segments at
-// once, one halo bit each at the segment's centre, and then looks up one by
-// one only the candidates of the segments whose bit is set, 64 at a time
-// (64 / G segments per iteration, in segment order, so the ballots still
-// list the samples in t order).
+// Uniform steps through the box lookup with halo bits.  A ray's candidates are
+// grouped into segments of G consecutive ones (segment j: candidates [j G,
+// j G + G)); one halo bit each is tested at the segment's centre, and only
+// the candidates of the segments whose bit is set are looked up.  The count
+// pass tests the segments of many rays at once (march.hip); fused inference
+// tests 64 of one ray and then looks up 64 candidates at a time (64 / G
+// segments per iteration, in segment order, so the ballots list the samples
+// in t order).
 //
 // A clear bit proves its segment empty.  The segment's midpoints lie within
 // (G/2) dt of its centre in t, so their fine-cell coordinates
@@ -316,17 +317,29 @@ __device__ __forceinline__ SegRay read_seg(int seg_logs, const RaySpan& span, co
     return SegRay{read_lane(seg_logs, lane), span.grid * g.halo_words};
 }
 
-// Halo bit of the cell holding point x (the box lookup's clamped cell
+// Index of the halo cell holding point x (the box lookup's clamped cell
 // coordinates, halved).
-__device__ __forceinline__ bool halo_bit(__amdgpu_buffer_rsrc_t rs, const GridK& g, uint32_t halo0, float x0,
-                                         float x1, float x2) {
+__device__ __forceinline__ uint32_t halo_cell(const GridK& g, float x0, float x1, float x2) {
     const uint32_t j0 = static_cast<uint32_t>(static_cast<int>(clamp_cell((x0 - g.lo[0]) * g.s[0], g.top)));
     const uint32_t j1 = static_cast<uint32_t>(static_cast<int>(clamp_cell((x1 - g.lo[1]) * g.s[1], g.top)));
     const uint32_t j2 = static_cast<uint32_t>(static_cast<int>(clamp_cell((x2 - g.lo[2]) * g.s[2], g.top)));
-    const uint32_t cell =
-        __umul24(j0 >> 1, g.halo_res2) + (__umul24(j1 >> 1, static_cast<uint32_t>(g.halo_res)) + (j2 >> 1));
+    return __umul24(j0 >> 1, g.halo_res2) + (__umul24(j1 >> 1, static_cast<uint32_t>(g.halo_res)) + (j2 >> 1));
+}
+
+// Its halo (or hole) bit.
+__device__ __forceinline__ bool halo_bit(__amdgpu_buffer_rsrc_t rs, uint32_t halo0, uint32_t cell) {
     const uint32_t w = __builtin_amdgcn_raw_buffer_load_b32(rs, (halo0 + (cell >> 5)) << 2, 0, 0);
     return ((w >> (cell & 31u)) & 1u) != 0u;
+}
+
+__device__ __forceinline__ bool halo_bit(__amdgpu_buffer_rsrc_t rs, const GridK& g, uint32_t halo0, float x0,
+                                         float x1, float x2) {
+    return halo_bit(rs, halo0, halo_cell(g, x0, x1, x2));
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t halo_rsrc(const uint32_t* halo, const GridK& g) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(halo), 0, static_cast<int>(g.halo_bytes),
+                                             kBufferWord3);
 }
 
 // Live-segment ballot of block b of a ray's segments (segment j = b 64 +
@@ -343,12 +356,10 @@ __device__ __forceinline__ uint64_t live_segments(const RaySpan& span, const uin
     const bool valid = k_first < kMaxCandidates && span.t_near + static_cast<float>(k_first) * p.dt < span.t_far;
     vm = ballot(valid);
     if (vm == 0ull) return 0ull;
-    const __amdgpu_buffer_rsrc_t hrs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint32_t*>(halo), 0, static_cast<int>(g.halo_bytes), kBufferWord3);
     const float tc = span.t_near + static_cast<float>(k_first + (1 << (log_g - 1))) * p.dt;
-    const bool hb = halo_bit(hrs, g, sg.halo0, span.o[0] + span.d[0] * tc, span.o[1] + span.d[1] * tc,
-                             span.o[2] + span.d[2] * tc);
-    return vm & ballot(hb);
+    const uint32_t cell =
+        halo_cell(g, span.o[0] + span.d[0] * tc, span.o[1] + span.d[1] * tc, span.o[2] + span.d[2] * tc);
+    return vm & ballot(halo_bit(halo_rsrc(halo, g), sg.halo0, cell));
 }
 
 int validate(const float* rays_o, const float* rays_d, int64_t n_rays, const uint32_t* bits,

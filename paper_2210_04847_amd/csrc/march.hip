@@ -336,104 +336,13 @@ __device__ __forceinline__ int march_ray_uniform(
     return count;
 }
 
-// Count pass of one ray by segments (whole wave): looks up every candidate
-// of the live segments, 64 at a time.  The occupancy ballots are turned
-// back into the plain traversal's chunk masks (chunk j: candidates
-// [64 j, 64 j + 64)), so the fill pass replays them exactly as it does for
-// the plain traversal: each segment's G bits lie inside one chunk (G
-// divides 64, segments are aligned to G), and the first lane of each
-// segment ORs them into that chunk's mask in this wave's LDS slice
-// (`chunk_masks`, 64 entries; chunks from n_masks on are not stored and the
-// fill traverses them again).  `list` is this wave's 64-byte LDS slice for
-// a block's live segments.  Returns the ray's count.
-__device__ __forceinline__ int count_ray_segments(const RaySpan& span, const uint32_t* __restrict__ bits,
-                                                  const uint32_t* __restrict__ halo, const GridK& g,
-                                                  const StepK& p, const SegRay& sg, uint8_t* list,
-                                                  uint64_t* chunk_masks, uint64_t* __restrict__ masks,
-                                                  int n_masks) {
-    const int lane = lane_id();
-    const int log_g = sg.log_g;
-    const int gmask = (1 << log_g) - 1;
-    const int per_iter = kWave >> log_g;  // segments per wave iteration
-    const uint64_t field = (1ull << (1 << log_g)) - 1ull;
-    chunk_masks[lane] = 0ull;
-    int count = 0;
-    bool done = false;
-    for (int b = 0; !done; ++b) {
-        uint64_t vm;
-        const uint64_t lm = live_segments(span, halo, g, p, sg, b, vm);
-        if (vm == 0ull) break;  // t at a segment's first candidate is non-decreasing in j
-        if (((lm >> lane) & 1ull) != 0ull) list[bits_below(lm)] = static_cast<uint8_t>(lane);
-        wave_lds_sync();
-        const int n_live = static_cast<int>(__popcll(lm));
-        // two chunks per iteration, both chunks' grid words in flight before
-        // either is tested (a chunk past the live segments looks up clamped
-        // cells and counts nothing)
-        for (int q = 0; q < n_live && !done; q += 2 * per_iter) {
-            int k[2];
-            float t0[2], t1[2];
-            uint64_t alive[2], m[2];
-            Probe pq[2];
-            uint32_t w[2];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int slot = q + u * per_iter + (lane >> log_g);
-                const bool in = slot < n_live;
-                const int seg = in ? static_cast<int>(list[slot]) : 0;
-                k[u] = ((b * kWave + seg) << log_g) + (lane & gmask);
-                t0[u] = span.t_near + static_cast<float>(k[u]) * p.dt;
-                t1[u] = span.t_near + static_cast<float>(k[u] + 1) * p.dt;
-                alive[u] = ballot(in && t0[u] < span.t_far);
-            }
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const float tm = (t0[u] + t1[u]) * 0.5f;
-                pq[u] = probe<NACC_LOOKUP_AABB>(g, span.word0, span.o[0] + span.d[0] * tm,
-                                                span.o[1] + span.d[1] * tm, span.o[2] + span.d[2] * tm);
-            }
-#pragma unroll
-            for (int u = 0; u < 2; ++u) w[u] = grid_word(grid_rsrc(bits, g), pq[u].word);
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                m[u] = alive[u] & ballot(((w[u] >> pq[u].bit) & 1u) != 0u);
-                if ((lane & gmask) == 0 && (k[u] >> kWaveLog2) < n_masks) {
-                    const uint64_t part = (m[u] >> lane) & field;  // this segment's hits
-                    if (part != 0ull) {
-                        __hip_atomic_fetch_or(chunk_masks + (k[u] >> kWaveLog2), part << (k[u] & (kWave - 1)),
-                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-                    }
-                }
-            }
-            count += static_cast<int>(__popcll(m[0])) + static_cast<int>(__popcll(m[1]));
-            if (p.max_per_ray > 0 && count >= p.max_per_ray) {
-                count = p.max_per_ray;
-                done = true;
-            }
-        }
-        if (vm != ~0ull) break;  // the ray's segments end in this block
-        wave_lds_sync();         // the list is written again by the next block
-    }
-    wave_lds_sync();
-    if (masks != nullptr && lane < n_masks) masks[lane] = chunk_masks[lane];
-    wave_lds_sync();  // read before the next ray clears them
-    return count;
-}
-
-// The box lookup with a skip buffer marches by segments (its halo bits).
-template <int LOOKUP, bool SKIP>
-constexpr bool kSegments = LOOKUP == NACC_LOOKUP_AABB && SKIP;
-
 template <int LOOKUP, bool SKIP, int WAVES>
 __global__ __launch_bounds__(WAVES * kWave) void count_uniform_kernel(
     const float* __restrict__ rays_o, const float* __restrict__ rays_d,
     const int32_t* __restrict__ grid_id, int64_t n_rays, const uint32_t* __restrict__ bits,
-    const uint8_t* __restrict__ skip, const uint32_t* __restrict__ halo, GridK g, ClipK c, StepK p,
-    int32_t* __restrict__ packed_info, int64_t* __restrict__ block_sums, uint64_t* __restrict__ masks, int n_masks,
-    int split) {
+    const uint8_t* __restrict__ skip, GridK g, ClipK c, StepK p, int32_t* __restrict__ packed_info,
+    int64_t* __restrict__ block_sums, uint64_t* __restrict__ masks, int n_masks, int split) {
     __shared__ int64_t wave_total[WAVES];
-    // segments: each wave's chunk masks, then its list of live segments
-    __shared__ uint64_t seg_masks[kSegments<LOOKUP, SKIP> ? WAVES * kWave : 1];
-    __shared__ uint8_t seg_lists[kSegments<LOOKUP, SKIP> ? WAVES * kWave : 1];
     const int wave = uniform<int>(static_cast<int>(threadIdx.x) / kWave);
     // workgroup b takes part b % split of the group of kRaysPerBlock rays
     // b / split: per = kRaysPerBlock / split rays from `first`; its samples
@@ -447,7 +356,6 @@ __global__ __launch_bounds__(WAVES * kWave) void count_uniform_kernel(
     if (wave + lane_id() * WAVES < per && mine < n_rays) {
         spans = ray_span<LOOKUP>(mine, rays_o, rays_d, grid_id, g, c, p);
     }
-    const int seg_logs = kSegments<LOOKUP, SKIP> ? seg_log(g, spans, p) : 0;
     int64_t total = 0;
     bool unused = false;
     for (int i = wave; i < per; i += WAVES) {
@@ -456,21 +364,9 @@ __global__ __launch_bounds__(WAVES * kWave) void count_uniform_kernel(
         const RaySpan span = read_span(spans, i / WAVES);
         uint64_t* ray_masks = masks != nullptr ? masks + r * n_masks : nullptr;
         const int ray_n_masks = masks != nullptr ? n_masks : 0;
-        int n;
-        if constexpr (kSegments<LOOKUP, SKIP>) {
-            const SegRay sg = read_seg(seg_logs, span, g, i / WAVES);
-            if (sg.log_g != 0) {
-                n = count_ray_segments(span, bits, halo, g, p, sg, seg_lists + wave * kWave,
-                                       seg_masks + wave * kWave, ray_masks, ray_n_masks);
-            } else {
-                n = march_ray_uniform<LOOKUP, false, false>(r, span, rays_o, rays_d, bits, skip, g, p, 0, 0, 0,
-                                                            nullptr, nullptr, nullptr, unused, ray_masks,
-                                                            ray_n_masks);
-            }
-        } else {
-            n = march_ray_uniform<LOOKUP, false, SKIP>(r, span, rays_o, rays_d, bits, skip, g, p, 0, 0, 0, nullptr,
-                                                       nullptr, nullptr, unused, ray_masks, ray_n_masks);
-        }
+        const int n = march_ray_uniform<LOOKUP, false, SKIP>(r, span, rays_o, rays_d, bits, skip, g, p, 0, 0, 0,
+                                                             nullptr, nullptr, nullptr, unused, ray_masks,
+                                                             ray_n_masks);
         if (lane_id() == 0) packed_info[2 * r + 1] = n;
         total += n;
     }
@@ -1526,7 +1422,7 @@ __device__ __forceinline__ Cells cells_within(__amdgpu_buffer_rsrc_t grs, const 
 }
 
 // The LDS of the segment count for `rays` rays a workgroup.
-constexpr int kConeRaysMax = kRaysPerBlock;
+constexpr int kSegmentRaysMax = kRaysPerBlock;
 constexpr int kConeRayFloats = 20;  // 16-byte fields, 16 different ones in different banks
 constexpr int kChunkQueue = kWave + kSegsPerChunk;
 constexpr int kSegStack = 2 * kWave;
@@ -1538,11 +1434,11 @@ constexpr int kSegLevelShift = 18;
 struct ConeLds {
     int tab, masks, starts, seg_t, seg_id, near_t, near_end, near_id, chunks, bytes;  // byte offsets, after the rays
 };
-__host__ __device__ inline int cone_mask_stride(int n_masks) { return (n_masks | 1) * 8; }  // bytes a ray
+__host__ __device__ inline int mask_row_bytes(int n_masks) { return (n_masks | 1) * 8; }  // bytes a ray
 __host__ __device__ inline ConeLds cone_lds(int rays, int n_masks, bool walks, bool ranges) {
     ConeLds l;
     l.masks = rays * kConeRayFloats * 4;
-    l.tab = l.masks + rays * cone_mask_stride(n_masks);
+    l.tab = l.masks + rays * mask_row_bytes(n_masks);
     l.starts = l.tab + (n_masks * kTableStride + 1) * 4;
     l.seg_t = l.starts + (walks ? rays * (n_masks + 1) * 4 : 0);
     l.seg_id = l.seg_t + kTaskWaves * kSegStack * 4;
@@ -1596,7 +1492,7 @@ __global__ __launch_bounds__(kTaskThreads) void count_cone_kernel(
     char* const lds = reinterpret_cast<char*>(lds4);
     constexpr bool kRanges = LOOKUP == NACC_LOOKUP_CONTRACT;
     const ConeLds l = cone_lds(rays, n_masks, walks != 0, kRanges);
-    const int stride = cone_mask_stride(n_masks);
+    const int stride = mask_row_bytes(n_masks);
     float* const s_tab = reinterpret_cast<float*>(lds + l.tab);
     float* const s_starts = reinterpret_cast<float*>(lds + l.starts);
     const int lane = lane_id();
@@ -1856,6 +1752,191 @@ __global__ __launch_bounds__(kTaskThreads) void count_cone_kernel(
     }
     const int sum = wave_sum(n);  // <= 64 * 2^24 fits int32
     if (lane == 0) block_sums[blockIdx.x] = sum;
+}
+
+// Count pass of uniform steps through the box with halo bits.  A workgroup
+// takes `rays` consecutive rays, a quarter of them a wave.  A wave's segments
+// (of G candidates, the smallest its rays allow), ray after ray, are tested
+// 64 at a time, one per lane: a clear halo bit leaves a segment out, a clear
+// hole bit (holes may be nullptr) makes all its candidates samples, and what
+// is left goes on a stack in LDS, from which 64 eighths of eight candidates
+// each are looked up at a time, one per lane, the eight grid words in flight
+// together.  All lanes work whatever the lengths of the rays and the share
+// of segments left.  The hits make the rays' chunk masks in LDS, from which
+// they are counted and stored.  Rays of more candidates than stored chunks
+// are taken in windows of as many, the masks of the first one stored; rays
+// too fast for segments (seg_log 0) look every candidate up.
+// Bound by VALU issue (85% of the cycles): 262,144 rays, 37 segments of 16
+// inside a ray, 21 near occupied cells: 138 us and 5 us for the hole bits,
+// 162 us without them (small blobs; a solid ball of 64 cells across gains
+// more), 208 us with a wave per ray after ray, half of whose lanes tested no
+// segment and a fifth looked no candidate up.
+constexpr int kBoxRayFloats = 12;  // 16-byte fields, 16 different ones in different banks
+
+__host__ __device__ inline int box_lds(int rays, int n_masks) {
+    return rays * (kBoxRayFloats * 4 + mask_row_bytes(n_masks)) + kTaskWaves * kSegStack * 4;
+}
+
+__global__ __launch_bounds__(kTaskThreads) void count_box_kernel(
+    const float* __restrict__ rays_o, const float* __restrict__ rays_d, const int32_t* __restrict__ grid_id,
+    int64_t n_rays, const uint32_t* __restrict__ bits, const uint32_t* __restrict__ halo,
+    const uint32_t* __restrict__ holes, GridK g, ClipK c, StepK p, int n_masks, int rays,
+    int32_t* __restrict__ packed_info, int64_t* __restrict__ block_sums, uint64_t* __restrict__ masks) {
+    extern __shared__ float4 lds4[];
+    __shared__ int wave_total[kTaskWaves];
+    const int stride = mask_row_bytes(n_masks);
+    char* const s_masks = reinterpret_cast<char*>(lds4) + rays * kBoxRayFloats * 4;
+    const int lane = lane_id();
+    const int wave = uniform<int>(static_cast<int>(threadIdx.x) / kWave);
+    uint32_t* const q = reinterpret_cast<uint32_t*>(s_masks + rays * stride) + wave * kSegStack;
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * rays;
+    if (static_cast<int>(threadIdx.x) < rays) {  // in the first wave
+        const int64_t r = first + threadIdx.x;
+        RaySpan span{};
+        if (r < n_rays) span = ray_span<NACC_LOOKUP_AABB>(r, rays_o, rays_d, grid_id, g, c, p);
+        float4* const ray = lds4 + threadIdx.x * (kBoxRayFloats / 4);
+        ray[0] = make_float4(span.o[0], span.o[1], span.o[2], span.t_near);
+        ray[1] = make_float4(span.d[0], span.d[1], span.d[2], span.valid ? span.t_far : -INFINITY);
+        ray[2] = make_float4(__uint_as_float(span.word0), __uint_as_float(span.grid * g.halo_words),
+                             __int_as_float(span.valid ? seg_log(g, span, p) : 0), 0.0f);
+    }
+    __syncthreads();
+    const int per = rays / kTaskWaves;  // the wave's rays, from ray0 on
+    const int ray0 = wave * per;
+    float t_near = 0.0f, t_far = -INFINITY;
+    int own_log = 0;
+    if (lane < per) {  // lane i: ray ray0 + i
+        const float4* const ray = lds4 + (ray0 + lane) * (kBoxRayFloats / 4);
+        t_near = ray[0].w;
+        t_far = ray[1].w;
+        own_log = __float_as_int(ray[2].z);
+    }
+    int log_g = 5;
+    for (; log_g > kMinSegmentLog2 && ballot(own_log != 0 && own_log < log_g) != 0ull; --log_g) {
+    }
+    const int part_log = log_g - 3;  // eighths of a segment
+    const int per_round = kWave >> part_log;
+    // candidates of the ray, at most (the last t below t_far, with the
+    // roundings of t and of this bound)
+    const float bound = (((t_far - t_near) + (fabsf(t_far) + fabsf(t_near)) * 0x1p-22f) / p.dt) * (1.0f + 0x1p-20f) + 2.0f;
+    const int k_end = !(t_near < t_far) ? 0
+                      : bound < static_cast<float>(kMaxCandidates) ? static_cast<int>(bound)
+                                                                   : kMaxCandidates;
+    const __amdgpu_buffer_rsrc_t grs = grid_rsrc(bits, g), hrs = halo_rsrc(halo, g), ors = halo_rsrc(holes, g);
+    const int window = n_masks * kWave;
+    const uint32_t inv = 65536u / static_cast<uint32_t>(n_masks) + 1u;  // i / n_masks, i < 1,024
+    const int64_t wave_first = first + ray0;
+    const int n_mine = static_cast<int>(max(min(static_cast<int64_t>(per), n_rays - wave_first), int64_t{0}));
+    int count = 0;
+    for (int kb = 0; kb < kMaxCandidates; kb += window) {
+        for (int i = lane; i < per * (stride / 8); i += kWave) {
+            reinterpret_cast<uint64_t*>(s_masks + ray0 * stride)[i] = 0ull;
+        }
+        const int n_segs = (min(max(k_end - kb, 0), window) + (1 << log_g) - 1) >> log_g;
+        const int before = wave_inclusive_sum(n_segs) - n_segs;
+        const int total = read_lane(before + n_segs, kWave - 1);
+        wave_lds_sync();
+        int f0 = 0, n_q = 0;  // segments tested; entries of the stack
+        for (;;) {
+            if (n_q >= per_round || (n_q > 0 && f0 >= total)) {
+                // look up 64 runs of eight candidates
+                const int n = min(n_q, per_round);
+                n_q -= n;
+                const int e = lane >> part_log;
+                const bool has = e < n;
+                const uint32_t id = q[n_q + (has ? e : 0)];
+                const int rl = static_cast<int>(id >> 16);
+                const int byte = static_cast<int>(id & 0xffffu) + (lane & ((1 << part_log) - 1));
+                const float4* const ray = lds4 + rl * (kBoxRayFloats / 4);
+                const float4 a = ray[0], b = ray[1], w4 = ray[2];
+                const float k0 = static_cast<float>(kb + byte * kConeBatch);
+                const uint32_t word0 = __float_as_uint(w4.x);
+                float t[kConeBatch + 1];
+#pragma unroll
+                for (int u = 0; u <= kConeBatch; ++u) t[u] = a.w + (k0 + static_cast<float>(u)) * p.dt;
+                uint32_t cell[kConeBatch], w[kConeBatch];
+#pragma unroll
+                for (int u = 0; u < kConeBatch; ++u) {
+                    const float tm = (t[u] + t[u + 1]) * 0.5f;
+                    const float x0 = a.x + b.x * tm, x1 = a.y + b.y * tm, x2 = a.z + b.z * tm;
+                    cell[u] =
+                        cell_index(g, (x0 - g.lo[0]) * g.s[0], (x1 - g.lo[1]) * g.s[1], (x2 - g.lo[2]) * g.s[2]);
+                    w[u] = grid_word(grs, word0 + (cell[u] >> 5));
+                }
+                uint32_t hits = 0u;
+#pragma unroll
+                for (int u = 0; u < kConeBatch; ++u) {
+                    const uint32_t bit = __builtin_amdgcn_ubfe(w[u], cell[u] & 31u, 1u);
+                    hits |= (t[u] < b.w ? bit : 0u) << u;
+                }
+                if (has && hits != 0u) s_masks[rl * stride + byte] = static_cast<char>(hits);
+            } else if (f0 < total) {
+                // test 64 segments: segment f of the wave, the s-th of ray L
+                const int f = f0 + lane;
+                f0 += kWave;
+                int L = 0;
+#pragma unroll
+                for (int step = kSegmentRaysMax / kTaskWaves / 2; step >= 1; step >>= 1) {
+                    if (lane_value(before, L + step) <= f) L += step;
+                }
+                const int s = f - lane_value(before, L);
+                const int rl = ray0 + min(L, per - 1);
+                const int k = kb + (s << log_g);
+                const float4* const ray = lds4 + rl * (kBoxRayFloats / 4);
+                const float4 a = ray[0], b = ray[1], w4 = ray[2];
+                const bool valid = f < total && a.w + static_cast<float>(k) * p.dt < b.w;
+                const float tc = a.w + static_cast<float>(k + (1 << (log_g - 1))) * p.dt;
+                const uint32_t halo0 = __float_as_uint(w4.y);
+                const uint32_t cell = halo_cell(g, a.x + b.x * tc, a.y + b.y * tc, a.z + b.z * tc);
+                const bool open = __float_as_int(w4.z) == 0;
+                bool full = false;
+                if (holes != nullptr) {
+                    const bool hole = halo_bit(ors, halo0, cell);
+                    full = !hole && a.w + static_cast<float>(k + (1 << log_g) - 1) * p.dt < b.w;
+                }
+                bool left = valid && (open | halo_bit(hrs, halo0, cell));
+                full = left && full && !open;
+                left = left && !full;
+                const uint32_t byte = static_cast<uint32_t>(k - kb) >> 3;
+                char* const at = s_masks + rl * stride + byte;
+                if (full) {
+                    if (log_g == 3) *reinterpret_cast<uint8_t*>(at) = 0xffu;
+                    else if (log_g == 4) *reinterpret_cast<uint16_t*>(at) = 0xffffu;
+                    else *reinterpret_cast<uint32_t*>(at) = ~0u;
+                }
+                const uint64_t m = ballot(left);
+                if (left) q[n_q + bits_below(m)] = (static_cast<uint32_t>(rl) << 16) | byte;
+                n_q += static_cast<int>(__popcll(m));
+            } else {
+                break;
+            }
+            wave_lds_sync();
+        }
+        if (lane < per) {
+            const uint64_t* const mm = reinterpret_cast<const uint64_t*>(s_masks + (ray0 + lane) * stride);
+#pragma unroll 4
+            for (int j = 0; j < n_masks; ++j) count += static_cast<int>(__popcll(mm[j]));
+        }
+        if (kb == 0) {
+            for (int i = lane; i < n_mine * n_masks; i += kWave) {
+                const int rl = static_cast<int>((static_cast<uint32_t>(i) * inv) >> 16);
+                masks[wave_first * n_masks + i] = *reinterpret_cast<const uint64_t*>(
+                    s_masks + (ray0 + rl) * stride + (i - rl * n_masks) * 8);
+            }
+        }
+        if (ballot(k_end > kb + window && !(p.max_per_ray > 0 && count >= p.max_per_ray)) == 0ull) break;
+        wave_lds_sync();
+    }
+    if (p.max_per_ray > 0) count = min(count, p.max_per_ray);
+    if (lane < n_mine) packed_info[2 * (wave_first + lane) + 1] = count;
+    const int sum = wave_sum(count);  // <= 16 * 2^24 fits int32
+    if (lane == 0) wave_total[wave] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int64_t s = 0;
+        for (int w = 0; w < kTaskWaves; ++w) s += wave_total[w];
+        block_sums[blockIdx.x] = s;
+    }
 }
 
 // Fill pass of the segment count.  A wave takes up to kFillRays consecutive
@@ -2256,12 +2337,13 @@ int march_split(int64_t groups, int waves) {
     return split;
 }
 
-// Rays per workgroup of the segment count: 64, or 32 where their masks
+// Rays per workgroup of the counts by segments: 64, or 32 where their masks
 // would leave too few workgroups to a CU (contraction, 600,000 rays of 40
-// chunks: 611 us a call with 64), and fewer for small batches, so that every
-// CU has eight workgroups.
-int cone_rays(int64_t n_rays, int n_masks) {
-    int rays = n_masks > 24 ? 32 : kConeRaysMax;
+// chunks: 611 us a call with 64, 584 with 32; 15 chunks, 262,144 rays: the
+// count 130 us with 64, 137 with 32, 160 with 16), and fewer for small
+// batches, so that every CU has eight workgroups.
+int segment_rays(int64_t n_rays, int n_masks) {
+    int rays = n_masks > 24 ? 32 : kSegmentRaysMax;
     while (rays > kTaskWaves && n_rays < static_cast<int64_t>(rays) * 2048) rays /= 2;
     return rays;
 }
@@ -2279,7 +2361,7 @@ struct Layout {
     int64_t chunk_t_off, t_far_off, extra_off;  // cone steps only (0 otherwise)
     int64_t stored_off, seg_t_off;              // cone steps, segment passes
     int64_t holding_off;                        // cone steps, segment passes: chunks holding samples
-    int64_t halo_off;                           // halo bits built by the count pass (0: none)
+    int64_t halo_off, holes_off;                // halo and hole bits built by the count pass (0: none)
     int64_t bytes;
 };
 
@@ -2287,13 +2369,15 @@ int64_t align256(int64_t b) { return ((b + 255) / 256) * 256; }
 
 // Whether a count pass without a skip buffer builds halo bits of its own
 // (halo.h, 4.5 us up to a few 128^3 grids, 23 us for 64 of them) in the
-// workspace, so as to look up only the candidates near occupied cells.
-// Uniform steps through the box gain 0.3 ns a ray (128^3: 110 -> 106 us a
-// call at 32,768 rays, 317 -> 243 us at 262,144; even at 16,384, 64 grids
-// even near 200,000).  Cone steps gain from the smallest batches on (they
-// also lose a separate expansion of the ray indices; cascades 94 -> 55 us at
-// 256 rays, 434 -> 175 us at 262,144; contraction 135 -> 63 and 1,281 ->
-// 258 us) unless a few rays are spread over many grids.
+// workspace, so as to look up only the candidates near occupied cells; and
+// whether uniform steps through the box build hole bits (5 us), with a skip
+// buffer too.  Uniform steps gain from about 16,384 rays on (128^3, a ball:
+// 109 -> 68 us a call at 32,768 rays, 482 -> 273 us at 262,144; even at
+// 16,384; cells occupied at random: 105 -> 87 and 330 -> 319 us).  Cone steps
+// gain from the smallest batches on (they also lose a separate expansion of
+// the ray indices; cascades 94 -> 55 us at 256 rays, 434 -> 175 us at
+// 262,144; contraction 135 -> 63 and 1,281 -> 258 us) unless a few rays are
+// spread over many grids.
 bool builds_halo(int64_t n_rays, int n_masks, const nacc_grid_desc& grid, const nacc_march_params& p) {
     if (n_masks == 0) return false;
     const int64_t words = halo_words(grid.res) * grid.n_grids;
@@ -2310,7 +2394,7 @@ Layout workspace_layout(int64_t n_rays, const nacc_grid_desc& grid, const nacc_m
         const int64_t k = candidate_bound(grid, p, int64_t{kMaxMaskChunks} * kWave);
         l.n_masks = static_cast<int>((k + kWave - 1) / kWave);
     }
-    const int64_t split = p.cone > 0.0f ? kRaysPerBlock / cone_rays(n_rays, l.n_masks) : march_split(nb, 1);
+    const int64_t split = std::max<int64_t>(kRaysPerBlock / segment_rays(n_rays, l.n_masks), march_split(nb, 1));
     l.sums_bytes = align256((nb * split + scan_scratch_values(nb * split)) * static_cast<int64_t>(sizeof(int64_t)));
     l.bytes = l.sums_bytes + align256(n_rays * l.n_masks * static_cast<int64_t>(sizeof(uint64_t)));
     l.chunk_t_off = l.t_far_off = l.extra_off = l.stored_off = l.seg_t_off = 0;
@@ -2325,10 +2409,14 @@ Layout workspace_layout(int64_t n_rays, const nacc_grid_desc& grid, const nacc_m
             l.seg_t_off + align256(n_rays * l.n_masks * kSegsPerChunk * static_cast<int64_t>(sizeof(float)));
         l.bytes = l.holding_off + align256(n_rays * static_cast<int64_t>(sizeof(uint64_t)));
     }
-    l.halo_off = 0;
+    l.halo_off = l.holes_off = 0;
     if (builds_halo(n_rays, l.n_masks, grid, p)) {
         l.halo_off = l.bytes;
         l.bytes += align256(halo_words(grid.res) * 4 * grid.n_grids);
+        if (p.cone == 0.0f) {
+            l.holes_off = l.bytes;
+            l.bytes += align256(halo_words(grid.res) * 4 * grid.n_grids);
+        }
     }
     return l;
 }
@@ -2359,9 +2447,6 @@ ConeWork cone_work(void* workspace, const Layout& l) {
     return w;
 }
 
-// Whether a cone-stepped call marches by segments (halo bits given).
-bool cone_segments(const ConeWork& cw, const uint32_t* halo) { return cw.n_masks > 0 && halo != nullptr; }
-
 // Halo bits of a skip buffer (see halo_offset).
 const uint32_t* halo_of(const uint8_t* skip, const GridK& g) {
     return skip == nullptr ? nullptr
@@ -2369,13 +2454,13 @@ const uint32_t* halo_of(const uint8_t* skip, const GridK& g) {
 }
 
 template <int LOOKUP, bool SKIP, int WAVES>
-void launch_count_uniform(const uint8_t* skip, const uint32_t* halo, int64_t nb, hipStream_t s, const float* o,
+void launch_count_uniform(const uint8_t* skip, int64_t nb, hipStream_t s, const float* o,
                           const float* d, const int32_t* gid, int64_t n, const uint32_t* bits, const GridK& g,
                           const ClipK& c, const StepK& p, int32_t* packed, int64_t* sums, uint64_t* masks,
                           int n_masks) {
     const int split = march_split(nb, WAVES);
     hipLaunchKernelGGL((count_uniform_kernel<LOOKUP, SKIP, WAVES>), dim3(static_cast<unsigned>(nb * split)),
-                       dim3(WAVES * kWave), 0, s, o, d, gid, n, bits, skip, halo, g, c, p, packed, sums, masks,
+                       dim3(WAVES * kWave), 0, s, o, d, gid, n, bits, skip, g, c, p, packed, sums, masks,
                        n_masks, split);
 }
 
@@ -2410,8 +2495,8 @@ void launch_count_cone(const ConeWork& cw, const uint8_t* skip, const uint32_t* 
                        const GridK& g, const ClipK& c, const StepK& p, int32_t* packed, int64_t* sums, uint64_t*,
                        int) {
     const ConeTable tab = cone_table(p, cw.n_masks);
-    if (cone_segments(cw, halo)) {
-        const int rays = cone_rays(n, cw.n_masks);
+    if (halo != nullptr) {
+        const int rays = segment_rays(n, cw.n_masks);
         const bool walks = LOOKUP != NACC_LOOKUP_CONTRACT || tab.n == 0;
         hipLaunchKernelGGL((count_cone_kernel<LOOKUP>), dim3(static_cast<unsigned>((n + rays - 1) / rays)),
                            dim3(kTaskThreads), cone_lds(rays, cw.n_masks, walks, LOOKUP == NACC_LOOKUP_CONTRACT).bytes, s, o, d, gid, n, bits, halo,
@@ -2428,6 +2513,15 @@ void launch_count_cone(const ConeWork& cw, const uint8_t* skip, const uint32_t* 
     }
     hipLaunchKernelGGL(cone_counts_kernel, dim3(nb), dim3(kRaysPerBlock), 0, s, n, cw.n_masks, p.max_per_ray, cw.masks,
                        cw.extra, packed, sums);
+}
+
+void launch_count_box(const uint32_t* halo, const uint32_t* holes, int64_t, hipStream_t s, const float* o,
+                      const float* d, const int32_t* gid, int64_t n, const uint32_t* bits, const GridK& g,
+                      const ClipK& c, const StepK& p, int32_t* packed, int64_t* sums, uint64_t* masks, int n_masks) {
+    const int rays = segment_rays(n, n_masks);
+    hipLaunchKernelGGL(count_box_kernel, dim3(static_cast<unsigned>((n + rays - 1) / rays)), dim3(kTaskThreads),
+                       box_lds(rays, n_masks), s, o, d, gid, n, bits, halo, holes, g, c, p, n_masks, rays, packed,
+                       sums, masks);
 }
 
 template <int LOOKUP, bool SKIP, typename... A>
@@ -2487,13 +2581,15 @@ using Lookup = std::integral_constant<int, LOOKUP>;
 // lookup's cone steps use them; the skip buffer's distances serve the
 // uniform steps of the other lookups.
 template <int LOOKUP, typename... A>
-void dispatch_count(const uint8_t* skip, const uint32_t* halo, const ConeWork* cw, A&&... a) {
+void dispatch_count(const uint8_t* skip, const uint32_t* halo, const uint32_t* holes, const ConeWork* cw, A&&... a) {
     if (cw != nullptr) {
         launch_count_cone<LOOKUP>(*cw, skip, halo, a...);
-    } else if (LOOKUP == NACC_LOOKUP_AABB ? halo != nullptr : skip != nullptr) {
-        launch_count_waves<LOOKUP, true>(skip, halo, a...);
+    } else if (LOOKUP == NACC_LOOKUP_AABB && halo != nullptr) {
+        launch_count_box(halo, holes, a...);
+    } else if (LOOKUP != NACC_LOOKUP_AABB && skip != nullptr) {
+        launch_count_waves<LOOKUP, true>(skip, a...);
     } else {
-        launch_count_waves<LOOKUP, false>(nullptr, nullptr, a...);
+        launch_count_waves<LOOKUP, false>(nullptr, a...);
     }
 }
 
@@ -2522,7 +2618,8 @@ const uint8_t* usable_skip(const uint8_t* skip, const nacc_grid_desc& grid) {
 int march_count_launch(const float* rays_o, const float* rays_d, const int32_t* grid_id, int64_t n_rays,
                        const uint32_t* grid_bits, const uint8_t* grid_skip, const nacc_grid_desc* grid,
                        const nacc_march_params* params, int32_t* packed_info, int64_t* total, int64_t* sums,
-                       uint64_t* masks, int n_masks, const ConeWork* cw, uint32_t* own_halo, hipStream_t s) {
+                       uint64_t* masks, int n_masks, const ConeWork* cw, uint32_t* own_halo, uint32_t* own_holes,
+                       hipStream_t s) {
     GridK g;
     ClipK c;
     StepK p;
@@ -2533,15 +2630,17 @@ int march_count_launch(const float* rays_o, const float* rays_d, const int32_t* 
     bool by_segments = false;
     if (nb > 0) {
         const uint32_t* halo = halo_of(skip, g);
-        if (halo == nullptr && own_halo != nullptr) {
-            launch_halo(grid_bits, g.res, g.n_grids, own_halo, s);
+        const bool own = halo == nullptr && own_halo != nullptr;
+        if (own || own_holes != nullptr) {
+            launch_halo(grid_bits, g.res, g.n_grids, own ? own_halo : nullptr, own_holes, s);
             st = check_launch("march halo");
             if (st != NACC_OK) return st;
-            halo = own_halo;
+            if (own) halo = own_halo;
         }
-        by_segments = cw != nullptr && cone_segments(*cw, halo);
+        if (n_masks == 0) halo = nullptr;  // no candidates: nothing to look up
+        by_segments = halo != nullptr && (cw != nullptr || grid->lookup == NACC_LOOKUP_AABB);
         auto run = [&](auto lookup) {
-            dispatch_count<decltype(lookup)::value>(skip, halo, cw, nb, s, rays_o, rays_d, grid_id, n_rays, grid_bits,
+            dispatch_count<decltype(lookup)::value>(skip, halo, own_holes, cw, nb, s, rays_o, rays_d, grid_id, n_rays, grid_bits,
                                                     g, c, p, packed_info, sums, masks, n_masks);
         };
         switch (grid->lookup) {
@@ -2556,9 +2655,10 @@ int march_count_launch(const float* rays_o, const float* rays_d, const int32_t* 
         scan_exclusive(sums, 0, total, nullptr, s);
         return check_launch("march scan");
     }
-    int part_rays = kRaysPerBlock;  // rays of a sum
-    if (cw == nullptr) part_rays /= march_split(nb, tuning().march_waves_per_group);
-    else if (by_segments) part_rays = cone_rays(n_rays, cw->n_masks);
+    // rays of a sum
+    const int part_rays = by_segments     ? segment_rays(n_rays, n_masks)
+                          : cw != nullptr ? kRaysPerBlock
+                                          : kRaysPerBlock / march_split(nb, tuning().march_waves_per_group);
     launch_starts(sums, (n_rays + part_rays - 1) / part_rays, __builtin_ctz(static_cast<unsigned>(part_rays)), n_rays,
                   packed_info, total, s);
     return check_launch("march starts");
@@ -2617,8 +2717,10 @@ int nacc_march_count(const float* rays_o, const float* rays_d, const int32_t* gr
     }
     uint32_t* own_halo =
         lay.halo_off != 0 ? reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + lay.halo_off) : nullptr;
+    uint32_t* own_holes =
+        lay.holes_off != 0 ? reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + lay.holes_off) : nullptr;
     return march_count_launch(rays_o, rays_d, grid_id, n_rays, grid_bits, grid_skip, grid, params, packed_info,
-                              total, static_cast<int64_t*>(workspace), masks, lay.n_masks, cw, own_halo,
+                              total, static_cast<int64_t*>(workspace), masks, lay.n_masks, cw, own_halo, own_holes,
                               as_stream(stream));
 }
 

@@ -311,3 +311,25 @@ def test_cone_fill_rays_per_wave(n_rays, cap):
         for scale in (0.1, 1.0):
             compare((o * np.float32(scale)).astype(np.float32), d, mask, 16, BOX, 0.05, 1e10, 0.01, cone=1 / 512,
                     max_per_ray=cap)
+
+
+@pytest.mark.parametrize("res,dt,p_occ,cap", [
+    (16, 0.0005, 0.02, 0), (16, 0.0005, 0.97, 70),  # more candidates than stored chunks: windows
+    (8, 0.02, 1.0, 0),                              # every segment inside occupied cells
+    (16, 0.03, 0.99, 0), (32, 0.0137, 0.98, 0), (64, 0.004, 0.995, 0),  # segments of 8 to 32
+    (64, 0.05, 0.5, 0),                             # rays too fast for segments
+    (64, 0.0137, 0.03, 5),
+])
+@pytest.mark.parametrize("n_rays,n_grids", [(60, 1), (16900, 1), (17401, 2)])
+def test_box_count(res, dt, p_occ, cap, n_rays, n_grids):
+    """Uniform steps by halo bits, and (from 16,384 rays and a quarter of
+    the halo words on) by hole bits: grids of solid parts with gaps."""
+    if n_rays > 60 and res == 16 and dt < 0.001:
+        n_rays = 16500
+    mask = synth.random_mask(n_grids * res ** 3, p_occ, 26).reshape(n_grids, res, res, res)
+    if p_occ > 0.9:
+        mask[:, res // 2:] = 1
+    o, d = synth.rays_toward_origin(n_rays, 70)
+    gid = np.random.default_rng(6).integers(0, n_grids, n_rays).astype(np.int32)
+    kw = dict(n_grids=n_grids, grid_id=gid) if n_grids > 1 else {}
+    compare(o, d, mask.reshape(-1), res, BOX, 0.0, 1e10, dt, max_per_ray=cap, **kw)
