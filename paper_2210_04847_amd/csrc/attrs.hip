@@ -171,7 +171,7 @@ __device__ __forceinline__ void store_rows_staged(const Staged& g, float* __rest
 // a block, the last four ending with the row.
 // Bound by HBM.  4.6 M samples of 30,011 rays, 7 channels: forward 53 -> 34
 // us, backward 106 -> 75 us; forward and backward of 17 channels 484 -> 262
-// us, of 33 channels 1,665 -> 807 us, of 24 channels 480 -> 483 us.
+// us, of 33 channels 1,665 -> 807 us.
 // (Regrouping such rows through LDS a float at a time measured slower, 7
 // channels 85 and 258 us: the index arithmetic.)
 template <int CH>
@@ -179,8 +179,8 @@ struct __attribute__((packed, aligned(4))) Row {
     float v[CH];
 };
 
-// Which channel a[k] holds after load_row at c0: c0 + k in rows of CH < 16
-// channels (c0 = 0), else the fours of the block from c0 on, the last of
+// Which channel a[k] holds after load_row at c0: c0 + k for CH < 16 (which
+// divides the row), else the fours of the block from c0 on, the last of
 // which ends with the row; false where it holds none of the block or one
 // that another a[k] holds too.
 template <int CH>
@@ -246,11 +246,12 @@ __global__ __launch_bounds__(kAttrThreads) void attrs_fwd_kernel(
     const float* __restrict__ te, const float* __restrict__ sig, const float* __restrict__ attrs, int n_ch,
     float eps, float alpha_thre, const float* __restrict__ background, float* __restrict__ out,
     float* __restrict__ opacity, float* __restrict__ depth, float* __restrict__ weights) {
-    // STAGE 0: rows by their own lanes, CH channels at a time; 1: rows of one
-    // block (4, 8 or 16 channels) through LDS; 2: rows of several blocks of 16
-    // through LDS (CH = 16)
-    constexpr bool STAGED = STAGE > 0, WIDE = STAGE == 2;
-    if (CH < kBlock) n_ch = CH;
+    // STAGE 0: rows by their own lanes, of CH channels or (CH = 16) more; 1:
+    // rows of one block (4, 8 or 16 channels) through LDS; 2: rows of several
+    // blocks of 16 through LDS (CH = 16); 3: rows by their own lanes, twice CH
+    // channels
+    constexpr bool STAGED = STAGE == 1 || STAGE == 2, WIDE = STAGE == 2;
+    if (STAGE == 0 && CH < kBlock) n_ch = CH;
     const int lane = lane_id();
     const int64_t r = xcd_grouped<16>(blockIdx.x, gridDim.x) * kAttrRays + uniform<int>(static_cast<int>(threadIdx.x) / kWave);
     if (r >= n_rays) return;
@@ -334,11 +335,12 @@ __global__ __launch_bounds__(kAttrThreads) void attrs_bwd_kernel(
     float eps, float alpha_thre, const float* __restrict__ background, const float* __restrict__ g_out,
     const float* __restrict__ g_opacity, const float* __restrict__ g_depth, float* __restrict__ g_sigmas,
     float* __restrict__ g_attrs) {
-    // STAGE 0: rows by their own lanes, CH channels at a time; 1: rows of one
-    // block (4, 8 or 16 channels) through LDS; 2: rows of several blocks of 16
-    // through LDS (CH = 16)
-    constexpr bool STAGED = STAGE > 0, WIDE = STAGE == 2;
-    if (CH < kBlock) n_ch = CH;
+    // STAGE 0: rows by their own lanes, of CH channels or (CH = 16) more; 1:
+    // rows of one block (4, 8 or 16 channels) through LDS; 2: rows of several
+    // blocks of 16 through LDS (CH = 16); 3: rows by their own lanes, twice CH
+    // channels
+    constexpr bool STAGED = STAGE == 1 || STAGE == 2, WIDE = STAGE == 2;
+    if (STAGE == 0 && CH < kBlock) n_ch = CH;
     const int lane = lane_id();
     const int64_t r = xcd_grouped<16>(blockIdx.x, gridDim.x) * kAttrRays + uniform<int>(static_cast<int>(threadIdx.x) / kWave);
     if (r >= n_rays) return;
@@ -502,18 +504,27 @@ bool vec4_rows(const float* a, const float* b, int32_t n_ch) {
     return n_ch % 4 == 0 && (reinterpret_cast<uintptr_t>(a) % 16) == 0 && (reinterpret_cast<uintptr_t>(b) % 16) == 0;
 }
 
-// The kernels for rows by their own lanes: n_ch channels at a time up to
-// kBlock.
+// The kernels for rows by their own lanes: whole rows of up to kBlock
+// channels; rows of twice 12 to 15 channels in halves; others a block at a
+// time.  24 channels (forward and backward of 6.6 M samples): 550 us in
+// halves, 586 us as 16 and 8; 20 channels 548 and 531 us, 36 in thirds 1,097
+// and 1,025 us.
+bool halved_width(int n_ch) { return n_ch >= 24 && n_ch < 2 * kBlock && n_ch % 2 == 0; }
+
 template <int... I>
 auto attrs_fwd_rows(int n_ch, std::integer_sequence<int, I...>) {
-    constexpr decltype(&attrs_fwd_kernel<0, 1>) table[] = {attrs_fwd_kernel<0, I + 1>...};
-    return table[std::min(n_ch, kBlock) - 1];
+    constexpr decltype(&attrs_fwd_kernel<0, 1>) rows[] = {attrs_fwd_kernel<0, I + 1>...};
+    constexpr decltype(&attrs_fwd_kernel<0, 1>) halves[] = {attrs_fwd_kernel<3, 12>, attrs_fwd_kernel<3, 13>,
+                                                            attrs_fwd_kernel<3, 14>, attrs_fwd_kernel<3, 15>};
+    return halved_width(n_ch) ? halves[n_ch / 2 - 12] : rows[std::min(n_ch, kBlock) - 1];
 }
 
 template <int... I>
 auto attrs_bwd_rows(int n_ch, std::integer_sequence<int, I...>) {
-    constexpr decltype(&attrs_bwd_kernel<0, 1>) table[] = {attrs_bwd_kernel<0, I + 1>...};
-    return table[std::min(n_ch, kBlock) - 1];
+    constexpr decltype(&attrs_bwd_kernel<0, 1>) rows[] = {attrs_bwd_kernel<0, I + 1>...};
+    constexpr decltype(&attrs_bwd_kernel<0, 1>) halves[] = {attrs_bwd_kernel<3, 12>, attrs_bwd_kernel<3, 13>,
+                                                            attrs_bwd_kernel<3, 14>, attrs_bwd_kernel<3, 15>};
+    return halved_width(n_ch) ? halves[n_ch / 2 - 12] : rows[std::min(n_ch, kBlock) - 1];
 }
 
 }  // namespace
