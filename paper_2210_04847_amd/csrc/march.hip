@@ -2369,9 +2369,8 @@ int64_t align256(int64_t b) { return ((b + 255) / 256) * 256; }
 
 // Whether a count pass without a skip buffer builds halo bits of its own
 // (halo.h, 4.5 us up to a few 128^3 grids, 23 us for 64 of them) in the
-// workspace, so as to look up only the candidates near occupied cells; and
-// whether uniform steps through the box build hole bits (5 us), with a skip
-// buffer too.  Uniform steps gain from about 16,384 rays on (128^3, a ball:
+// workspace, so as to look up only the candidates near occupied cells.
+// Uniform steps gain from about 16,384 rays on (128^3, a ball:
 // 109 -> 68 us a call at 32,768 rays, 482 -> 273 us at 262,144; even at
 // 16,384; cells occupied at random: 105 -> 87 and 330 -> 319 us).  Cone steps
 // gain from the smallest batches on (they also lose a separate expansion of
@@ -2383,6 +2382,15 @@ bool builds_halo(int64_t n_rays, int n_masks, const nacc_grid_desc& grid, const 
     const int64_t words = halo_words(grid.res) * grid.n_grids;
     if (p.cone > 0.0f) return words <= 65536 + 16 * n_rays;
     return grid.lookup == NACC_LOOKUP_AABB && n_rays >= 16384 + words / 4;
+}
+
+// Whether uniform steps through the box build hole bits, with a skip buffer
+// too: 5 us for a 128^3 grid, about 20 us for 64, and they take a tenth off
+// the time of the count where there are solid parts (small blobs, 262,144
+// rays: 24 us) and add to it where there are none.
+bool builds_holes(int64_t n_rays, int n_masks, const nacc_grid_desc& grid, const nacc_march_params& p) {
+    return n_masks > 0 && p.cone == 0.0f && grid.lookup == NACC_LOOKUP_AABB &&
+           n_rays >= 16384 + 2 * halo_words(grid.res) * grid.n_grids;
 }
 
 Layout workspace_layout(int64_t n_rays, const nacc_grid_desc& grid, const nacc_march_params& p) {
@@ -2413,10 +2421,10 @@ Layout workspace_layout(int64_t n_rays, const nacc_grid_desc& grid, const nacc_m
     if (builds_halo(n_rays, l.n_masks, grid, p)) {
         l.halo_off = l.bytes;
         l.bytes += align256(halo_words(grid.res) * 4 * grid.n_grids);
-        if (p.cone == 0.0f) {
-            l.holes_off = l.bytes;
-            l.bytes += align256(halo_words(grid.res) * 4 * grid.n_grids);
-        }
+    }
+    if (builds_holes(n_rays, l.n_masks, grid, p)) {
+        l.holes_off = l.bytes;
+        l.bytes += align256(halo_words(grid.res) * 4 * grid.n_grids);
     }
     return l;
 }

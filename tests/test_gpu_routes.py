@@ -320,10 +320,10 @@ def test_cone_fill_rays_per_wave(n_rays, cap):
     (64, 0.05, 0.5, 0),                             # rays too fast for segments
     (64, 0.0137, 0.03, 5),
 ])
-@pytest.mark.parametrize("n_rays,n_grids", [(60, 1), (16900, 1), (17401, 2)])
+@pytest.mark.parametrize("n_rays,n_grids", [(60, 1), (16900, 1), (18500, 1), (17401, 2)])
 def test_box_count(res, dt, p_occ, cap, n_rays, n_grids):
-    """Uniform steps by halo bits, and (from 16,384 rays and a quarter of
-    the halo words on) by hole bits: grids of solid parts with gaps."""
+    """Uniform steps by halo bits, and (from 16,384 rays and twice the halo
+    words on) by hole bits: grids of solid parts with gaps."""
     if n_rays > 60 and res == 16 and dt < 0.001:
         n_rays = 16500
     mask = synth.random_mask(n_grids * res ** 3, p_occ, 26).reshape(n_grids, res, res, res)
