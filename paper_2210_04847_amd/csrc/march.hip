@@ -813,9 +813,10 @@ __device__ __forceinline__ uint32_t cell_index(const GridK& g, float u0, float u
 // selections (wide_levels keeps the scales far from the ends of the exponent
 // range).  Contraction: the fast cells first, then the exact ones where any
 // lane needs them, four candidates at a time: all eight together hold 110
-// registers, and half the waves fit (210 us for 131,072 rays of 40 chunks
-// against 165).  The other lookups hold eight in 62 registers (262,144 rays
-// of a cascade: 129 us against 135 four at a time).
+// registers, and half the waves fit (131,071 rays of 39 chunks: count 210 us;
+// 137 us four at a time and with cells_within before them).  The other
+// lookups hold eight in 62 registers (262,144 rays of a cascade: 129 us
+// against 135 four at a time).
 template <int LOOKUP>
 __device__ __forceinline__ uint32_t segment_hits(__amdgpu_buffer_rsrc_t grs, const GridK& g, const StepK& p,
                                                  uint32_t word0, const SegLevels& lv, const float o[3],
@@ -2385,9 +2386,10 @@ bool builds_halo(int64_t n_rays, int n_masks, const nacc_grid_desc& grid, const 
 }
 
 // Whether uniform steps through the box build hole bits, with a skip buffer
-// too: 5 us for a 128^3 grid, about 20 us for 64, and they take a tenth off
-// the time of the count where there are solid parts (small blobs, 262,144
-// rays: 24 us) and add to it where there are none.
+// too: 5 us for a 128^3 grid.  They shorten the count where there are solid
+// parts (small blobs, 262,144 rays: 162 -> 138 us) and lengthen it where there
+// are none (a thin shell in each of 64 grids, 262,144 rays: 178 us a call
+// without them, 251 with).
 bool builds_holes(int64_t n_rays, int n_masks, const nacc_grid_desc& grid, const nacc_march_params& p) {
     return n_masks > 0 && p.cone == 0.0f && grid.lookup == NACC_LOOKUP_AABB &&
            n_rays >= 16384 + 2 * halo_words(grid.res) * grid.n_grids;
