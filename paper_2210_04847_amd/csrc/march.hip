@@ -33,6 +33,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "fill_list.h"
 #include "halo.h"
 #include "lattice.h"
 #include "scan.h"
@@ -430,6 +431,8 @@ constexpr int kFillQueue = 3 * kWave;        // halves left over (< 64) and thos
 constexpr int kFillCodes = kWave * 32 + kWave;  // samples of 64 halves, from any place in a block
 constexpr int kCodeRayShift = 12;            // code: ray of the wave << 12 | candidate (< 64 chunks x 64)
 
+static_assert(kListBlock == kWave, "a position of a block per lane");
+
 struct FillOut {
     int32_t* ray_indices;
     float* t_starts;
@@ -498,12 +501,9 @@ __device__ __forceinline__ int store_halves(const FillOut& out, FillLds& q, int 
         }
     }
     wave_lds_sync();
-    int b = block;
-    if (b + kWave == head_end && head_end <= end) {
-        q.head[lane] = q.codes[lane];
-        b += kWave;
-    }
-    for (; b + kWave <= end; b += kWave) store_sample(out, times, first_ray, b, q.codes[b - block + lane]);
+    const int b = walk_blocks(
+        block, head_end, end, [&]() { q.head[lane] = q.codes[lane]; },
+        [&](int p) { store_sample(out, times, first_ray, p, q.codes[p - block + lane]); });
     if (b > block) {
         const uint16_t c = q.codes[b - block + lane];
         wave_lds_sync();
@@ -512,21 +512,6 @@ __device__ __forceinline__ int store_halves(const FillOut& out, FillLds& q, int 
     }
     wave_lds_sync();
     return end;
-}
-
-// The list of a wave: it holds the positions [block, pos); `queued` halves
-// wait for it; head_end: see store_halves.
-struct FillList {
-    int pos, block, head_end, queued;
-};
-
-__device__ __forceinline__ FillList begin_list(int pos) {
-    FillList l;
-    l.pos = pos;
-    l.block = pos & ~(kWave - 1);
-    l.head_end = l.block == pos ? -1 : l.block + kWave;
-    l.queued = 0;
-    return l;
 }
 
 // Queues the samples of 64 chunks, a lane's mask and the code of its first
@@ -674,7 +659,7 @@ __global__ __launch_bounds__(kFillThreads) void fill_uniform_kernel(
     // every ray's samples are those of its stored chunks (the first `limit`
     // of them), and they lie side by side inside the output
     const bool simple = ballot(lane < n_mine && (limit > stored || (limit > 0 && start != pos0 + before))) == 0ull &&
-                        pos0 >= 0 && static_cast<int64_t>(pos0) + n_out <= min(capacity, static_cast<int64_t>(INT32_MAX));
+                        list_fits(pos0, n_out, capacity);
     const bool capped = ballot(limit < stored) != 0ull;
     FillList list = begin_list(pos0);
     const UniformTimes times{q.t_near, p.dt};
@@ -2038,8 +2023,7 @@ __global__ __launch_bounds__(kTaskThreads, 6) void fill_cone_rays_kernel(
     const bool on_table = limit == 0 || (stored < kOwnLattice && !(t_end < INFINITY) &&
                                          static_cast<uint32_t>(limit) <= stored &&
                                          start == static_cast<int64_t>(pos0) + before);
-    const bool simple =
-        ballot(!on_table) == 0ull && pos0 >= 0 && static_cast<int64_t>(pos0) + n_out <= min(capacity, static_cast<int64_t>(INT32_MAX));
+    const bool simple = ballot(!on_table) == 0ull && list_fits(pos0, n_out, capacity);
     const FillOut out{ray_indices, t_starts, t_ends};
     const TableTimes times{s_times};
     FillList list = begin_list(pos0);
