@@ -166,3 +166,55 @@ def test_prune_random_configurations(seed):
                                                        max_count=int(3 * mean) + 1,
                                                        sigma_max=smax)
     check_prune(packed, ts, te, sg, eps, thre)
+
+
+@pytest.mark.parametrize("n_rays", [1, 16383, 16384, 32768, 131072, 131073, 262144, 262145, 600000])
+@pytest.mark.parametrize("long_rays", [False, True])
+def test_pruned_samples_of_many_rays(n_rays, long_rays):
+    """1 to 16 rays per wave: the flags of samples away from both thresholds,
+    and every output sample, which the flags select exactly; rays of no, one
+    and many chunks, and (a few) of hundreds, most of them cut early; an
+    output too short for the samples holds the first ones."""
+    lib = _lib()
+    rng = np.random.default_rng(701)
+    count = rng.choice([0, 1, 63, 64, 65, 130, 200], n_rays, p=[0.4, 0.25, 0.1, 0.1, 0.05, 0.05, 0.05])
+    if long_rays:
+        count[rng.integers(0, n_rays, 25)] = rng.integers(5000, 20000, 25)
+    t = lambda a: torch.from_numpy(a).cuda()
+    start = np.cumsum(count) - count
+    packed = t(np.stack([start, count], 1).astype(np.int32))
+    e = int(count.sum())
+    g = torch.Generator(device="cuda").manual_seed(702)
+    ts = torch.rand(e, generator=g, device="cuda")
+    te = ts + 0.01
+    sg = torch.rand(e, generator=g, device="cuda") ** 4 * 200.0
+    keep = torch.full((e,), 7, dtype=torch.uint8, device="cuda")
+    out = torch.empty((n_rays, 2), dtype=torch.int32, device="cuda")
+    total = torch.empty(1, dtype=torch.int64, device="cuda")
+    ws = torch.empty(lib.prune_workspace_size(n_rays), dtype=torch.uint8, device="cuda")
+    lib.prune_count(packed, ts, te, sg, 1e-2, 0.05, keep, out, total, ws)
+    assert int((keep > 1).sum()) == 0
+    # the flags, by the transmittance and opacity in 64 bits
+    ray = torch.repeat_interleave(torch.arange(n_rays, device="cuda"), t(count))
+    tau = sg.double() * (te - ts).double()
+    c = torch.cat([tau.new_zeros(1), tau.cumsum(0)])
+    trans = torch.exp(-(c[:-1] - c[t(start)[ray]]))
+    alpha = -torch.expm1(-tau)
+    sure = ((trans / 1e-2 - 1).abs() > BAND) & ((alpha / 0.05 - 1).abs() > BAND)
+    kept = keep == 1
+    assert torch.equal(kept[sure], ((trans >= 1e-2) & (alpha >= 0.05))[sure])
+    # counts, starts and samples follow the flags
+    n_kept = torch.zeros(n_rays, dtype=torch.long, device="cuda").index_add_(0, ray, kept.long())
+    k = int(total.item())
+    assert k == int(kept.sum()) and torch.equal(out[:, 1].long(), n_kept)
+    assert torch.equal(out[:, 0].long(), n_kept.cumsum(0) - n_kept)
+    want = [ray[kept].int(), ts[kept], te[kept], sg[kept]]
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for room in (k, k - k // 3 - 1):
+        if room < 0:
+            continue
+        got = [torch.full((room + 8,), -3.0, device="cuda").to(w.dtype) for w in want]
+        lib.prune_fill(packed, ts, te, sg, keep, out, *(a[:room] for a in got), status)
+        assert int(status.item()) == (0 if room == k else lib.NACC_ECAPACITY)
+        for a, w in zip(got, want):
+            assert torch.equal(a[:room], w[:room]) and bool((a[room:] == -3).all())

@@ -333,3 +333,12 @@ def test_box_count(res, dt, p_occ, cap, n_rays, n_grids):
     gid = np.random.default_rng(6).integers(0, n_grids, n_rays).astype(np.int32)
     kw = dict(n_grids=n_grids, grid_id=gid) if n_grids > 1 else {}
     compare(o, d, mask.reshape(-1), res, BOX, 0.0, 1e10, dt, max_per_ray=cap, **kw)
+
+
+@pytest.mark.parametrize("n_rays", [65535, 65536])
+def test_contraction_rays_per_workgroup(n_rays):
+    """40 chunks a ray: 16 and 32 rays a workgroup of the cone count."""
+    mask = synth.random_mask(64 ** 3, 0.01, 27)
+    o, d = synth.rays_unbounded(n_rays, 71)
+    compare(o, d, mask, 64, np.array(synth.CONTRACT_BOX, np.float32), 0.2, 1e4, synth.STEP_1024,
+            cone=1 / 256, lookup=2, max_per_ray=64)
