@@ -1875,13 +1875,12 @@ __global__ __launch_bounds__(kTaskThreads) void count_box_kernel(
                 const uint32_t halo0 = __float_as_uint(w4.y);
                 const uint32_t cell = halo_cell(g, a.x + b.x * tc, a.y + b.y * tc, a.z + b.z * tc);
                 const bool open = __float_as_int(w4.z) == 0;
-                bool full = false;
-                if (holes != nullptr) {
-                    const bool hole = halo_bit(ors, halo0, cell);
-                    full = !hole && a.w + static_cast<float>(k + (1 << log_g) - 1) * p.dt < b.w;
-                }
                 bool left = valid && (open | halo_bit(hrs, halo0, cell));
-                full = left && full && !open;
+                bool full = false;
+                if (holes != nullptr) {  // read for the segments left alone
+                    if (left && !open) full = !halo_bit(ors, halo0, cell);
+                    full = full && a.w + static_cast<float>(k + (1 << log_g) - 1) * p.dt < b.w;
+                }
                 left = left && !full;
                 const uint32_t byte = static_cast<uint32_t>(k - kb) >> 3;
                 char* const at = s_masks + rl * stride + byte;
