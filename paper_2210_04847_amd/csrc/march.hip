@@ -1757,12 +1757,22 @@ __global__ __launch_bounds__(kTaskThreads) void count_cone_kernel(
 // 162 us without them (small blobs; a solid ball of 64 cells across gains
 // more), 208 us with a wave per ray after ray, half of whose lanes tested no
 // segment and a fifth looked no candidate up.
+// CAP (max_per_ray > 0): the candidates of the rays are taken in turns, and a
+// ray that holds the cap's number of samples after one takes part no more:
+// what its later turns hold is cut off.  A turn is as long as the cap (no ray
+// reaches it earlier) or has a round of the wave's segments, two where the
+// wave has eight rays or more.  262,144 rays, cells at random (2%), cap 1: 320
+// us a call without turns, 170 with; fine steps (8,660 candidates a ray), cap
+// 16: 1,329 -> 676 us, a solid box 235 -> 163 us, a ball 368 -> 287 us (343 and
+// 314 us with turns of one round; 8,192 rays, two a wave, a solid box 89 us
+// with two rounds, 72 with one).
 constexpr int kBoxRayFloats = 12;  // 16-byte fields, 16 different ones in different banks
 
 __host__ __device__ inline int box_lds(int rays, int n_masks) {
     return rays * (kBoxRayFloats * 4 + mask_row_bytes(n_masks)) + kTaskWaves * kSegStack * 4;
 }
 
+template <bool CAP>
 __global__ __launch_bounds__(kTaskThreads) void count_box_kernel(
     const float* __restrict__ rays_o, const float* __restrict__ rays_d, const int32_t* __restrict__ grid_id,
     int64_t n_rays, const uint32_t* __restrict__ bits, const uint32_t* __restrict__ halo,
@@ -1805,11 +1815,20 @@ __global__ __launch_bounds__(kTaskThreads) void count_box_kernel(
     // candidates of the ray, at most (the last t below t_far, with the
     // roundings of t and of this bound)
     const float bound = (((t_far - t_near) + (fabsf(t_far) + fabsf(t_near)) * 0x1p-22f) / p.dt) * (1.0f + 0x1p-20f) + 2.0f;
-    const int k_end = !(t_near < t_far) ? 0
-                      : bound < static_cast<float>(kMaxCandidates) ? static_cast<int>(bound)
-                                                                   : kMaxCandidates;
+    int k_end = !(t_near < t_far) ? 0
+                : bound < static_cast<float>(kMaxCandidates) ? static_cast<int>(bound)
+                                                             : kMaxCandidates;
     const __amdgpu_buffer_rsrc_t grs = grid_rsrc(bits, g), hrs = halo_rsrc(halo, g), ors = halo_rsrc(holes, g);
     const int window = n_masks * kWave;
+    const int turn_segs = per >= 8 ? 2 * kWave : kWave;
+    const int turn = !CAP ? window
+                          : min(window, max((min(p.max_per_ray, window) + kWave - 1) & ~(kWave - 1),
+                                            max((turn_segs << log_g) / per, kWave)));
+    // samples found so far of a ray, where there is a cap
+    auto taken_of = [&](int rl) { return reinterpret_cast<int*>(lds4 + rl * (kBoxRayFloats / 4) + 2) + 3; };
+    auto take = [&](int rl, int n) {
+        __hip_atomic_fetch_add(taken_of(rl), n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    };
     const uint32_t inv = 65536u / static_cast<uint32_t>(n_masks) + 1u;  // i / n_masks, i < 1,024
     const int64_t wave_first = first + ray0;
     const int n_mine = static_cast<int>(max(min(static_cast<int64_t>(per), n_rays - wave_first), int64_t{0}));
@@ -1818,84 +1837,94 @@ __global__ __launch_bounds__(kTaskThreads) void count_box_kernel(
         for (int i = lane; i < per * (stride / 8); i += kWave) {
             reinterpret_cast<uint64_t*>(s_masks + ray0 * stride)[i] = 0ull;
         }
-        const int n_segs = (min(max(k_end - kb, 0), window) + (1 << log_g) - 1) >> log_g;
-        const int before = wave_inclusive_sum(n_segs) - n_segs;
-        const int total = read_lane(before + n_segs, kWave - 1);
-        wave_lds_sync();
-        int f0 = 0, n_q = 0;  // segments tested; entries of the stack
-        for (;;) {
-            if (n_q >= per_round || (n_q > 0 && f0 >= total)) {
-                // look up 64 runs of eight candidates
-                const int n = min(n_q, per_round);
-                n_q -= n;
-                const int e = lane >> part_log;
-                const bool has = e < n;
-                const uint32_t id = q[n_q + (has ? e : 0)];
-                const int rl = static_cast<int>(id >> 16);
-                const int byte = static_cast<int>(id & 0xffffu) + (lane & ((1 << part_log) - 1));
-                const float4* const ray = lds4 + rl * (kBoxRayFloats / 4);
-                const float4 a = ray[0], b = ray[1], w4 = ray[2];
-                const float k0 = static_cast<float>(kb + byte * kConeBatch);
-                const uint32_t word0 = __float_as_uint(w4.x);
-                float t[kConeBatch + 1];
-#pragma unroll
-                for (int u = 0; u <= kConeBatch; ++u) t[u] = a.w + (k0 + static_cast<float>(u)) * p.dt;
-                uint32_t cell[kConeBatch], w[kConeBatch];
-#pragma unroll
-                for (int u = 0; u < kConeBatch; ++u) {
-                    const float tm = (t[u] + t[u + 1]) * 0.5f;
-                    const float x0 = a.x + b.x * tm, x1 = a.y + b.y * tm, x2 = a.z + b.z * tm;
-                    cell[u] =
-                        cell_index(g, (x0 - g.lo[0]) * g.s[0], (x1 - g.lo[1]) * g.s[1], (x2 - g.lo[2]) * g.s[2]);
-                    w[u] = grid_word(grs, word0 + (cell[u] >> 5));
-                }
-                uint32_t hits = 0u;
-#pragma unroll
-                for (int u = 0; u < kConeBatch; ++u) {
-                    const uint32_t bit = __builtin_amdgcn_ubfe(w[u], cell[u] & 31u, 1u);
-                    hits |= (t[u] < b.w ? bit : 0u) << u;
-                }
-                if (has && hits != 0u) s_masks[rl * stride + byte] = static_cast<char>(hits);
-            } else if (f0 < total) {
-                // test 64 segments: segment f of the wave, the s-th of ray L
-                const int f = f0 + lane;
-                f0 += kWave;
-                int L = 0;
-#pragma unroll
-                for (int step = kSegmentRaysMax / kTaskWaves / 2; step >= 1; step >>= 1) {
-                    if (lane_value(before, L + step) <= f) L += step;
-                }
-                const int s = f - lane_value(before, L);
-                const int rl = ray0 + min(L, per - 1);
-                const int k = kb + (s << log_g);
-                const float4* const ray = lds4 + rl * (kBoxRayFloats / 4);
-                const float4 a = ray[0], b = ray[1], w4 = ray[2];
-                const bool valid = f < total && a.w + static_cast<float>(k) * p.dt < b.w;
-                const float tc = a.w + static_cast<float>(k + (1 << (log_g - 1))) * p.dt;
-                const uint32_t halo0 = __float_as_uint(w4.y);
-                const uint32_t cell = halo_cell(g, a.x + b.x * tc, a.y + b.y * tc, a.z + b.z * tc);
-                const bool open = __float_as_int(w4.z) == 0;
-                bool left = valid && (open | halo_bit(hrs, halo0, cell));
-                bool full = false;
-                if (holes != nullptr) {  // read for the segments left alone
-                    if (left && !open) full = !halo_bit(ors, halo0, cell);
-                    full = full && a.w + static_cast<float>(k + (1 << log_g) - 1) * p.dt < b.w;
-                }
-                left = left && !full;
-                const uint32_t byte = static_cast<uint32_t>(k - kb) >> 3;
-                char* const at = s_masks + rl * stride + byte;
-                if (full) {
-                    if (log_g == 3) *reinterpret_cast<uint8_t*>(at) = 0xffu;
-                    else if (log_g == 4) *reinterpret_cast<uint16_t*>(at) = 0xffffu;
-                    else *reinterpret_cast<uint32_t*>(at) = ~0u;
-                }
-                const uint64_t m = ballot(left);
-                if (left) q[n_q + bits_below(m)] = (static_cast<uint32_t>(rl) << 16) | byte;
-                n_q += static_cast<int>(__popcll(m));
-            } else {
-                break;
-            }
+        int n_q = 0;  // entries of the stack
+        for (int kw = kb; kw < kb + window; kw += turn) {
             wave_lds_sync();
+            if (CAP && lane < per && taken_of(ray0 + lane)[0] >= p.max_per_ray) k_end = 0;
+            const bool last = ballot(k_end > kw + turn) == 0ull || kw + turn >= kb + window;
+            const int n_segs = (min(max(k_end - kw, 0), min(turn, kb + window - kw)) + (1 << log_g) - 1) >> log_g;
+            const int before = wave_inclusive_sum(n_segs) - n_segs;
+            const int total = read_lane(before + n_segs, kWave - 1);
+            int f0 = 0;  // segments tested
+            for (;;) {
+                if (n_q >= per_round || (n_q > 0 && f0 >= total && last)) {
+                    // look up 64 runs of eight candidates
+                    const int n = min(n_q, per_round);
+                    n_q -= n;
+                    const int e = lane >> part_log;
+                    const bool has = e < n;
+                    const uint32_t id = q[n_q + (has ? e : 0)];
+                    const int rl = static_cast<int>(id >> 16);
+                    const int byte = static_cast<int>(id & 0xffffu) + (lane & ((1 << part_log) - 1));
+                    const float4* const ray = lds4 + rl * (kBoxRayFloats / 4);
+                    const float4 a = ray[0], b = ray[1], w4 = ray[2];
+                    const float k0 = static_cast<float>(kb + byte * kConeBatch);
+                    const uint32_t word0 = __float_as_uint(w4.x);
+                    float t[kConeBatch + 1];
+#pragma unroll
+                    for (int u = 0; u <= kConeBatch; ++u) t[u] = a.w + (k0 + static_cast<float>(u)) * p.dt;
+                    uint32_t cell[kConeBatch], w[kConeBatch];
+#pragma unroll
+                    for (int u = 0; u < kConeBatch; ++u) {
+                        const float tm = (t[u] + t[u + 1]) * 0.5f;
+                        const float x0 = a.x + b.x * tm, x1 = a.y + b.y * tm, x2 = a.z + b.z * tm;
+                        cell[u] =
+                            cell_index(g, (x0 - g.lo[0]) * g.s[0], (x1 - g.lo[1]) * g.s[1], (x2 - g.lo[2]) * g.s[2]);
+                        w[u] = grid_word(grs, word0 + (cell[u] >> 5));
+                    }
+                    uint32_t hits = 0u;
+#pragma unroll
+                    for (int u = 0; u < kConeBatch; ++u) {
+                        const uint32_t bit = __builtin_amdgcn_ubfe(w[u], cell[u] & 31u, 1u);
+                        hits |= (t[u] < b.w ? bit : 0u) << u;
+                    }
+                    if (has && hits != 0u) {
+                        s_masks[rl * stride + byte] = static_cast<char>(hits);
+                        if (CAP) take(rl, __popc(hits));
+                    }
+                } else if (f0 < total) {
+                    // test 64 segments: segment f of the wave, the s-th of ray L
+                    const int f = f0 + lane;
+                    f0 += kWave;
+                    int L = 0;
+#pragma unroll
+                    for (int step = kSegmentRaysMax / kTaskWaves / 2; step >= 1; step >>= 1) {
+                        if (lane_value(before, L + step) <= f) L += step;
+                    }
+                    const int s = f - lane_value(before, L);
+                    const int rl = ray0 + min(L, per - 1);
+                    const int k = kw + (s << log_g);
+                    const float4* const ray = lds4 + rl * (kBoxRayFloats / 4);
+                    const float4 a = ray[0], b = ray[1], w4 = ray[2];
+                    const bool valid = f < total && a.w + static_cast<float>(k) * p.dt < b.w;
+                    const float tc = a.w + static_cast<float>(k + (1 << (log_g - 1))) * p.dt;
+                    const uint32_t halo0 = __float_as_uint(w4.y);
+                    const uint32_t cell = halo_cell(g, a.x + b.x * tc, a.y + b.y * tc, a.z + b.z * tc);
+                    const bool open = __float_as_int(w4.z) == 0;
+                    bool left = valid && (open | halo_bit(hrs, halo0, cell));
+                    bool full = false;
+                    if (holes != nullptr) {  // read for the segments left alone
+                        if (left && !open) full = !halo_bit(ors, halo0, cell);
+                        full = full && a.w + static_cast<float>(k + (1 << log_g) - 1) * p.dt < b.w;
+                    }
+                    left = left && !full;
+                    const uint32_t byte = static_cast<uint32_t>(k - kb) >> 3;
+                    char* const at = s_masks + rl * stride + byte;
+                    if (full) {
+                        if (log_g == 3) *reinterpret_cast<uint8_t*>(at) = 0xffu;
+                        else if (log_g == 4) *reinterpret_cast<uint16_t*>(at) = 0xffffu;
+                        else *reinterpret_cast<uint32_t*>(at) = ~0u;
+                        if (CAP) take(rl, 1 << log_g);
+                    }
+                    const uint64_t m = ballot(left);
+                    if (left) q[n_q + bits_below(m)] = (static_cast<uint32_t>(rl) << 16) | byte;
+                    n_q += static_cast<int>(__popcll(m));
+                } else {
+                    break;
+                }
+                wave_lds_sync();
+            }
+            if (last) break;
         }
         if (lane < per) {
             const uint64_t* const mm = reinterpret_cast<const uint64_t*>(s_masks + (ray0 + lane) * stride);
@@ -1909,10 +1938,10 @@ __global__ __launch_bounds__(kTaskThreads) void count_box_kernel(
                     s_masks + (ray0 + rl) * stride + (i - rl * n_masks) * 8);
             }
         }
-        if (ballot(k_end > kb + window && !(p.max_per_ray > 0 && count >= p.max_per_ray)) == 0ull) break;
+        if (ballot(k_end > kb + window && !(CAP && count >= p.max_per_ray)) == 0ull) break;
         wave_lds_sync();
     }
-    if (p.max_per_ray > 0) count = min(count, p.max_per_ray);
+    if (CAP) count = min(count, p.max_per_ray);
     if (lane < n_mine) packed_info[2 * (wave_first + lane) + 1] = count;
     const int sum = wave_sum(count);  // <= 16 * 2^24 fits int32
     if (lane == 0) wave_total[wave] = sum;
@@ -2512,9 +2541,9 @@ void launch_count_box(const uint32_t* halo, const uint32_t* holes, int64_t, hipS
                       const float* d, const int32_t* gid, int64_t n, const uint32_t* bits, const GridK& g,
                       const ClipK& c, const StepK& p, int32_t* packed, int64_t* sums, uint64_t* masks, int n_masks) {
     const int rays = segment_rays(n, n_masks);
-    hipLaunchKernelGGL(count_box_kernel, dim3(static_cast<unsigned>((n + rays - 1) / rays)), dim3(kTaskThreads),
-                       box_lds(rays, n_masks), s, o, d, gid, n, bits, halo, holes, g, c, p, n_masks, rays, packed,
-                       sums, masks);
+    hipLaunchKernelGGL(p.max_per_ray > 0 ? count_box_kernel<true> : count_box_kernel<false>,
+                       dim3(static_cast<unsigned>((n + rays - 1) / rays)), dim3(kTaskThreads), box_lds(rays, n_masks),
+                       s, o, d, gid, n, bits, halo, holes, g, c, p, n_masks, rays, packed, sums, masks);
 }
 
 template <int LOOKUP, bool SKIP, typename... A>

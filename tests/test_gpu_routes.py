@@ -342,3 +342,18 @@ def test_contraction_rays_per_workgroup(n_rays):
     o, d = synth.rays_unbounded(n_rays, 71)
     compare(o, d, mask, 64, np.array(synth.CONTRACT_BOX, np.float32), 0.2, 1e4, synth.STEP_1024,
             cone=1 / 256, lookup=2, max_per_ray=64)
+
+
+@pytest.mark.parametrize("n_rays", [1, 900, 8200, 16500])
+@pytest.mark.parametrize("res,dt,p_occ", [(64, 0.0137, 0.02), (32, 0.004, 0.3), (16, 0.0009, 0.05), (8, 0.0011, 1.0),
+                                          (64, 0.05, 0.5)])
+@pytest.mark.parametrize("cap", [1, 7, 130, 4000])
+def test_box_count_in_turns(n_rays, res, dt, p_occ, cap):
+    """Rays capped after the first candidates, in a later turn, in the second
+    window of stored chunks, and never; 1 to 16 rays a wave."""
+    if dt < 0.003:
+        n_rays = min(n_rays, 900)
+    mask = synth.random_mask(res ** 3, p_occ, 28).reshape(res, res, res)
+    mask[:res // 4, :, ::3] = 0
+    o, d = synth.rays_toward_origin(n_rays, 72)
+    compare(o, d, mask.reshape(-1), res, BOX, 0.0, 1e10, dt, max_per_ray=cap)
