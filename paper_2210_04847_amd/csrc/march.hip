@@ -1757,6 +1757,15 @@ __global__ __launch_bounds__(kTaskThreads) void count_cone_kernel(
 // 162 us without them (small blobs; a solid ball of 64 cells across gains
 // more), 208 us with a wave per ray after ray, half of whose lanes tested no
 // segment and a fifth looked no candidate up.
+// SPREAD (more than one grid): of 64 runs a lane looks up one candidate of
+// eight, so that neighbouring lanes read neighbouring cells, and a ballot
+// holds eight runs' bytes; it reads a ray's data anew where the ray changes.
+// With a run a lane every load touches as many cache lines as lanes, the same
+// ones eight times over, and rays of many grids drive them out of the L1 and
+// L2 in between.  262,144 rays in 64 grids of blobs: 407 -> 305 us a call, of 2%
+// random cells 627 -> 427, in 2 grids 270 and 270, 339 and 297.  One grid stays
+// in the L2: blobs 297 both ways, 2% random cells 321 and 295, but a thin shell
+// 138 and 143, 0.02% random cells 107 and 112.
 // CAP (max_per_ray > 0): the candidates of the rays are taken in turns, and a
 // ray that holds the cap's number of samples after one takes part no more:
 // what its later turns hold is cut off.  A turn is as long as the cap (no ray
@@ -1772,7 +1781,7 @@ __host__ __device__ inline int box_lds(int rays, int n_masks) {
     return rays * (kBoxRayFloats * 4 + mask_row_bytes(n_masks)) + kTaskWaves * kSegStack * 4;
 }
 
-template <bool CAP>
+template <bool CAP, bool SPREAD>
 __global__ __launch_bounds__(kTaskThreads) void count_box_kernel(
     const float* __restrict__ rays_o, const float* __restrict__ rays_d, const int32_t* __restrict__ grid_id,
     int64_t n_rays, const uint32_t* __restrict__ bits, const uint32_t* __restrict__ halo,
@@ -1851,36 +1860,84 @@ __global__ __launch_bounds__(kTaskThreads) void count_box_kernel(
                     // look up 64 runs of eight candidates
                     const int n = min(n_q, per_round);
                     n_q -= n;
-                    const int e = lane >> part_log;
-                    const bool has = e < n;
-                    const uint32_t id = q[n_q + (has ? e : 0)];
-                    const int rl = static_cast<int>(id >> 16);
-                    const int byte = static_cast<int>(id & 0xffffu) + (lane & ((1 << part_log) - 1));
-                    const float4* const ray = lds4 + rl * (kBoxRayFloats / 4);
-                    const float4 a = ray[0], b = ray[1], w4 = ray[2];
-                    const float k0 = static_cast<float>(kb + byte * kConeBatch);
-                    const uint32_t word0 = __float_as_uint(w4.x);
-                    float t[kConeBatch + 1];
+                    if constexpr (SPREAD) {
+                        // eight runs a load, one after the other, so that
+                        // neighbouring lanes read neighbouring cells
+                        const int runs = n << part_log, run_mask = (1 << part_log) - 1;
+                        int rl = -1;
+                        float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f), b = a;
+                        uint32_t word0 = 0u;
+                        uint32_t cell[kConeBatch], w[kConeBatch];
+                        uint64_t inside[kConeBatch];
 #pragma unroll
-                    for (int u = 0; u <= kConeBatch; ++u) t[u] = a.w + (k0 + static_cast<float>(u)) * p.dt;
-                    uint32_t cell[kConeBatch], w[kConeBatch];
+                        for (int u = 0; u < kConeBatch; ++u) {
+                            const int run = u * (kWave / kConeBatch) + lane / kConeBatch;
+                            const uint32_t id = q[n_q + min(run >> part_log, n - 1)];
+                            const int r = static_cast<int>(id >> 16);
+                            if (ballot(r != rl) != 0ull) {  // another ray, seldom
+                                rl = r;
+                                const float4* const ray = lds4 + rl * (kBoxRayFloats / 4);
+                                a = ray[0];
+                                b = ray[1];
+                                word0 = __float_as_uint(ray[2].x);
+                            }
+                            const int byte = static_cast<int>(id & 0xffffu) + (run & run_mask);
+                            const float k = static_cast<float>(kb + byte * kConeBatch + lane % kConeBatch);
+                            const float t0 = a.w + k * p.dt, t1 = a.w + (k + 1.0f) * p.dt;
+                            const float tm = (t0 + t1) * 0.5f;
+                            const float x0 = a.x + b.x * tm, x1 = a.y + b.y * tm, x2 = a.z + b.z * tm;
+                            cell[u] = cell_index(g, (x0 - g.lo[0]) * g.s[0], (x1 - g.lo[1]) * g.s[1],
+                                                 (x2 - g.lo[2]) * g.s[2]);
+                            w[u] = grid_word(grs, word0 + (cell[u] >> 5));
+                            inside[u] = ballot(run < runs && t0 < b.w);
+                        }
+                        // lane i: the hits of run i
+                        uint64_t m = 0ull;
 #pragma unroll
-                    for (int u = 0; u < kConeBatch; ++u) {
-                        const float tm = (t[u] + t[u + 1]) * 0.5f;
-                        const float x0 = a.x + b.x * tm, x1 = a.y + b.y * tm, x2 = a.z + b.z * tm;
-                        cell[u] =
-                            cell_index(g, (x0 - g.lo[0]) * g.s[0], (x1 - g.lo[1]) * g.s[1], (x2 - g.lo[2]) * g.s[2]);
-                        w[u] = grid_word(grs, word0 + (cell[u] >> 5));
-                    }
-                    uint32_t hits = 0u;
+                        for (int u = 0; u < kConeBatch; ++u) {
+                            const uint64_t hit = inside[u] & ballot(((w[u] >> (cell[u] & 31u)) & 1u) != 0u);
+                            if (lane / kConeBatch == u) m = hit;
+                        }
+                        const uint32_t hits = static_cast<uint32_t>(m >> (lane % kConeBatch * kConeBatch)) & 0xffu;
+                        if (hits != 0u) {
+                            const uint32_t id = q[n_q + (lane >> part_log)];
+                            const int own = static_cast<int>(id >> 16);
+                            s_masks[own * stride + static_cast<int>(id & 0xffffu) + (lane & run_mask)] =
+                                static_cast<char>(hits);
+                            if (CAP) take(own, __popc(hits));
+                        }
+                    } else {
+                        const int e = lane >> part_log;
+                        const bool has = e < n;
+                        const uint32_t id = q[n_q + (has ? e : 0)];
+                        const int rl = static_cast<int>(id >> 16);
+                        const int byte = static_cast<int>(id & 0xffffu) + (lane & ((1 << part_log) - 1));
+                        const float4* const ray = lds4 + rl * (kBoxRayFloats / 4);
+                        const float4 a = ray[0], b = ray[1], w4 = ray[2];
+                        const float k0 = static_cast<float>(kb + byte * kConeBatch);
+                        const uint32_t word0 = __float_as_uint(w4.x);
+                        float t[kConeBatch + 1];
 #pragma unroll
-                    for (int u = 0; u < kConeBatch; ++u) {
-                        const uint32_t bit = __builtin_amdgcn_ubfe(w[u], cell[u] & 31u, 1u);
-                        hits |= (t[u] < b.w ? bit : 0u) << u;
-                    }
-                    if (has && hits != 0u) {
-                        s_masks[rl * stride + byte] = static_cast<char>(hits);
-                        if (CAP) take(rl, __popc(hits));
+                        for (int u = 0; u <= kConeBatch; ++u) t[u] = a.w + (k0 + static_cast<float>(u)) * p.dt;
+                        uint32_t cell[kConeBatch], w[kConeBatch];
+#pragma unroll
+                        for (int u = 0; u < kConeBatch; ++u) {
+                            const float tm = (t[u] + t[u + 1]) * 0.5f;
+                            const float x0 = a.x + b.x * tm, x1 = a.y + b.y * tm, x2 = a.z + b.z * tm;
+                            cell[u] =
+                                cell_index(g, (x0 - g.lo[0]) * g.s[0], (x1 - g.lo[1]) * g.s[1], (x2 - g.lo[2]) * g.s[2]);
+                            w[u] = grid_word(grs, word0 + (cell[u] >> 5));
+                        }
+                        uint32_t hits = 0u;
+#pragma unroll
+                        for (int u = 0; u < kConeBatch; ++u) {
+                            const uint32_t bit = __builtin_amdgcn_ubfe(w[u], cell[u] & 31u, 1u);
+                            hits |= (t[u] < b.w ? bit : 0u) << u;
+                        }
+                        if (has && hits != 0u) {
+                            s_masks[rl * stride + byte] = static_cast<char>(hits);
+                            if (CAP) take(rl, __popc(hits));
+                        }
                     }
                 } else if (f0 < total) {
                     // test 64 segments: segment f of the wave, the s-th of ray L
@@ -2383,9 +2440,12 @@ int64_t align256(int64_t b) { return ((b + 255) / 256) * 256; }
 // Whether a count pass without a skip buffer builds halo bits of its own
 // (halo.h, 4.5 us up to a few 128^3 grids, 23 us for 64 of them) in the
 // workspace, so as to look up only the candidates near occupied cells.
-// Uniform steps gain from about 16,384 rays on (128^3, a ball:
-// 109 -> 68 us a call at 32,768 rays, 482 -> 273 us at 262,144; even at
-// 16,384; cells occupied at random: 105 -> 87 and 330 -> 319 us).  Cone steps
+// Uniform steps gain from about 16,384 rays on (128^3, a ball: 109 -> 68 us a
+// call at 32,768 rays, 478 -> 262 us at 262,144; even at 16,384; 2% of the
+// cells at random: 105 -> 87 and 331 -> 321 us; 262,144 rays in 64 grids of
+// blobs 502 -> 305 us, of 0.4% random cells 355 -> 313 us).  The one loss known
+// is that of 64 grids of 2% random cells, whose halo bits are nearly all set:
+// 400 -> 427 us, the 23 us of building them.  Cone steps
 // gain from the smallest batches on (they also lose a separate expansion of
 // the ray indices; cascades 94 -> 55 us at 256 rays, 434 -> 175 us at
 // 262,144; contraction 135 -> 63 and 1,281 -> 258 us) unless a few rays are
@@ -2541,7 +2601,9 @@ void launch_count_box(const uint32_t* halo, const uint32_t* holes, int64_t, hipS
                       const float* d, const int32_t* gid, int64_t n, const uint32_t* bits, const GridK& g,
                       const ClipK& c, const StepK& p, int32_t* packed, int64_t* sums, uint64_t* masks, int n_masks) {
     const int rays = segment_rays(n, n_masks);
-    hipLaunchKernelGGL(p.max_per_ray > 0 ? count_box_kernel<true> : count_box_kernel<false>,
+    const bool cap = p.max_per_ray > 0, spread = g.n_grids > 1;
+    hipLaunchKernelGGL(cap ? (spread ? count_box_kernel<true, true> : count_box_kernel<true, false>)
+                           : (spread ? count_box_kernel<false, true> : count_box_kernel<false, false>),
                        dim3(static_cast<unsigned>((n + rays - 1) / rays)), dim3(kTaskThreads), box_lds(rays, n_masks),
                        s, o, d, gid, n, bits, halo, holes, g, c, p, n_masks, rays, packed, sums, masks);
 }

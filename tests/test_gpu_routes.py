@@ -357,3 +357,21 @@ def test_box_count_in_turns(n_rays, res, dt, p_occ, cap):
     mask[:res // 4, :, ::3] = 0
     o, d = synth.rays_toward_origin(n_rays, 72)
     compare(o, d, mask.reshape(-1), res, BOX, 0.0, 1e10, dt, max_per_ray=cap)
+
+
+@pytest.mark.parametrize("res,dt,p_occ,cap", [
+    (16, 0.0009, 0.05, 0), (16, 0.0009, 0.97, 70),  # windows of stored chunks
+    (8, 0.02, 1.0, 0), (16, 0.03, 0.3, 0), (32, 0.0137, 0.5, 9), (64, 0.004, 0.1, 0),  # segments of 8 to 32
+    (64, 0.05, 0.5, 0),                             # rays too fast for segments
+])
+@pytest.mark.parametrize("n_rays,n_grids", [(1, 2), (70, 3), (4100, 7), (19000, 3)])
+def test_box_count_of_several_grids(res, dt, p_occ, cap, n_rays, n_grids):
+    """Lookups of eight runs a load: rays of different grids in a wave, some
+    with no grid; full and partly filled rounds; 1 to 4 rays a wave."""
+    if dt < 0.001:
+        n_rays = min(n_rays, 300)
+    mask = synth.random_mask(n_grids * res ** 3, p_occ, 29)
+    o, d = synth.rays_toward_origin(n_rays, 73)
+    gid = np.random.default_rng(7).integers(-1, n_grids + 1, n_rays).astype(np.int32)
+    gid[0] = n_grids - 1
+    compare(o, d, mask, res, BOX, 0.0, 1e10, dt, max_per_ray=cap, n_grids=n_grids, grid_id=gid)
