@@ -7,6 +7,7 @@
 //   sample_cells Philox4x64-10 per sample -> cell, jittered position
 //   update_max   atomic max on the FP32 bit patterns (order-independent)
 //   pack         one ballot per wavefront -> two 32-bit words of bits
+#include <algorithm>
 #include <cmath>
 
 #include "common.h"
@@ -152,7 +153,8 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const float* __restrict_
 // z and y in one launch, those along x in planes of constant y in another.
 // Bound by latency (a few dependent LDS reads per cell and axis): four grids
 // of 128^3 cells 5.6 + 3.6 us, 3.3 + 3 x 5.5 us with a launch for the occupancy and
-// one per axis, each reading its window from memory; larger grids still are.
+// one per axis, each reading its window from memory; larger grids, and many
+// small ones (by_planes), still are.
 
 // Coarse occupancy: one lane per coarse cell, 16 fine-row reads (the 4 bits
 // of a row lie in one word since 4 | res).
@@ -216,35 +218,47 @@ __device__ __forceinline__ uint8_t axis_distance(const uint8_t* plane, int i, in
 }
 
 constexpr int kPlaneCells = 128;
-constexpr int kPlaneThreads = 1024;
+constexpr int kPlaneThreads = 1024;  // at most; a thread a cell of smaller planes
+
+int plane_threads(int c) { return std::min(kPlaneThreads, (c * c + kWave - 1) / kWave * kWave); }
+
+// A workgroup a plane pays while the plane has some 128 cells, or the
+// workgroups are few enough to be there at once.  Build of the buffer by planes
+// and by the passes per axis: 64 grids of 64^3 cells 16 and 27 us, of 16^3 15 and
+// 20; 512 grids of 48^3 45 and 55 us; 1,024 of 16^3 27 and 24, 2,048 of 32^3 84 and
+// 70, 8,192 of 16^3 154 and 84.  A launch holds less than 2^32 threads.
+bool by_planes(int c, int64_t planes) {
+    return c <= kPlaneCells && (c * c >= 128 || planes <= 2048) &&
+           planes * plane_threads(c) < (int64_t{1} << 32);
+}
 
 // Workgroup grid c + x: occupancy, then distances along z and y.
 __global__ __launch_bounds__(kPlaneThreads) void skip_planes_kernel(const uint32_t* __restrict__ bits, int res,
                                                                     uint32_t words, uint8_t* __restrict__ out) {
     __shared__ uint8_t a[kPlaneCells * kPlaneCells], b[kPlaneCells * kPlaneCells];
-    const int c = res / 4, n = c * c;
+    const int c = res / 4, n = c * c, n_threads = static_cast<int>(blockDim.x);
     const int x = static_cast<int>(blockIdx.x) % c;
     const uint32_t* fine = bits + static_cast<int64_t>(blockIdx.x / static_cast<unsigned>(c)) * words;
-    for (int i = threadIdx.x; i < n; i += kPlaneThreads) {
+    for (int i = threadIdx.x; i < n; i += n_threads) {
         a[i] = coarse_occupied(fine, res, x, i / c, i % c) ? 0 : NACC_SKIP_CAP;
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < n; i += kPlaneThreads) b[i] = axis_distance(a, i, i % c, c, 1);
+    for (int i = threadIdx.x; i < n; i += n_threads) b[i] = axis_distance(a, i, i % c, c, 1);
     __syncthreads();
     uint8_t* dst = out + static_cast<int64_t>(blockIdx.x) * n;
-    for (int i = threadIdx.x; i < n; i += kPlaneThreads) dst[i] = axis_distance(b, i, i / c, c, c);
+    for (int i = threadIdx.x; i < n; i += n_threads) dst[i] = axis_distance(b, i, i / c, c, c);
 }
 
 // Workgroup grid c + y: distances along x.
 __global__ __launch_bounds__(kPlaneThreads) void skip_x_kernel(const uint8_t* __restrict__ in, int c,
                                                                uint8_t* __restrict__ out) {
     __shared__ uint8_t a[kPlaneCells * kPlaneCells];
-    const int n = c * c;
+    const int n = c * c, n_threads = static_cast<int>(blockDim.x);
     const int64_t first = static_cast<int64_t>(blockIdx.x / static_cast<unsigned>(c)) * n * c +
                           static_cast<int64_t>(blockIdx.x % static_cast<unsigned>(c)) * c;
-    for (int i = threadIdx.x; i < n; i += kPlaneThreads) a[i] = in[first + static_cast<int64_t>(i / c) * n + i % c];
+    for (int i = threadIdx.x; i < n; i += n_threads) a[i] = in[first + static_cast<int64_t>(i / c) * n + i % c];
     __syncthreads();
-    for (int i = threadIdx.x; i < n; i += kPlaneThreads) {
+    for (int i = threadIdx.x; i < n; i += n_threads) {
         out[first + static_cast<int64_t>(i / c) * n + i % c] = axis_distance(a, i, i / c, c, c);
     }
 }
@@ -349,13 +363,14 @@ int nacc_grid_build_skip(const uint32_t* bits, const nacc_grid_desc* grid, uint8
     uint8_t* scratch = skip + n;
     hipStream_t s = as_stream(stream);
     uint32_t* halo = reinterpret_cast<uint32_t*>(skip + halo_offset(grid->res, grid->n_grids));
-    if (c <= kPlaneCells) {
-        const dim3 planes(static_cast<unsigned>(static_cast<int64_t>(c) * grid->n_grids));
-        hipLaunchKernelGGL(skip_planes_kernel, planes, dim3(kPlaneThreads), 0, s, bits, grid->res,
+    const int64_t n_planes = static_cast<int64_t>(c) * grid->n_grids;
+    if (by_planes(c, n_planes)) {
+        const dim3 planes(static_cast<unsigned>(n_planes)), threads(static_cast<unsigned>(plane_threads(c)));
+        hipLaunchKernelGGL(skip_planes_kernel, planes, threads, 0, s, bits, grid->res,
                            static_cast<uint32_t>(cells / 32), scratch);
         int st = check_launch("grid skip planes");
         if (st != NACC_OK) return st;
-        hipLaunchKernelGGL(skip_x_kernel, planes, dim3(kPlaneThreads), 0, s, scratch, c, field);
+        hipLaunchKernelGGL(skip_x_kernel, planes, threads, 0, s, scratch, c, field);
         st = check_launch("grid skip distance");
         if (st != NACC_OK) return st;
         launch_halo(bits, grid->res, grid->n_grids, halo, nullptr, s);

@@ -375,3 +375,49 @@ def test_box_count_of_several_grids(res, dt, p_occ, cap, n_rays, n_grids):
     gid = np.random.default_rng(7).integers(-1, n_grids + 1, n_rays).astype(np.int32)
     gid[0] = n_grids - 1
     compare(o, d, mask, res, BOX, 0.0, 1e10, dt, max_per_ray=cap, n_grids=n_grids, grid_id=gid)
+
+
+def _check_skip(nacc, res, n, mask):
+    """Distances and halo bits of n grids, against scipy (as above), for as
+    many different ones as `mask` [m, res, res, res] holds, repeated."""
+    from scipy.ndimage import distance_transform_cdt, maximum_filter
+    m = mask.shape[0]
+    lib = nacc._lib
+    desc = lib.grid_desc(BOX[:3], BOX[3:], res, n)
+    words = np.packbits(mask.reshape(m, -1), axis=1, bitorder="little").view(np.int32)
+    bits = _cuda(words).repeat(-(-n // m), 1)[:n].reshape(-1)
+    buf = torch.full((lib.grid_skip_bytes(desc),), 77, dtype=torch.uint8, device="cuda")
+    lib.grid_build_skip(bits, desc, buf)
+    c, h = res // 4, res // 2
+    hw = -(-h ** 3 // 64) * 8  # bytes of a grid's halo bits
+    field = buf[:n * c ** 3].view(n, -1)
+    halo = buf[-(-2 * c ** 3 * n // 256) * 256:].view(n, hw)
+    want_f = np.empty((m, c ** 3), np.uint8)
+    want_h = np.zeros((m, hw), np.uint8)
+    for i in range(m):
+        coarse = mask[i].reshape(c, 4, c, 4, c, 4).any(axis=(1, 3, 5))
+        far = distance_transform_cdt(~coarse, metric="chessboard") if coarse.any() else np.full(coarse.shape, 15)
+        want_f[i] = np.minimum(far, 15).ravel()
+        near = maximum_filter(mask[i].astype(bool), size=5, mode="constant").reshape(h, 2, h, 2, h, 2)
+        b = np.packbits(near.any(axis=(1, 3, 5)).ravel(), bitorder="little")
+        want_h[i, :b.size] = b
+    for got, want, name in ((field, want_f, "distances"), (halo, want_h, "halo bits")):
+        w = _cuda(want).repeat(-(-n // m), 1)[:n]
+        assert torch.equal(got, w), f"{name} of {n} grids of {res}^3"
+
+
+@pytest.mark.parametrize("res,n", [(4, 1), (4, 2048), (4, 2049), (4, 300001), (8, 3), (8, 1024), (8, 1025), (16, 512),
+                                   (16, 513), (32, 256), (32, 257), (44, 186), (44, 187), (48, 187)])
+def test_skip_buffer_of_many_small_grids(res, n):
+    """Either side of the number of planes up to which small grids are built
+    plane by plane; grids of one word a plane and less."""
+    mask = np.stack([synth.random_mask(res ** 3, p, 90 + i).reshape(res, res, res)
+                     for i, p in enumerate((0.0, 1.0, 0.5, 4 / res ** 3, 1 / res ** 3, 1 / res ** 3, 0.02))])
+    _check_skip(_nacc(), res, n, mask)
+
+
+def test_skip_buffer_of_very_many_grids():
+    """4.2 million grids of 4^3 cells: as many planes, past 2^32 threads with
+    1,024 a plane."""
+    mask = np.stack([synth.random_mask(64, p, 97 + i).reshape(4, 4, 4) for i, p in enumerate((0.02, 0.0, 0.3))])
+    _check_skip(_nacc(), 4, (1 << 22) + 5, mask)
