@@ -67,7 +67,7 @@ struct SegWalk {
     bool last = false;  // the current block is the ray's last
 };
 
-template <int LOOKUP, bool PER_SET, bool SEG>
+template <int LOOKUP, bool PER_SET, bool SEG, bool FAR>
 __device__ __forceinline__ void render_ray_fused(int64_t r, const RaySpan& span, const SegRay& sg,
                                                  const float* __restrict__ table,
                                                  int n_blobs, int n_sets, const int32_t* __restrict__ ray_set,
@@ -205,21 +205,26 @@ __device__ __forceinline__ void render_ray_fused(int64_t r, const RaySpan& span,
             t1 = t_near + static_cast<float>(k + 1) * p.dt;
         }
         {
-            // the chunk's samples lie within `reach` of the point halfway
-            // between its ends (the contraction brings points no farther
-            // apart), with the rounding of t and of the positions, a few
-            // ulps of the largest coordinate each, taken generously
-            const float ta = uniform<float>(t0), tb = read_lane(t1, n_chunk - 1);
-            const float tc = 0.5f * (ta + tb);
-            float c0 = o[0] + d[0] * tc, c1 = o[1] + d[1] * tc, c2 = o[2] + d[2] * tc;
-            to_scene(contract, c0, c1, c2);
-            const float far = ray_size * (fabsf(ta) + fabsf(tb) + 1.0f);
-            const float reach = 0.5f * (tb - ta) * d_norm + far * 0x1p-18f;
             float x0 = midpoint_coord(o[0], d[0], t0, t1);
             float x1 = midpoint_coord(o[1], d[1], t0, t1);
             float x2 = midpoint_coord(o[2], d[2], t0, t1);
             to_scene(contract, x0, x1, x2);
-            const float s = eval_near(blobs, n_blobs, c0, c1, c2, reach, x0, x1, x2);
+            float s;
+            if (!FAR) {
+                eval_field(table, n_blobs, set, x0, x1, x2, s);
+            } else {
+                // the chunk's samples lie within `reach` of the point halfway
+                // between its ends (the contraction brings points no farther
+                // apart), with the rounding of t and of the positions, a few
+                // ulps of the largest coordinate each, taken generously
+                const float ta = uniform<float>(t0), tb = read_lane(t1, n_chunk - 1);
+                const float tc = 0.5f * (ta + tb);
+                float c0 = o[0] + d[0] * tc, c1 = o[1] + d[1] * tc, c2 = o[2] + d[2] * tc;
+                to_scene(contract, c0, c1, c2);
+                const float far = ray_size * (fabsf(ta) + fabsf(tb) + 1.0f);
+                const float reach = 0.5f * (tb - ta) * d_norm + far * 0x1p-18f;
+                s = eval_near(blobs, n_blobs, c0, c1, c2, reach, x0, x1, x2);
+            }
             if (valid) {
                 sigma = s;
                 eval_rgb(cc, x0, x1, x2, cr, cg, cb);
@@ -259,7 +264,7 @@ __device__ __forceinline__ void render_ray_fused(int64_t r, const RaySpan& span,
 // clocks (nullable): the device wall clock when the workgroup started and
 // when its last wave finished, per workgroup.
 // group: rays per workgroup, kFusedWaves to kFusedRays.
-template <int LOOKUP, bool PER_SET, bool SEG>
+template <int LOOKUP, bool PER_SET, bool SEG, bool FAR>
 __global__ __launch_bounds__(kFusedWaves * kWave) void fused_render_kernel(
     const float* __restrict__ table, int n_blobs, int n_sets, const int32_t* __restrict__ ray_set,
     const float* __restrict__ rays_o, const float* __restrict__ rays_d, const int32_t* __restrict__ grid_id,
@@ -290,8 +295,9 @@ __global__ __launch_bounds__(kFusedWaves * kWave) void fused_render_kernel(
         const RaySpan span = read_span(spans, i / kFusedWaves);
         if (!span.valid) continue;
         const SegRay sg = read_seg(seg_logs, span, g, i / kFusedWaves);
-        render_ray_fused<LOOKUP, PER_SET, SEG>(r, span, sg, table, n_blobs, n_sets, ray_set, rays_o, rays_d, bits, halo,
-                                               g, p, eps, rings[wave], lists[wave], color, opacity, depth, kept);
+        render_ray_fused<LOOKUP, PER_SET, SEG, FAR>(r, span, sg, table, n_blobs, n_sets, ray_set, rays_o, rays_d, bits,
+                                                    halo, g, p, eps, rings[wave], lists[wave], color, opacity, depth,
+                                                    kept);
     }
     if (clocks != nullptr) {
         __syncthreads();
@@ -312,21 +318,28 @@ int fused_group(int64_t n_rays) {
     return n_rays < 40000 ? 4 : (n_rays < 160000 ? 8 : (n_rays < 400000 ? 16 : 32));
 }
 
+// Blobs from which on the far ones are left out of a chunk (either way gives
+// the same bits): that costs a distance per blob and lane and a walk over the
+// bits of the near ones.  262,144 rays, blobs of 0.1 to 0.3 in a box of 3: 1 blob
+// 145 us with, 134 without; 8 blobs 271 and 248; 16 347 and 355; 32 434 and 525;
+// 100 1,623 and 2,180.  Blobs that reach across the whole box lose by it at any
+// number (16 of radius 1 to 2 370 and 327 us); telling them apart in the kernel cost
+// the narrow ones 1 to 3%.
+constexpr int kFarBlobs = 16;
+
 template <int LOOKUP, bool SEG>
 void launch_fused_seg(bool per_set, int group, hipStream_t s, const float* table, int n_blobs, int n_sets,
                       const int32_t* ray_set, const float* o, const float* d, const int32_t* gid, int64_t n,
                       const uint32_t* bits, const uint32_t* halo, const GridK& g, const ClipK& c, const StepK& p,
                       float eps, float* color, float* opacity, float* depth, int32_t* kept, uint64_t* clocks) {
     const unsigned nb = static_cast<unsigned>((n + group - 1) / group);
-    if (per_set) {
-        hipLaunchKernelGGL((fused_render_kernel<LOOKUP, true, SEG>), dim3(nb), dim3(kFusedWaves * kWave), 0, s,
-                           table, n_blobs, n_sets, ray_set, o, d, gid, n, bits, halo, g, c, p, eps, color, opacity,
-                           depth, kept, clocks, group);
-    } else {
-        hipLaunchKernelGGL((fused_render_kernel<LOOKUP, false, SEG>), dim3(nb), dim3(kFusedWaves * kWave), 0, s,
-                           table, n_blobs, n_sets, ray_set, o, d, gid, n, bits, halo, g, c, p, eps, color, opacity,
-                           depth, kept, clocks, group);
-    }
+    const bool far = n_blobs >= kFarBlobs;
+    auto kernel = per_set ? (far ? fused_render_kernel<LOOKUP, true, SEG, true>
+                                 : fused_render_kernel<LOOKUP, true, SEG, false>)
+                          : (far ? fused_render_kernel<LOOKUP, false, SEG, true>
+                                 : fused_render_kernel<LOOKUP, false, SEG, false>);
+    hipLaunchKernelGGL(kernel, dim3(nb), dim3(kFusedWaves * kWave), 0, s, table, n_blobs, n_sets, ray_set, o, d, gid, n,
+                       bits, halo, g, c, p, eps, color, opacity, depth, kept, clocks, group);
 }
 
 }  // namespace

@@ -421,3 +421,24 @@ def test_skip_buffer_of_very_many_grids():
     1,024 a plane."""
     mask = np.stack([synth.random_mask(64, p, 97 + i).reshape(4, 4, 4) for i, p in enumerate((0.02, 0.0, 0.3))])
     _check_skip(_nacc(), 4, (1 << 22) + 5, mask)
+
+
+@pytest.mark.parametrize("n_blobs", [1, 15, 16])
+@pytest.mark.parametrize("n_sets", [1, 3])
+def test_fused_few_blobs(n_blobs, n_sets):
+    """Either side of the number of blobs from which far ones are left out,
+    with one set of centres and with several."""
+    nacc = _nacc()
+    scene = synth.moving_blob_scene(n_blobs, n_sets, 75) if n_sets > 1 else synth.blob_scene(n_blobs, 75)
+    grid = nacc.OccupancyGrid(synth.BOX_1_5, 32)
+    grid.set_occupancy(torch.ones(32 ** 3), 0.5)
+    field = nacc.BlobField(scene)
+    o, d = (_cuda(a) for a in synth.rays_toward_origin(1500, 76, jitter_std=0.4))
+    ray_set = torch.arange(1500, dtype=torch.int32, device="cuda") % n_sets if n_sets > 1 else None
+    packed, ri, ts, te = nacc.ray_marching(o, d, grid, 0.0, 1e10, 0.01)
+    sig, rgb = field.samples(o, d, ri, ts, te, ray_set)
+    color, opacity, depth = nacc.rendering(packed, ts, te, sig, rgb, early_stop_eps=1e-4)
+    got = nacc.render_fused(field, o, d, grid, 0.0, 1e10, 0.01, 1e-4, ray_set=ray_set)
+    assert float(opacity.max()) > 0.5
+    for g, want in zip(got, (color, opacity, depth)):
+        assert torch.equal(g.reshape(-1).view(torch.int32), want.reshape(-1).view(torch.int32))
