@@ -6,6 +6,7 @@
 
 #include <cstdint>
 
+#include "launch_rows.h"
 #include "nacc.h"
 
 namespace nacc {
@@ -18,6 +19,13 @@ void clear_error();
 int check_launch(const char* what);
 // Launch parameters picked by the caller or the autotuner (nacc_set_tuning).
 const nacc_tuning& tuning();
+
+// Grid of `blocks` workgroups; kernels number them by row_block() of
+// row_blocks(), and find no work past the last one.
+inline dim3 grid_rows(int64_t blocks, int threads) {
+    const LaunchRows l = launch_rows(blocks, threads);
+    return dim3(l.length, l.rows);
+}
 
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
@@ -70,6 +78,12 @@ namespace dev {
 __device__ __forceinline__ int lane_id() {
     return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
 }
+
+__device__ __forceinline__ int64_t row_block() {
+    return static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
+}
+
+__device__ __forceinline__ int64_t row_blocks() { return static_cast<int64_t>(gridDim.y) * gridDim.x; }
 
 __device__ __forceinline__ uint64_t ballot(bool p) {
     return __builtin_amdgcn_ballot_w64(p);

@@ -275,7 +275,7 @@ __global__ __launch_bounds__(kFusedWaves * kWave) void fused_render_kernel(
     __shared__ uint8_t lists[kFusedWaves][SEG ? kWave : 1];
     const uint64_t t_start = clocks != nullptr ? wall_clock64() : 0ull;
     const int wave = uniform<int>(static_cast<int>(threadIdx.x) / kWave);
-    const int64_t first = static_cast<int64_t>(blockIdx.x) * group;
+    const int64_t first = row_block() * group;
     // this wave's rays are first + wave + j kFusedWaves; lane j clips ray j
     const int64_t mine = first + wave + static_cast<int64_t>(lane_id()) * kFusedWaves;
     RaySpan spans{};
@@ -301,9 +301,9 @@ __global__ __launch_bounds__(kFusedWaves * kWave) void fused_render_kernel(
     }
     if (clocks != nullptr) {
         __syncthreads();
-        if (threadIdx.x == 0) {
-            clocks[2 * blockIdx.x] = t_start;
-            clocks[2 * blockIdx.x + 1] = wall_clock64();
+        if (threadIdx.x == 0 && first < n_rays) {
+            clocks[2 * row_block()] = t_start;
+            clocks[2 * row_block() + 1] = wall_clock64();
         }
     }
 }
@@ -332,14 +332,13 @@ void launch_fused_seg(bool per_set, int group, hipStream_t s, const float* table
                       const int32_t* ray_set, const float* o, const float* d, const int32_t* gid, int64_t n,
                       const uint32_t* bits, const uint32_t* halo, const GridK& g, const ClipK& c, const StepK& p,
                       float eps, float* color, float* opacity, float* depth, int32_t* kept, uint64_t* clocks) {
-    const unsigned nb = static_cast<unsigned>((n + group - 1) / group);
     const bool far = n_blobs >= kFarBlobs;
     auto kernel = per_set ? (far ? fused_render_kernel<LOOKUP, true, SEG, true>
                                  : fused_render_kernel<LOOKUP, true, SEG, false>)
                           : (far ? fused_render_kernel<LOOKUP, false, SEG, true>
                                  : fused_render_kernel<LOOKUP, false, SEG, false>);
-    hipLaunchKernelGGL(kernel, dim3(nb), dim3(kFusedWaves * kWave), 0, s, table, n_blobs, n_sets, ray_set, o, d, gid, n,
-                       bits, halo, g, c, p, eps, color, opacity, depth, kept, clocks, group);
+    hipLaunchKernelGGL(kernel, grid_rows((n + group - 1) / group, kFusedWaves * kWave), dim3(kFusedWaves * kWave), 0, s,
+                       table, n_blobs, n_sets, ray_set, o, d, gid, n, bits, halo, g, c, p, eps, color, opacity, depth, kept, clocks, group);
 }
 
 }  // namespace

@@ -616,7 +616,7 @@ __global__ __launch_bounds__(kFillThreads) void fill_uniform_kernel(
     __shared__ FillLds lds[kFillWaves];
     const int lane = lane_id();
     const int wave = uniform<int>(static_cast<int>(threadIdx.x) / kWave);
-    const int64_t first = (xcd_grouped<16>(blockIdx.x, gridDim.x) * kFillWaves + wave) * per;
+    const int64_t first = (xcd_grouped<16>(row_block(), row_blocks()) * kFillWaves + wave) * per;
     const int n_mine = static_cast<int>(max(min(static_cast<int64_t>(per), n_rays - first), int64_t{0}));
     FillLds& q = lds[wave];
     const FillOut out{ray_indices, t_starts, t_ends};
@@ -1794,7 +1794,7 @@ __global__ __launch_bounds__(kTaskThreads) void count_box_kernel(
     const int lane = lane_id();
     const int wave = uniform<int>(static_cast<int>(threadIdx.x) / kWave);
     uint32_t* const q = reinterpret_cast<uint32_t*>(s_masks + rays * stride) + wave * kSegStack;
-    const int64_t first = static_cast<int64_t>(blockIdx.x) * rays;
+    const int64_t block = row_block(), first = block * rays;
     if (static_cast<int>(threadIdx.x) < rays) {  // in the first wave
         const int64_t r = first + threadIdx.x;
         RaySpan span{};
@@ -2003,10 +2003,10 @@ __global__ __launch_bounds__(kTaskThreads) void count_box_kernel(
     const int sum = wave_sum(count);  // <= 16 * 2^24 fits int32
     if (lane == 0) wave_total[wave] = sum;
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 0 && first < n_rays) {
         int64_t s = 0;
         for (int w = 0; w < kTaskWaves; ++w) s += wave_total[w];
-        block_sums[blockIdx.x] = s;
+        block_sums[block] = s;
     }
 }
 
@@ -2562,7 +2562,7 @@ void launch_fill_uniform(const uint8_t* skip, int64_t nb, hipStream_t s, const f
                          int32_t* status, const uint64_t* masks, int n_masks) {
     const int per = fill_rays(n, n_masks);
     const int64_t rays = static_cast<int64_t>(per) * kFillWaves;
-    hipLaunchKernelGGL((fill_uniform_kernel<LOOKUP, SKIP>), dim3(static_cast<unsigned>((n + rays - 1) / rays)),
+    hipLaunchKernelGGL((fill_uniform_kernel<LOOKUP, SKIP>), grid_rows((n + rays - 1) / rays, kFillThreads),
                        dim3(kFillThreads), 0, s, o, d, gid, n, bits, skip, g, c, p, packed, capacity, ri, ts, te,
                        status, masks, n_masks, per);
 }
@@ -2604,7 +2604,7 @@ void launch_count_box(const uint32_t* halo, const uint32_t* holes, int64_t, hipS
     const bool cap = p.max_per_ray > 0, spread = g.n_grids > 1;
     hipLaunchKernelGGL(cap ? (spread ? count_box_kernel<true, true> : count_box_kernel<true, false>)
                            : (spread ? count_box_kernel<false, true> : count_box_kernel<false, false>),
-                       dim3(static_cast<unsigned>((n + rays - 1) / rays)), dim3(kTaskThreads), box_lds(rays, n_masks),
+                       grid_rows((n + rays - 1) / rays, kTaskThreads), dim3(kTaskThreads), box_lds(rays, n_masks),
                        s, o, d, gid, n, bits, halo, holes, g, c, p, n_masks, rays, packed, sums, masks);
 }
 
