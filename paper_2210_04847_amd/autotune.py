@@ -8,6 +8,10 @@ descent over the knobs on the caller's real workload: each candidate is timed
 with HIP events over a few steps and accepted only if the step's outputs are
 bit-identical to those of the reference setting (a candidate that changed a
 result would be a bug, and is rejected).
+
+march_waves_per_group acts on uniform steps marched without halo bits (small
+batches and the nested and contracted lookups); leave it out of the candidates
+of other steps.
 """
 from __future__ import annotations
 

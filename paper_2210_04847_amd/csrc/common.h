@@ -20,6 +20,10 @@ int check_launch(const char* what);
 // Launch parameters picked by the caller or the autotuner (nacc_set_tuning).
 const nacc_tuning& tuning();
 
+// Whether the count pass of such a marching call follows
+// tuning().march_waves_per_group: uniform steps without halo bits.
+bool march_follows_waves(int64_t n_rays, const nacc_grid_desc& grid, const nacc_march_params& params, bool has_skip);
+
 // Grid of `blocks` workgroups; kernels number them by row_block() of
 // row_blocks(), and find no work past the last one.
 inline dim3 grid_rows(int64_t blocks, int threads) {

@@ -2750,6 +2750,13 @@ int march_count_launch(const float* rays_o, const float* rays_d, const int32_t* 
 
 }  // namespace
 
+bool nacc::march_follows_waves(int64_t n_rays, const nacc_grid_desc& grid, const nacc_march_params& params,
+                               bool has_skip) {
+    if (params.cone > 0.0f) return false;
+    const Layout l = workspace_layout(n_rays, grid, params);
+    return grid.lookup != NACC_LOOKUP_AABB || l.n_masks == 0 || !(has_skip || l.halo_off != 0);
+}
+
 extern "C" {
 
 int64_t nacc_march_workspace_size(int64_t n_rays, const nacc_grid_desc* grid, const nacc_march_params* params) {

@@ -270,6 +270,7 @@ int autotune(nacc_plan* p, int repeats, nacc_tuning* best_out, float* best_ms_ou
     static const std::vector<int> kValues[4] = {
         {1, 2, 4, 8, 16}, {1, 2, 3, 4}, {4096, 8192, 16384, 65536}, {0, 1}};
     const bool training = p->d.target != nullptr;
+    const bool waves = march_follows_waves(p->d.n_rays, p->d.grid, p->d.params, p->d.grid_skip != nullptr);
     nacc_tuning best;
     nacc_get_tuning(&best);
     hipEvent_t a = nullptr, b = nullptr;
@@ -283,6 +284,7 @@ int autotune(nacc_plan* p, int repeats, nacc_tuning* best_out, float* best_ms_ou
     for (int round = 0; round < 2; ++round)
     for (int knob = 0; st == NACC_OK && knob < 4; ++knob) {
         if (!training && knob >= 1) break;  // the rendering knobs act on the fused loss kernel only
+        if (!waves && knob == 0) continue;  // the step's count pass does not follow it
         for (int v : kValues[knob]) {
             if (v == get_knob(best, knob)) continue;
             nacc_tuning trial = best;

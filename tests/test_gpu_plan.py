@@ -335,3 +335,21 @@ def test_after_stage_runs_last(dyn):
             assert _same(copied[:e], want) and _same(st.g_sigmas[:e], want)
     finally:
         plan.close()
+
+
+@pytest.mark.parametrize("waves", [2, 16])
+def test_plan_autotune_leaves_unused_settings(dyn, waves):
+    """A step whose count pass goes by halo bits does not follow the waves per
+    group: the tuner keeps what it finds."""
+    w, inp = dyn
+    import paper_2210_04847_amd as nacc
+    lib = nacc._lib
+    base = lib.get_tuning()
+    plan = _step(w, inp, skip_field=True).plan()
+    try:
+        lib.set_tuning(march_waves_per_group=waves)
+        best, _ = plan.autotune(repeats=2)
+        assert best["march_waves_per_group"] == waves
+    finally:
+        plan.close()
+        lib.set_tuning(**base)
