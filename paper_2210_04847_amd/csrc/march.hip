@@ -182,10 +182,9 @@ struct ChunkMasks {
 // masks as one chunk at a time.
 template <int LOOKUP, bool FILL>
 __device__ __forceinline__ int march_ray_uniform_x2(
-    int64_t r, const RaySpan& span, const float* __restrict__ rays_o, const float* __restrict__ rays_d,
-    const uint32_t* __restrict__ bits, const GridK& g, const StepK& p, int64_t start, int limit,
-    int64_t capacity, int32_t* __restrict__ ray_indices, float* __restrict__ t_starts, float* __restrict__ t_ends,
-    bool& overflow, uint64_t* __restrict__ masks, int n_masks, int first_chunk, int count0) {
+    int64_t r, const RaySpan& span, const uint32_t* __restrict__ bits, const GridK& g, const StepK& p, int64_t start,
+    int limit, int64_t capacity, int32_t* __restrict__ ray_indices, float* __restrict__ t_starts,
+    float* __restrict__ t_ends, bool& overflow, uint64_t* __restrict__ masks, int n_masks, int first_chunk, int count0) {
     if (!span.valid) return 0;
     const int lane = lane_id();
     const float* o = span.o;
@@ -264,16 +263,13 @@ __device__ __forceinline__ int march_ray_uniform_x2(
 // over at the cost of its lattice arithmetic.
 template <int LOOKUP, bool FILL, bool SKIP>
 __device__ __forceinline__ int march_ray_uniform(
-    int64_t r, const RaySpan& span, const float* __restrict__ rays_o, const float* __restrict__ rays_d,
-    const uint32_t* __restrict__ bits, const uint8_t* __restrict__ skip,
-    const GridK& g, const StepK& p, int64_t start, int limit, int64_t capacity,
-    int32_t* __restrict__ ray_indices, float* __restrict__ t_starts, float* __restrict__ t_ends,
-    bool& overflow, uint64_t* __restrict__ masks = nullptr, int n_masks = 0, int first_chunk = 0,
+    int64_t r, const RaySpan& span, const uint32_t* __restrict__ bits, const uint8_t* __restrict__ skip,
+    const GridK& g, const StepK& p, int64_t start, int limit, int64_t capacity, int32_t* __restrict__ ray_indices,
+    float* __restrict__ t_starts, float* __restrict__ t_ends, bool& overflow, uint64_t* __restrict__ masks = nullptr, int n_masks = 0, int first_chunk = 0,
     int count0 = 0) {
     if constexpr (!SKIP) {
-        return march_ray_uniform_x2<LOOKUP, FILL>(r, span, rays_o, rays_d, bits, g, p, start, limit, capacity,
-                                                  ray_indices, t_starts, t_ends, overflow, masks, n_masks,
-                                                  first_chunk, count0);
+        return march_ray_uniform_x2<LOOKUP, FILL>(r, span, bits, g, p, start, limit, capacity, ray_indices, t_starts,
+                                                  t_ends, overflow, masks, n_masks, first_chunk, count0);
     }
     if (!span.valid) return 0;
     const int lane = lane_id();
@@ -365,9 +361,8 @@ __global__ __launch_bounds__(WAVES * kWave) void count_uniform_kernel(
         const RaySpan span = read_span(spans, i / WAVES);
         uint64_t* ray_masks = masks != nullptr ? masks + r * n_masks : nullptr;
         const int ray_n_masks = masks != nullptr ? n_masks : 0;
-        const int n = march_ray_uniform<LOOKUP, false, SKIP>(r, span, rays_o, rays_d, bits, skip, g, p, 0, 0, 0,
-                                                             nullptr, nullptr, nullptr, unused, ray_masks,
-                                                             ray_n_masks);
+        const int n = march_ray_uniform<LOOKUP, false, SKIP>(r, span, bits, skip, g, p, 0, 0, 0, nullptr, nullptr,
+                                                             nullptr, unused, ray_masks, ray_n_masks);
         if (lane_id() == 0) packed_info[2 * r + 1] = n;
         total += n;
     }
@@ -698,8 +693,8 @@ __global__ __launch_bounds__(kFillThreads) void fill_uniform_kernel(
         const int written = fill_chunks_checked(r, span.t_near, p.dt, ray_start, ray_limit, capacity, out, overflow,
                                                 mine);
         if (written < ray_limit) {  // samples past the stored chunks: traverse from there
-            march_ray_uniform<LOOKUP, true, SKIP>(r, span, rays_o, rays_d, bits, skip, g, p, ray_start, ray_limit,
-                                                  capacity, ray_indices, t_starts, t_ends, overflow, nullptr, 0,
+            march_ray_uniform<LOOKUP, true, SKIP>(r, span, bits, skip, g, p, ray_start, ray_limit, capacity,
+                                                  ray_indices, t_starts, t_ends, overflow, nullptr, 0,
                                                   masks != nullptr ? n_masks : 0, written);
         }
     }
@@ -1159,12 +1154,12 @@ __global__ __launch_bounds__(kRaysPerBlock) void cone_starts_kernel(
 
 // Occupancy bits of the 64 candidates of one chunk from its first t; `ended`
 // tells whether the ray's candidates stop inside the chunk.
-template <int LOOKUP, bool SKIP>
-__device__ __forceinline__ uint64_t cone_chunk_bits(const uint32_t* __restrict__ bits,
-                                                    const uint8_t* __restrict__ skip, const GridK& g,
-                                                    const SkipRay& sk, float& skip_end, uint32_t word0,
+template <int LOOKUP>
+__device__ __forceinline__ uint64_t cone_chunk_bits(const uint32_t* __restrict__ bits, const GridK& g, uint32_t word0,
                                                     const float o[3], const float d[3], float& t, float t_far,
                                                     const StepK& p, bool& ended) {
+    SkipRay sk{};  // not read
+    float skip_end = -INFINITY;
     uint64_t m = 0ull;
     ended = false;
 #pragma unroll 1
@@ -1172,7 +1167,7 @@ __device__ __forceinline__ uint64_t cone_chunk_bits(const uint32_t* __restrict__
         float tb[kConeBatch + 1];
         const int n_valid = cone_steps(t, t_far, p, tb);
         const uint32_t hits =
-            cone_hits<LOOKUP, SKIP>(bits, skip, g, sk, skip_end, word0, o, d, tb, n_valid) & ((1u << n_valid) - 1u);
+            cone_hits<LOOKUP, false>(bits, nullptr, g, sk, skip_end, word0, o, d, tb, n_valid) & ((1u << n_valid) - 1u);
         m |= static_cast<uint64_t>(hits) << (b * kConeBatch);
         if (n_valid < kConeBatch) {
             ended = true;
@@ -1209,16 +1204,13 @@ __global__ __launch_bounds__(kTaskThreads) void count_cone_chunks_kernel(
     }
     uint32_t word0;
     grid_of_ray<LOOKUP>(grid_id, r, g, word0);  // valid: the ray has candidates
-    SkipRay sk{};
-    float skip_end = -INFINITY;
     bool ended;
-    masks[task] = cone_chunk_bits<LOOKUP, false>(bits, nullptr, g, sk, skip_end, word0, o, d, t, t_far, p, ended);
+    masks[task] = cone_chunk_bits<LOOKUP>(bits, g, word0, o, d, t, t_far, p, ended);
     if (j == n_masks - 1 && !ended) {
         // past the stored chunks: count the rest of the ray here
         int count = 0;
         for (int k0 = n_masks * kWave; k0 < kMaxCandidates; k0 += kWave) {
-            count += __popcll(
-                cone_chunk_bits<LOOKUP, false>(bits, nullptr, g, sk, skip_end, word0, o, d, t, t_far, p, ended));
+            count += __popcll(cone_chunk_bits<LOOKUP>(bits, g, word0, o, d, t, t_far, p, ended));
             if (ended) break;
         }
         extra[r] = count;
@@ -1304,7 +1296,7 @@ __global__ __launch_bounds__(kTaskThreads) void fill_cone_chunks_kernel(
         uint32_t word0;
         grid_of_ray<LOOKUP>(grid_id, r, g, word0);
         SkipRay sk{};
-            float skip_end = -INFINITY;
+        float skip_end = -INFINITY;
         for (int k0 = n_masks * kWave; k0 < kMaxCandidates && idx < limit; k0 += kConeBatch) {
             float tb[kConeBatch + 1];
             const int n_valid = cone_steps(t, t_far, p, tb);
@@ -1723,13 +1715,10 @@ __global__ __launch_bounds__(kTaskThreads) void count_cone_kernel(
         t_more[r] = t_end;
         if (t_end < INFINITY) {
             // past the stored chunks: count the rest of the ray here
-            SkipRay sk{};
-            float skip_end = -INFINITY;
             bool ended = false;
             float t = t_end;
             for (int k0 = n_masks * kWave; k0 < kMaxCandidates && !ended; k0 += kWave) {
-                total += __popcll(cone_chunk_bits<LOOKUP, false>(bits, nullptr, g, sk, skip_end, word0, o, d, t,
-                                                                 t_far, p, ended));
+                total += __popcll(cone_chunk_bits<LOOKUP>(bits, g, word0, o, d, t, t_far, p, ended));
             }
         }
         if (p.max_per_ray > 0) total = min(total, static_cast<int64_t>(p.max_per_ray));
