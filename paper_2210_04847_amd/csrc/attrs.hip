@@ -316,13 +316,21 @@ __global__ __launch_bounds__(kAttrThreads) void attrs_fwd_kernel(
                 if (depth != nullptr) depth[r] = acc_d;
             }
         }
+        auto finish = [&](int k, int ch) {
+            float v = wave_sum1(acc[k]);
+            if (background != nullptr) v += background[ch] * (1.0f - total_a);
+            if (lane == 0) out[r * n_ch + ch] = v;
+        };
+        if (STAGE != 0 || CH < kBlock || c0 + CH <= n_ch) {  // a whole block (or rows of 4 or 8 channels)
 #pragma unroll
-        for (int k = 0; k < CH; ++k) {
-            int ch;
-            if (channel_of<CH>(k, n_ch, c0, ch)) {
-                float v = wave_sum1(acc[k]);
-                if (background != nullptr) v += background[ch] * (1.0f - total_a);
-                if (lane == 0) out[r * n_ch + ch] = v;
+            for (int k = 0; k < CH; ++k) {
+                if (STAGE != 1 || k < n_ch) finish(k, c0 + k);
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < CH; ++k) {
+                int ch;
+                if (channel_of<CH>(k, n_ch, c0, ch)) finish(k, ch);
             }
         }
     }
