@@ -408,7 +408,7 @@ def lattice_candidates(w, rays_o, rays_d):
 RENDER_SOURCES = ("paper_2210_04847_amd/csrc/render.hip+paper_2210_04847_amd/csrc/transmittance.h+"
                   "paper_2210_04847_amd/csrc/common.h")
 MARCH_SOURCES = ("paper_2210_04847_amd/csrc/march.hip+paper_2210_04847_amd/csrc/lattice.h+"
-                 "paper_2210_04847_amd/csrc/halo.h+"
+                 "paper_2210_04847_amd/csrc/halo.h+paper_2210_04847_amd/csrc/fill_list.h+"
                  "paper_2210_04847_amd/csrc/scan.h+paper_2210_04847_amd/csrc/common.h")
 
 

@@ -180,8 +180,10 @@ const char* nacc_status_str(int status);
  * workspace holds the scan's partial sums and one 64-bit occupancy mask per
  * ray and chunk of 64 candidates (enough chunks for the longest chord of the
  * clip box), which let nacc_march_fill write the samples without traversing
- * the grid again; for cone steps the chunks' starts, and, for batches large
- * enough to gain from them, halo bits for a call without a skip buffer. */
+ * the grid again; for cone steps the chunks' starts; and, for batches large
+ * enough to gain from them, halo bits for a call without a skip buffer and,
+ * for uniform steps through the box with or without one, hole bits (the halo
+ * of the empty cells, from which solid parts are known). */
 int64_t nacc_march_workspace_size(int64_t n_rays, const nacc_grid_desc* grid,
                                   const nacc_march_params* params);
 

@@ -50,8 +50,8 @@ __device__ __forceinline__ void eval_field(const float* __restrict__ table, int 
 // adding the product leaves the sum as it is.  `reach` carries the rounding
 // of the positions; the distance to c is lowered by 2^-16 of itself for its
 // own rounding, and -160 leaves 2^11 below the smallest subnormal, 2^-149.
-// (32 blobs of 0.03 to 0.1 in a box of 3: an image of 640,000 rays in 844 ->
-// 734 us.)
+// (32 blobs of 0.03 to 0.1 in a box of 3, 640,000 rays of one view, 64 rays a
+// workgroup: 844 -> 734 us.)
 __device__ __forceinline__ uint64_t near_blobs(const float* __restrict__ blob, int n_blobs, int i, float c0, float c1,
                                                float c2, float reach) {
     const int b = 64 * i + static_cast<int>(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)));

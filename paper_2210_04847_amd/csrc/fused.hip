@@ -312,8 +312,10 @@ __global__ __launch_bounds__(kFusedWaves * kWave) void fused_render_kernel(
 // differ by the samples they hold, so a small image needs many short waves
 // (64 rays against 4: 3,072 rays 116 -> 21 us, 30,000 rays 212 -> 54 us),
 // while a large one gains from what a wave does once for all its rays (4
-// against 32: 640,000 rays 824 -> 675 us).  In between: 120,000 rays 174 us
-// with 8 (16: 177, 4: 185), 226,400 rays 317 us with 16 (8: 324, 32: 337).
+// against 32: 640,000 rays of one view 824 -> 675 us).  In between: 120,000 rays
+// 174 us with 8 (16: 177, 4: 185), 226,400 rays 317 us with 16 (8: 324, 32: 337).
+// (Kernel times, each pair on one view: views of a scene differ by a fifth, 557
+// to 665 us a call at 640,000 rays.)
 int fused_group(int64_t n_rays) {
     return n_rays < 40000 ? 4 : (n_rays < 160000 ? 8 : (n_rays < 400000 ? 16 : 32));
 }

@@ -4,26 +4,31 @@
 // Samples are the lattice intervals of each ray whose midpoint lies in an
 // occupied cell.  Empty space is pruned while marching, so the ragged output
 // is produced by three steps:
-//   count  every ray's sample count, plus one partial sum per workgroup;
-//   scan   exclusive scan of the workgroup sums, then of the counts inside
-//          each workgroup -> packed_info (start, count) and the total;
-//   fill   the same traversal again, writing each sample at its offset.
+//   count   every ray's samples, one sum per part of 4 to 64 rays, and, where a
+//           workspace is given, a 64-bit mask of the samples of every chunk of 64
+//           candidates (the first kMaxMaskChunks of a ray);
+//   starts  exclusive sums of the parts and of the counts inside them ->
+//           packed_info (start, count) and the total (scan.h);
+//   fill    the samples of the masks, at their offsets; without masks, and past
+//           the chunks that have them, the rays are traversed again.
 //
-// Uniform steps: one wavefront per ray, the 64 lanes test 64 consecutive
-// lattice candidates at once, so the 64 grid-word loads of an iteration are
-// independent (they overlap in flight instead of forming a dependent chain)
-// and the 256 KiB bit grid stays resident in the XCD's L2.  A ballot of the
-// occupied lanes gives the count (popcount) and, in the fill pass, each
-// lane's output slot (mbcnt), so the writes of a wave are contiguous.
-//
-// Cone steps: the lattice is a recurrence in t, so one lane walks one ray.
-//
-// Empty space: with a skip field (nacc_grid_build_skip), a test at one
-// candidate's midpoint gives a stretch of t ahead in which every candidate
-// midpoint is sure to fall in empty cells of the same grid level; those
-// candidates are passed over without grid lookups.  The bound allows for
-// the FP32 rounding of positions, so the sample set is exactly the one of
-// the plain traversal.
+// Which kernels run:
+//   uniform steps, box lookup, halo bits (the skip buffer's, or built for the
+//     call, halo.h): count_box_kernel, segments of many rays tested and looked
+//     up together;
+//   other uniform steps: count_uniform_kernel, a wavefront per ray whose lanes
+//     test 64 consecutive candidates at once; the cascades and the contraction
+//     pass over stretches that the skip buffer's distances clear;
+//   every uniform fill: fill_uniform_kernel, up to 8 rays a wave;
+//   cone steps with halo bits: count_cone_kernel (chunks, segments and lookups
+//     of many rays, 64 at a time) and fill_cone_rays_kernel;
+//   cone steps without (a few rays over many grids): a lane per chunk,
+//     cone_starts_kernel, count_cone_chunks_kernel, cone_counts_kernel,
+//     fill_cone_chunks_kernel; without a workspace fill_cone_kernel, a lane per
+//     ray.
+// What a test leaves out is proven empty with the FP32 rounding of positions
+// allowed for, so that every way gives exactly the samples of the plain
+// traversal.
 //
 // All lattice arithmetic follows the FP32 contract in nacc.h: this file is
 // compiled with -ffp-contract=off and `fp contract(off)`, and uses only
@@ -1450,7 +1455,8 @@ constexpr uint32_t kOwnLattice = 1u << 31;
 // one ray per lane (`walks`: the lookup has a clip box, or there is no
 // table), and their segment starts from them.  A stalled step repeats t:
 // the lookups find no candidate there.
-// Bound by VALU issue (95% of the cycles).  262,144 rays of a cascade of 15
+// Bound by VALU issue (84% of a 64-lane instruction per SIMD every 4 clocks on
+// the cascades, 75% with the contraction).  262,144 rays of a cascade of 15
 // chunks (92 segments inside the ray, 55 of kept chunks, 19 looked up, 10
 // holding samples): 129 us, where a pass for the chunk starts, one lane per
 // chunk with the wave's segments looked up together, and one for the counts
@@ -1741,11 +1747,12 @@ __global__ __launch_bounds__(kTaskThreads) void count_cone_kernel(
 // they are counted and stored.  Rays of more candidates than stored chunks
 // are taken in windows of as many, the masks of the first one stored; rays
 // too fast for segments (seg_log 0) look every candidate up.
-// Bound by VALU issue (85% of the cycles): 262,144 rays, 37 segments of 16
-// inside a ray, 21 near occupied cells: 138 us and 5 us for the hole bits,
-// 162 us without them (small blobs; a solid ball of 64 cells across gains
-// more), 208 us with a wave per ray after ray, half of whose lanes tested no
-// segment and a fifth looked no candidate up.
+// Bound by VALU issue (79% of a 64-lane instruction per SIMD every 4 clocks):
+// 262,144 rays, 37 segments of 16 inside a ray, 21 near occupied cells: 131 us and 5 us for the hole bits
+// (138 with a hole bit read for every segment; 162 without hole bits on these
+// small blobs, a solid ball of 64 cells across gains more), 208 us with a wave
+// per ray after ray, half of whose lanes tested no segment and a fifth looked no
+// candidate up.
 // SPREAD (more than one grid): of 64 runs a lane looks up one candidate of
 // eight, so that neighbouring lanes read neighbouring cells, and a ballot
 // holds eight runs' bytes; it reads a ray's data anew where the ray changes.

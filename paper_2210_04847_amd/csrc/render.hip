@@ -880,7 +880,7 @@ __global__ __launch_bounds__(kRenderThreads) void prune_count_kernel(
 // samples of the one before go into a ring in LDS at their output position,
 // from which whole aligned blocks of 64 positions are stored.
 // 8.5 M kept of 33.0 M samples, 262,144 rays: 138 us (a chunk's flags, then its
-// samples, then their stores, one after the other) -> 102 us.
+// samples, then their stores, one after the other) -> 100 us.
 constexpr int kPruneRing = 2 * kWave;
 
 struct PruneRing {
